@@ -16,7 +16,7 @@ CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "lib", "libmalt.so")
 CALIB = os.path.join(PKG, "calib")
 CALIB_LIB = os.path.join(PKG, "lib", "libmalt_calib.so")
-SOURCES = ["malt_api.hip", "elementwise.hip", "ns_sym.hip", "ns_update.hip", "small_ns.hip"]
+SOURCES = ["malt_api.hip", "elementwise.hip", "ns_sym.hip", "ns_update.hip", "ns_mid.hip", "small_ns.hip"]
 ARCH = "gfx950"
 
 

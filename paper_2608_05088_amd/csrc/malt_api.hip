@@ -8,6 +8,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <map>
 #include <mutex>
 #include <string>
 #include <vector>
@@ -49,7 +50,10 @@ struct MatPlan {
   int64_t m, n, mc, nc, mp, np;
   bool tall, split, small;
   int64_t sm_gchunks;                  // fp32 path: Gram partials
-  int64_t k1_ct, k1_rt, k2_tr, k2_tc, k2_tiles, upd_tiles, sym_tiles;
+  int64_t dm, dn;                      // Newton-Schulz domain: mc, nc padded to the largest tile in use
+  int32_t gsplit;                      // parts of the Gram's contraction
+  bool gmid;                           // Gram on the smaller tiles (Layout::tile_gm)
+  int64_t k1_ct, k1_rt, k2_tr, k2_tc, k2_tiles, upd_tiles;
   // offsets
   int64_t st_M, st_l, st_r, st_nu;     // floats from state base
   size_t ws_scal, ws_Lv, ws_Rv, ws_rowpart, ws_colpart, ws_k2part, ws_gpart;
@@ -65,9 +69,14 @@ struct Layout {
   size_t ws_desc = 0, ws_ptrs = 0;
   size_t ws_t_ew = 0, ws_t_fin = 0, ws_t_k2 = 0, ws_t_gram = 0, ws_t_poly = 0, ws_t_upd = 0;
   size_t ws_t_smg = 0, ws_t_smp = 0, ws_t_smu = 0;
-  int64_t n_ew = 0, n_fin = 0, n_k2 = 0, n_sym = 0, n_upd = 0;
+  int64_t n_ew = 0, n_fin = 0, n_k2 = 0;
   int64_t n_k2w = 0;   // scale+convert tiles of wide matrices, listed before those of tall ones
   int64_t n_gram = 0, n_poly = 0, n_updd = 0;   // dispatch-ordered NS lists (padded)
+  // Newton-Schulz tile edge of each phase (64, 128: ns_mid.hip; 256: ns_sym.hip,
+  // ns_update.hip), and of the Gram of the matrices marked gmid.
+  int tile_g = NS_TILE, tile_gm = 0, tile_p = NS_TILE, tile_u = NS_TILE;
+  size_t ws_t_gmid = 0, ws_t_gred = 0;
+  int64_t n_gmid = 0, n_gred = 0;   // smaller-tile Gram list (dispatch order), reduction of the cut ones
   int64_t n_smg = 0, n_smp = 0, n_smu = 0;   // fp32 Newton-Schulz lists
 };
 
@@ -159,51 +168,64 @@ std::vector<Tile> xcd_order(const std::vector<Tile>& list, const std::vector<dou
   return out;
 }
 
-// Gram, polynomial and update lists in dispatch order (the Gram and the
-// polynomial share tiles but not costs: K is n' for one and m' for the other).
-void ns_dispatch_lists(const Layout& L, const std::vector<Tile>& sym, const std::vector<Tile>& upd,
-                       std::vector<Tile>& gram, std::vector<Tile>& poly, std::vector<Tile>& upd_d) {
-  constexpr double kTileFixed = 1.5;   // prologue + epilogue, in stages
-  std::vector<double> cg(sym.size()), cp(sym.size()), cu(upd.size());
-  for (size_t k = 0; k < sym.size(); ++k) {
-    const MatPlan& q = L.mats[sym[k].mat];
-    // A diagonal tile loads one operand panel instead of two.
-    const double f = sym[k].ti == sym[k].tj ? 0.75 : 1.0;
-    cg[k] = f * double(q.np) / NS_BK + kTileFixed;
-    cp[k] = f * double(q.mp) / NS_BK + kTileFixed;
-  }
-  for (size_t k = 0; k < upd.size(); ++k) {
-    const MatPlan& q = L.mats[upd[k].mat];
-    cu[k] = double(q.split ? 2 * q.mp : q.mp) / NS_BK + kTileFixed;
-  }
-  gram = xcd_order(sym, cg);
-  poly = xcd_order(sym, cp);
-  upd_d = xcd_order(upd, cu);
+// Every work list of a plan. The Newton-Schulz lists gram, gmid, poly and upd
+// are in dispatch order (padded with mat = -1).
+struct Lists {
+  std::vector<Tile> ew, fin, k2, gram, gmid, gred, poly, upd, smg, smp, smu;
+};
+
+// Upper tiles (ti <= tj) of matrix i's symmetric products on tile edge T.
+template <class F>
+void upper_tiles(const MatPlan& q, int T, F&& f) {
+  const int32_t n = int32_t(q.dm / T);
+  for (int32_t ti = 0; ti < n; ++ti)
+    for (int32_t tj = ti; tj < n; ++tj) f(ti, tj);
 }
 
-void build_tiles(const Layout& L, std::vector<Tile>& ew, std::vector<Tile>& fin, std::vector<Tile>& k2,
-                 std::vector<Tile>& sym, std::vector<Tile>& upd, std::vector<Tile>& smg, std::vector<Tile>& smp,
-                 std::vector<Tile>& smu) {
+void build_tiles(const Layout& L, Lists& O) {
+  constexpr double kTileFixed = 1.5;   // prologue + epilogue, in stages
   const std::vector<int32_t> ord = cost_order(L);
+  std::vector<Tile> gram, gmid, poly, upd;
+  std::vector<double> cg, cgm, cp, cu;
   for (int32_t i : ord) {
     const MatPlan& q = L.mats[i];
     for (int32_t ti = 0; ti < q.k1_rt; ++ti)
-      for (int32_t tj = 0; tj < q.k1_ct; ++tj) ew.push_back({i, ti, tj, 0});
-    for (int32_t c = 0; c < cdiv(q.m, FIN_W); ++c) fin.push_back({i, 0, c, 0});
-    for (int32_t c = 0; c < cdiv(q.n, FIN_W); ++c) fin.push_back({i, 1, c, 0});
+      for (int32_t tj = 0; tj < q.k1_ct; ++tj) O.ew.push_back({i, ti, tj, 0});
+    for (int32_t c = 0; c < cdiv(q.m, FIN_W); ++c) O.fin.push_back({i, 0, c, 0});
+    for (int32_t c = 0; c < cdiv(q.n, FIN_W); ++c) O.fin.push_back({i, 1, c, 0});
     if (q.small) {
-      for (int32_t c = 0; c < q.sm_gchunks; ++c) smg.push_back({i, c, 0, 0});
-      smp.push_back({i, 0, 0, 0});
-      for (int32_t c = 0; c < q.upd_tiles; ++c) smu.push_back({i, c, 0, c});
+      for (int32_t c = 0; c < q.sm_gchunks; ++c) O.smg.push_back({i, c, 0, 0});
+      O.smp.push_back({i, 0, 0, 0});
+      for (int32_t c = 0; c < q.upd_tiles; ++c) O.smu.push_back({i, c, 0, c});
       continue;
     }
-    const int32_t T = int32_t(q.mp / NS_TILE), TN = int32_t(q.np / NS_TILE);
+    // Costs in 64-k stages. A diagonal tile loads one operand panel, not two.
+    const double kg = double(q.dn) / NS_BK, kp = double(q.dm) / NS_BK;
+    if (q.gmid) {
+      upper_tiles(q, L.tile_gm, [&](int32_t ti, int32_t tj) {
+        for (int32_t k = 0; k < q.gsplit; ++k) {
+          gmid.push_back({i, ti, tj, k});
+          cgm.push_back((ti == tj ? 0.75 : 1.0) * kg / q.gsplit + kTileFixed);
+        }
+        if (q.gsplit > 1)
+          for (int32_t k = 0; k < L.tile_gm / 16; ++k) O.gred.push_back({i, ti, tj, k});
+      });
+    } else {
+      upper_tiles(q, L.tile_g, [&](int32_t ti, int32_t tj) {
+        gram.push_back({i, ti, tj, 0});
+        cg.push_back((ti == tj ? 0.75 : 1.0) * kg + kTileFixed);
+      });
+    }
+    upper_tiles(q, L.tile_p, [&](int32_t ti, int32_t tj) {
+      poly.push_back({i, ti, tj, 0});
+      cp.push_back((ti == tj ? 0.75 : 1.0) * kp + kTileFixed);
+    });
     int32_t idx = 0;
-    for (int32_t ti = 0; ti < T; ++ti)
-      for (int32_t tj = ti; tj < T; ++tj) sym.push_back({i, ti, tj, idx++});
-    idx = 0;
-    for (int32_t tj = 0; tj < TN; ++tj)       // column panel major: neighbours share X^T panels
-      for (int32_t ti = 0; ti < T; ++ti) upd.push_back({i, ti, tj, idx++});
+    for (int32_t tj = 0; tj < q.dn / L.tile_u; ++tj)       // column panel major: neighbours share X^T panels
+      for (int32_t ti = 0; ti < q.dm / L.tile_u; ++ti) {
+        upd.push_back({i, ti, tj, idx++});
+        cu.push_back((q.split ? 2.0 : 1.0) * kp + kTileFixed);
+      }
   }
   // Scale+convert: the wide matrices' tiles, then the tall ones' (two kernels).
   for (int pass = 0; pass < 2; ++pass)
@@ -212,12 +234,225 @@ void build_tiles(const Layout& L, std::vector<Tile>& ew, std::vector<Tile>& fin,
       if (q.tall != (pass == 1)) continue;
       int32_t idx = 0;
       for (int32_t ti = 0; ti < q.k2_tr; ++ti)
-        for (int32_t tj = 0; tj < q.k2_tc; ++tj) k2.push_back({i, ti, tj, idx++});
+        for (int32_t tj = 0; tj < q.k2_tc; ++tj) O.k2.push_back({i, ti, tj, idx++});
     }
+  O.gram = xcd_order(gram, cg);
+  O.gmid = xcd_order(gmid, cgm);
+  O.poly = xcd_order(poly, cp);
+  O.upd = xcd_order(upd, cu);
 }
 
+// ---------------------------------------------------------------------------
+// Newton-Schulz tile edges.  A 256 x 256 tile moves the fewest operand bytes per
+// flop and wins whenever a launch has enough of them to fill 256 CUs; a small
+// set does not (one GPT-2 Small block has 24 Gram tiles), and then smaller
+// tiles finish sooner although each CU runs them less efficiently.  The
+// launch's time is estimated for each edge as
+//     max(sum over tiles of (a * stages + f) / 256 CUs, longest tile b * stages + g)
+// in microseconds, stages of 64 k, with whole rounds of tiles where there are
+// few, and the plan takes the best edges per phase.  a, f: a CU's time per stage
+// and tile with the chip full; b, g: the time of a tile that has a CU to itself.  Measured on sets of 1 to 96 matrices of 256 to 4096 rows (a GPT-2
+// Small block, us per launch, 64 / 128 / 256 tiles: Gram 16 / 35 / 60,
+// polynomial 9 / 15 / 26, update 24 / 24 / 22; the 48 matrices of GPT-2 Small:
+// 119 / 91 / 78, 45 / 40 / 57, 260 / 180 / 130).
+// ---------------------------------------------------------------------------
+struct TileCost {
+  double a, f, b, g;
+};
 
-Layout make_layout(const malt_shape_t* shapes, int32_t n, malt_variant_t variant) {
+TileCost tile_cost(int T, int phase) {
+  if (T == 64) return {0.20, 0.9, 0.22, 3.5};
+  if (T == 128) return {0.62, phase == PH_GRAM ? 1.6 : 2.5, 0.65, 5.0};
+  const double f = phase == PH_POLY ? 10.5 : phase == PH_GRAM ? 7.0 : 6.0;
+  return {1.5, f, 1.3, f};
+}
+
+constexpr int kCUs = 256;
+
+// Tiles of one matrix in one launch: `off` full ones, `diag` diagonal ones
+// (three quarters of the work), each of `stages` stages in `parts` parts.
+struct TileSet {
+  int64_t off, diag;
+  double stages;
+  int32_t parts;
+};
+
+double launch_time(const std::vector<TileSet>& sets, int T, int phase) {
+  const TileCost c = tile_cost(T, phase);
+  const int per_cu = T == 64 ? ns::MidGeom<64>::WPE : T == 128 ? ns::MidGeom<128>::WPE : 1;
+  const int64_t slots = int64_t(kCUs) * per_cu;
+  double sum = 0.0, alone = 0.0, loaded = 0.0;   // all tiles; the longest by itself, beside per_cu - 1 others
+  int64_t n = 0;
+  for (const TileSet& q : sets) {
+    const double work = c.a * q.stages + c.f * q.parts, st = q.stages / q.parts;
+    sum += (q.off + 0.75 * q.diag) * work;
+    alone = std::max(alone, c.b * st + c.g);
+    loaded = std::max(loaded, per_cu * (c.a * st + c.f));
+    n += (q.off + q.diag) * q.parts;
+  }
+  if (n <= kCUs) return n ? alone : 0.0;
+  if (n <= slots) return std::max(sum / kCUs, alone + std::max(0.0, loaded - alone) * double(n - kCUs) / double(slots - kCUs));
+  if (n > 2 * slots) return std::max(alone, sum / kCUs);
+  // A few rounds of tiles, each to the slot free first: long contractions
+  // first, as in the work lists (where a matrix's last tiles are full ones).
+  std::vector<TileSet> order = sets;
+  std::stable_sort(order.begin(), order.end(),
+                   [](const TileSet& x, const TileSet& y) { return x.stages / x.parts > y.stages / y.parts; });
+  std::map<double, int64_t> free_at{{0.0, slots}};   // slots by the time they are free
+  auto place = [&](int64_t count, double t) {
+    while (count > 0) {
+      const auto first = free_at.begin();
+      const double at = first->first;
+      const int64_t k = std::min(count, first->second);
+      if ((first->second -= k) == 0) free_at.erase(first);
+      free_at[at + t] += k;
+      count -= k;
+    }
+  };
+  for (const TileSet& q : order) {
+    const double t = per_cu * (c.a * q.stages / q.parts + c.f);
+    place(q.diag * q.parts, 0.75 * t);
+    place(q.off * q.parts, t);
+  }
+  return std::max(alone, free_at.rbegin()->first);
+}
+
+TileSet sym_tiles_of(int64_t dm, int T, double stages) {
+  const int64_t n = dm / T;
+  return {n * (n - 1) / 2, n, stages, 1};
+}
+
+// Parts for a Gram on smaller tiles whose longest tile would outlast the rest
+// of the launch: enough that no tile takes longer than the launch's work
+// spread over the chip (or 8 us).  The partial tiles lie in the iterate buffer
+// that the update overwrites, and must fit there.
+void split_gram(const Layout& L, std::vector<TileSet>& sets, const std::vector<int32_t>& mats, int T) {
+  const TileCost c = tile_cost(T, PH_GRAM);
+  double sum = 0.0;
+  for (const TileSet& q : sets)
+    sum += q.off * (c.a * q.stages + c.f) + q.diag * (0.75 * c.a * q.stages + c.f);
+  const double limit = std::max(8.0, sum / kCUs);
+  for (size_t k = 0; k < sets.size(); ++k) {
+    TileSet& q = sets[k];
+    if (c.b * q.stages + c.g <= 1.3 * limit) continue;
+    const MatPlan& m = L.mats[mats[k]];
+    const int64_t fit = (2 * m.mp * m.np) / (4 * (q.off + q.diag) * T * T);
+    const int64_t want = int64_t(ceil(c.b * q.stages / (limit - c.g)));
+    q.parts = int32_t(std::max<int64_t>(1, std::min({want, fit, int64_t(q.stages) / 2})));
+  }
+}
+
+// The reduction of the cut matrices' partial tiles: a launch, and the partial
+// tiles written and read once.
+double reduce_time(const std::vector<TileSet>& sets, int T) {
+  double bytes = 0.0;
+  for (const TileSet& q : sets)
+    if (q.parts > 1) bytes += 8.0 * double(T) * T * double(q.off + q.diag) * q.parts;
+  return bytes > 0.0 ? 5.0 + bytes / 4e6 : 0.0;
+}
+
+// Chooses the tile edges and, with the Gram on smaller tiles, the parts of
+// long contractions: the combination with the least estimated time, edges of
+// 256 unless the gain is over 5%.  The domain of every matrix is padded to the
+// largest edge in use, so the three largest edges are compared as wholes.
+void choose_tiles(Layout& L) {
+  std::vector<int32_t> mats;
+  for (size_t i = 0; i < L.mats.size(); ++i) {
+    MatPlan& q = L.mats[i];
+    q.dm = q.mp;
+    q.dn = q.np;
+    q.gsplit = 1;
+    q.gmid = false;
+    if (!q.small) mats.push_back(int32_t(i));
+  }
+  if (mats.empty()) return;
+  struct Choice {
+    int g = NS_TILE, gm = 128, p = NS_TILE, u = NS_TILE, edge = NS_TILE;
+    std::vector<int32_t> parts;   // per entry of mats; 0: not on the smaller Gram tiles
+    double t = 0.0;
+  };
+  Choice best;
+  for (int edge = NS_TILE; edge >= 64; edge /= 2) {
+    Choice c;
+    c.edge = edge;
+    double tg = 0.0, tp = 0.0, tu = 0.0;
+    for (int T = edge; T >= 64; T /= 2) {
+      const double keep = T == edge ? 1.0 : 0.95;
+      std::vector<TileSet> g, p, u;
+      for (int32_t i : mats) {
+        const MatPlan& q = L.mats[i];
+        const int64_t dm = pad_to(q.mc, edge), dn = pad_to(q.nc, edge);
+        const double kp = double(dm) / NS_BK;
+        g.push_back(sym_tiles_of(dm, T, double(dn) / NS_BK));
+        p.push_back(sym_tiles_of(dm, T, kp));
+        u.push_back({(dm / T) * (dn / T), 0, q.split ? 2 * kp : kp, 1});
+      }
+      const double ep = launch_time(p, T, PH_POLY), eu = launch_time(u, T, PH_UPDATE);
+      if (T == edge || ep < keep * tp) { c.p = T; tp = ep; }
+      if (T == edge || eu < keep * tu) { c.u = T; tu = eu; }
+      const std::vector<TileSet> whole = g;
+      const double eg = launch_time(whole, T, PH_GRAM);
+      if (T == edge || eg < keep * tg) {
+        c.g = T;
+        c.gm = T;
+        c.parts.assign(mats.size(), T == NS_TILE ? 0 : 1);
+        tg = eg;
+      }
+      if (T == NS_TILE) {
+        // Long matrices cut on 128-tiles beside the others on 256-tiles.
+        double sum = 0.0;
+        const TileCost tc = tile_cost(T, PH_GRAM);
+        for (const TileSet& q : whole) sum += q.off * (tc.a * q.stages + tc.f) + q.diag * (0.75 * tc.a * q.stages + tc.f);
+        std::vector<TileSet> rest, cut;
+        std::vector<int32_t> cm, where;
+        for (size_t k = 0; k < mats.size(); ++k) {
+          const MatPlan& q = L.mats[mats[k]];
+          if (tc.b * whole[k].stages + tc.f > 2.0 * std::max(sum / kCUs, 20.0)) {
+            cut.push_back(sym_tiles_of(q.dm, 128, whole[k].stages));
+            cm.push_back(mats[k]);
+            where.push_back(int32_t(k));
+          } else {
+            rest.push_back(whole[k]);
+          }
+        }
+        if (!cut.empty()) {
+          split_gram(L, cut, cm, 128);
+          const double e = launch_time(rest, NS_TILE, PH_GRAM) + launch_time(cut, 128, PH_GRAM) + reduce_time(cut, 128) + 5.0;
+          if (e < 0.95 * tg) {
+            c.gm = 128;
+            tg = e;
+            for (size_t k = 0; k < cut.size(); ++k) c.parts[where[k]] = cut[k].parts;
+          }
+        }
+      } else {
+        split_gram(L, g, mats, T);
+        const double e = launch_time(g, T, PH_GRAM) + reduce_time(g, T);
+        if (e < 0.95 * tg) {
+          c.g = c.gm = T;
+          tg = e;
+          for (size_t k = 0; k < mats.size(); ++k) c.parts[k] = g[k].parts;
+        }
+      }
+    }
+    c.t = tg + tp + tu;
+    // At the same edges per phase the smaller domain has less to do.
+    const bool same = std::max({best.g, best.gm, best.p, best.u}) <= edge;
+    if (edge == NS_TILE || c.t < (same ? 1.001 : 0.95) * best.t) best = c;
+  }
+  L.tile_g = best.g;
+  L.tile_gm = best.gm;
+  L.tile_p = best.p;
+  L.tile_u = best.u;
+  for (size_t k = 0; k < mats.size(); ++k) {
+    MatPlan& q = L.mats[mats[k]];
+    q.dm = pad_to(q.mc, best.edge);
+    q.dn = pad_to(q.nc, best.edge);
+    q.gmid = best.parts[k] > 0;
+    q.gsplit = std::max(1, best.parts[k]);
+  }
+}
+
+Layout make_layout(const malt_shape_t* shapes, int32_t n, malt_variant_t variant, Lists& T) {
   Layout L;
   L.mats.resize(n);
   // State: [M... | l... | r... | nu...], float32, unpadded.
@@ -244,25 +479,17 @@ Layout make_layout(const malt_shape_t* shapes, int32_t n, malt_variant_t variant
     if (p.tall) { p.k2_tr = p.np / K2_T; p.k2_tc = p.mp / K2_T; }
     else { p.k2_tr = p.mp / K2W_R; p.k2_tc = p.np / EW_TC; }
     p.k2_tiles = p.k2_tr * p.k2_tc;
-    const int64_t T = p.mp / NS_TILE;
-    // fp32 path: no matrix-core tiles; the update's partial slots are its
-    // column chunks.
-    p.sym_tiles = p.small ? 0 : T * (T + 1) / 2;
-    p.upd_tiles = p.small ? p.np / SM_CH_U : T * (p.np / NS_TILE);
     p.ns_flops_sym_per_iter = 3.0 * double(p.mc) * p.mc * p.nc + double(p.mc) * p.mc * p.mc;
     L.n_ew += p.k1_rt * p.k1_ct;
     L.n_fin += cdiv(p.m, FIN_W) + cdiv(p.n, FIN_W);
     L.n_k2 += p.k2_tiles;
     if (!p.tall) L.n_k2w += p.k2_tiles;
-    if (p.small) {
-      L.n_smg += p.sm_gchunks;
-      L.n_smp += 1;
-      L.n_smu += p.upd_tiles;
-    } else {
-      L.n_sym += p.sym_tiles;
-      L.n_upd += p.upd_tiles;
-    }
   }
+  choose_tiles(L);
+  for (MatPlan& p : L.mats)
+    // fp32 path: no matrix-core tiles; the update's partial slots are its
+    // column chunks.
+    p.upd_tiles = p.small ? p.np / SM_CH_U : (p.dm / L.tile_u) * (p.dn / L.tile_u);
   size_t off = 0;
   auto take = [&](size_t bytes) { const size_t o = off; off = align256(off + bytes); return o; };
   L.ws_desc = take(sizeof(MatDesc) * n);
@@ -272,14 +499,19 @@ Layout make_layout(const malt_shape_t* shapes, int32_t n, malt_variant_t variant
   L.ws_t_k2 = take(sizeof(Tile) * L.n_k2);
   {
     // The padded lengths of the dispatch-ordered lists depend on the costs.
-    std::vector<Tile> ew, fin, k2, sym, upd, smg, smp, smu, gram, poly, updd;
-    build_tiles(L, ew, fin, k2, sym, upd, smg, smp, smu);
-    ns_dispatch_lists(L, sym, upd, gram, poly, updd);
-    L.n_gram = int64_t(gram.size());
-    L.n_poly = int64_t(poly.size());
-    L.n_updd = int64_t(updd.size());
+    build_tiles(L, T);
+    L.n_gram = int64_t(T.gram.size());
+    L.n_gmid = int64_t(T.gmid.size());
+    L.n_gred = int64_t(T.gred.size());
+    L.n_poly = int64_t(T.poly.size());
+    L.n_updd = int64_t(T.upd.size());
+    L.n_smg = int64_t(T.smg.size());
+    L.n_smp = int64_t(T.smp.size());
+    L.n_smu = int64_t(T.smu.size());
   }
   L.ws_t_gram = take(sizeof(Tile) * L.n_gram);
+  L.ws_t_gmid = take(sizeof(Tile) * L.n_gmid);
+  L.ws_t_gred = take(sizeof(Tile) * L.n_gred);
   L.ws_t_poly = take(sizeof(Tile) * L.n_poly);
   L.ws_t_upd = take(sizeof(Tile) * L.n_updd);
   L.ws_t_smg = take(sizeof(Tile) * L.n_smg);
@@ -457,6 +689,8 @@ void fill_desc(const malt_plan* p, std::vector<MatDesc>& D) {
     d.scal = reinterpret_cast<double*>(w + q.ws_scal);
     d.small = q.small ? 1 : 0;
     d.sm_gchunks = int32_t(q.sm_gchunks);
+    d.dm = int32_t(q.dm); d.dn = int32_t(q.dn);
+    d.gsplit = q.gsplit;
     for (int b = 0; b < 2; ++b) d.Xs[b] = q.small ? reinterpret_cast<float*>(w + q.ws_Xs[b]) : nullptr;
     d.Ap = q.small ? reinterpret_cast<float*>(w + q.ws_Ap) : nullptr;
     d.Bs = q.small ? reinterpret_cast<float*>(w + q.ws_Bs) : nullptr;
@@ -482,7 +716,8 @@ malt_status_t check_init_args(const malt_shape_t* shapes, int32_t n, malt_varian
 // resuming), and synchronises the stream.  Allocates no device or pinned host
 // memory.
 malt_status_t init_plan(malt_plan* p, const malt_shape_t* shapes, int32_t n, malt_variant_t variant,
-                        void* state_mem, char* ws, int32_t from_existing, int64_t step, void* stream) {
+                        const Lists& T, void* state_mem, char* ws, int32_t from_existing, int64_t step,
+                        void* stream) {
   if (ranges_overlap(reinterpret_cast<uintptr_t>(state_mem), p->L.state_bytes, reinterpret_cast<uintptr_t>(ws),
                      p->L.ws_bytes))
     return fail(MALT_ERR_ALIAS, "state and workspace buffers overlap");
@@ -499,25 +734,23 @@ malt_status_t init_plan(malt_plan* p, const malt_shape_t* shapes, int32_t n, mal
 
   std::vector<MatDesc> D;
   fill_desc(p, D);
-  std::vector<Tile> ew, fin, k2, sym, upd, smg, smp, smu;
-  build_tiles(p->L, ew, fin, k2, sym, upd, smg, smp, smu);
-  std::vector<Tile> gram, poly, updd;
-  ns_dispatch_lists(p->L, sym, upd, gram, poly, updd);
-
   // Every table in one host image of the workspace head.
-  const size_t head = p->L.ws_t_smu + sizeof(Tile) * smu.size();
+  const size_t head = p->L.ws_t_smu + sizeof(Tile) * T.smu.size();
   std::vector<char> h(head, 0);
   char* hc = h.data();
+  auto put = [&](size_t off, const std::vector<Tile>& v) { memcpy(hc + off, v.data(), sizeof(Tile) * v.size()); };
   memcpy(hc + p->L.ws_desc, D.data(), sizeof(MatDesc) * n);
-  memcpy(hc + p->L.ws_t_ew, ew.data(), sizeof(Tile) * ew.size());
-  memcpy(hc + p->L.ws_t_fin, fin.data(), sizeof(Tile) * fin.size());
-  memcpy(hc + p->L.ws_t_k2, k2.data(), sizeof(Tile) * k2.size());
-  memcpy(hc + p->L.ws_t_gram, gram.data(), sizeof(Tile) * gram.size());
-  memcpy(hc + p->L.ws_t_poly, poly.data(), sizeof(Tile) * poly.size());
-  memcpy(hc + p->L.ws_t_upd, updd.data(), sizeof(Tile) * updd.size());
-  memcpy(hc + p->L.ws_t_smg, smg.data(), sizeof(Tile) * smg.size());
-  memcpy(hc + p->L.ws_t_smp, smp.data(), sizeof(Tile) * smp.size());
-  memcpy(hc + p->L.ws_t_smu, smu.data(), sizeof(Tile) * smu.size());
+  put(p->L.ws_t_ew, T.ew);
+  put(p->L.ws_t_fin, T.fin);
+  put(p->L.ws_t_k2, T.k2);
+  put(p->L.ws_t_gram, T.gram);
+  put(p->L.ws_t_gmid, T.gmid);
+  put(p->L.ws_t_gred, T.gred);
+  put(p->L.ws_t_poly, T.poly);
+  put(p->L.ws_t_upd, T.upd);
+  put(p->L.ws_t_smg, T.smg);
+  put(p->L.ws_t_smp, T.smp);
+  put(p->L.ws_t_smu, T.smu);
 
   e = launch_zero_fill(p->ws, p->L.ws_bytes, s);
   if (e == hipSuccess) e = hipMemcpyAsync(p->ws, hc, head, hipMemcpyHostToDevice, s);
@@ -569,13 +802,103 @@ struct BoundsCheck {
   }
 };
 
-malt_status_t check_bounds(const Layout& L, int64_t shrink, int64_t* checked) {
+// Tile lists of the smaller-tile kernels (ns_mid.hip): direct-load spans over
+// each tile's part of the contraction, partial tiles, outputs.
+template <int T>
+bool check_mid(BoundsCheck& B, int phase, const std::vector<Tile>& list, const std::vector<Tile>& reduce) {
+  using G = ns::MidGeom<T>;
+  using ML = ns::MidLoads<T>;
+  const uint64_t u2 = 2;
+  const char* kname = phase == PH_GRAM ? "ns_mid_gram" : phase == PH_POLY ? "ns_mid_poly" : "ns_mid_update";
+  const Layout& L = B.L;
+  if (!B.cond(list.size() % NXCD == 0, kname, Tile{-1, 0, 0, 0}, "dispatch list not a multiple of the XCDs"))
+    return false;
+  auto rk_span = [](int row0, uint64_t ld) {
+    uint64_t v = 0;
+    for (int g = 0; g < ML::PER_OPER; ++g)
+      for (int lane = 0; lane < 64; ++lane) v = std::max(v, ML::voff_rk(g, lane, row0, int(ld)));
+    return v + 16;
+  };
+  auto kn_span = [](int col0, uint64_t np) {
+    uint64_t v = 0;
+    for (int g = 0; g < ML::PER_OPER; ++g)
+      for (int lane = 0; lane < 64; ++lane) v = std::max(v, ML::voff_kn(g, lane, col0, int(np)));
+    return v + 16;
+  };
+  for (const Tile& t : list) {
+    if (t.mat < 0) continue;   // padding: the workgroup returns at once
+    if (!B.mat_ok(kname, t)) return false;
+    const MatPlan& q = L.mats[t.mat];
+    const int n = int(q.dm / T), row0 = t.ti * T, col0 = t.tj * T;
+    if (!B.cond(!q.small && q.dm % T == 0 && q.dn % T == 0 && q.dm <= q.mp && q.dn <= q.np && q.mc <= q.dm &&
+                    q.nc <= q.dn,
+                kname, t, "domain is not whole tiles of the padded matrix"))
+      return false;
+    if (phase == PH_UPDATE) {
+      if (!B.cond(t.ti >= 0 && t.ti < n && t.tj >= 0 && t.tj < q.dn / T && t.idx >= 0 && t.idx < q.upd_tiles, kname, t,
+                  "tile outside the matrix or partial slot out of range"))
+        return false;
+      const int ldb = int(q.split ? 2 * q.mp : q.mp), KH = int(q.dm / G::BK), KT = q.split ? 2 * KH : KH;
+      uint64_t sx = 0, sb = 0;
+      for (int kt = 0; kt < KT; ++kt) {
+        sb = std::max(sb, ML::soff_b(kt, KH, int(q.mp)));
+        sx = std::max(sx, ML::soff_x(kt, KH, int(q.np)));
+      }
+      if (!B.range(kname, "B' rows", t, 0, rk_span(row0, ldb) + sb, u2 * q.mp * ldb, true) ||
+          !B.range(kname, "X k-rows", t, 0, kn_span(col0, q.np) + sx, u2 * q.mp * q.np, true) ||
+          !B.range(kname, "X' tile", t, u2 * (uint64_t(row0) * q.np + col0),
+                   u2 * (uint64_t(row0 + T - 1) * q.np + col0 + T), u2 * q.mp * q.np) ||
+          !B.range(kname, "graft partials", t, 8 * uint64_t(t.idx), 8 * uint64_t(t.idx) + 8, 8 * uint64_t(q.upd_tiles)))
+        return false;
+      continue;
+    }
+    const int S = phase == PH_GRAM ? q.gsplit : 1;
+    const int ld = int(phase == PH_GRAM ? q.np : q.mp), KT = int((phase == PH_GRAM ? q.dn : q.dm) / G::BK);
+    const int ke = ns::mid_k0(t.idx + 1, S, KT);
+    if (!B.cond(t.ti >= 0 && t.ti <= t.tj && t.tj < n && t.idx >= 0 && t.idx < S &&
+                    ns::mid_k0(t.idx, S, KT) < ke && ke <= KT,
+                kname, t, "not an upper tile of the matrix or an empty part of the contraction"))
+      return false;
+    const uint64_t panel = rk_span(std::max(row0, col0), ld) + ML::soff_rk(ke - 1);
+    if (!B.range(kname, "operand panels", t, 0, panel, u2 * q.mp * ld, true)) return false;
+    if (S > 1) {
+      const uint64_t p0 = 4 * ns::mid_part(t.ti, t.tj, t.idx, n, S, T);
+      if (!B.range(kname, "partial tile", t, p0, p0 + 4 * T * T, u2 * q.mp * q.np)) return false;
+      continue;
+    }
+    const uint64_t ldo = (phase == PH_POLY && q.split) ? 2 * q.mp : q.mp, off = ldo - q.mp;
+    const uint64_t far = uint64_t(std::max(row0, col0)) + T;
+    if (!B.range(kname, "output (tile and mirror)", t, u2 * (uint64_t(std::min(row0, col0)) * ldo),
+                 u2 * ((far - 1) * ldo + off + far), u2 * q.mp * ldo))
+      return false;
+    // The tile of the last diagonal position also writes B' = a I past the domain.
+    if (phase == PH_POLY && t.ti == t.tj && t.ti == n - 1 && q.dm < q.mp &&
+        !B.range(kname, "B' on the padding", t, u2 * (uint64_t(q.dm) * ldo + q.dm),
+                 u2 * (uint64_t(q.mp - 1) * ldo + off + q.mp), u2 * q.mp * ldo))
+      return false;
+  }
+  for (const Tile& t : reduce) {
+    if (!B.mat_ok("ns_mid_reduce", t)) return false;
+    const MatPlan& q = L.mats[t.mat];
+    const int n = int(q.dm / T);
+    if (!B.cond(q.gmid && q.gsplit > 1 && t.ti >= 0 && t.ti <= t.tj && t.tj < n && t.idx >= 0 && t.idx < T / 16,
+                "ns_mid_reduce", t, "not a piece of an upper tile of a cut Gram"))
+      return false;
+    const uint64_t p0 = 4 * (ns::mid_part(t.ti, t.tj, 0, n, q.gsplit, T) + uint64_t(t.idx) * 16 * T);
+    const uint64_t far = uint64_t(t.tj + 1) * T;
+    if (!B.range("ns_mid_reduce", "partial tiles", t, p0, p0 + 4 * (uint64_t(q.gsplit - 1) * T * T + 16 * T),
+                 u2 * q.mp * q.np) ||
+        !B.range("ns_mid_reduce", "A (piece and mirror)", t, 0, u2 * ((far - 1) * q.mp + far), u2 * q.mp * q.mp))
+      return false;
+  }
+  return true;
+}
+
+malt_status_t check_bounds(const Layout& L, const Lists& W, int64_t shrink, int64_t* checked) {
   using UL = ns::UpdLoads<ns::UpdGeom>;
   constexpr int NW = ns::NW, LANES = 64;
   BoundsCheck B{L, shrink};
-  std::vector<Tile> ew, fin, k2, sym, upd, smg, smp, smu, gram, poly, updd;
-  build_tiles(L, ew, fin, k2, sym, upd, smg, smp, smu);
-  ns_dispatch_lists(L, sym, upd, gram, poly, updd);
+  const std::vector<Tile>&ew = W.ew, &fin = W.fin, &k2 = W.k2, &smg = W.smg, &smp = W.smp, &smu = W.smu;
   const uint64_t u2 = 2, u4 = 4;
 
   // Workspace regions lie inside the workspace, in order, without overlap.
@@ -683,7 +1006,8 @@ malt_status_t check_bounds(const Layout& L, int64_t shrink, int64_t* checked) {
   // whole contraction, the polynomial's reload of A's tile, and the stores of
   // the tile and its mirror.
   for (int phase = 0; phase < 2; ++phase) {
-    const std::vector<Tile>& list = phase == 0 ? gram : poly;
+    if ((phase == 0 ? L.tile_g : L.tile_p) != NS_TILE) continue;
+    const std::vector<Tile>& list = phase == 0 ? W.gram : W.poly;
     const char* kname = phase == 0 ? "ns_gram" : "ns_poly";
     if (!B.cond(list.size() % NXCD == 0, kname, Tile{-1, 0, 0, 0}, "dispatch list not a multiple of the XCDs"))
       return B.st;
@@ -729,6 +1053,7 @@ malt_status_t check_bounds(const Layout& L, int64_t shrink, int64_t* checked) {
   }
   // Newton-Schulz update: B' rows and X k-rows over the contraction (X's k
   // wraps at mp for split matrices), the X' tile, the graft partial slot.
+  const std::vector<Tile> no_tiles, &updd = L.tile_u == NS_TILE ? W.upd : no_tiles;
   if (!B.cond(updd.size() % NXCD == 0, "ns_update", Tile{-1, 0, 0, 0}, "dispatch list not a multiple of the XCDs"))
     return B.st;
   for (const Tile& t : updd) {
@@ -757,6 +1082,15 @@ malt_status_t check_bounds(const Layout& L, int64_t shrink, int64_t* checked) {
                  8 * uint64_t(q.upd_tiles)))
       return B.st;
   }
+  // The smaller tiles.
+  if (!(L.tile_gm == 64 ? check_mid<64>(B, PH_GRAM, W.gmid, W.gred) : check_mid<128>(B, PH_GRAM, W.gmid, W.gred)))
+    return B.st;
+  if (L.tile_p != NS_TILE && !(L.tile_p == 64 ? check_mid<64>(B, PH_POLY, W.poly, no_tiles)
+                                              : check_mid<128>(B, PH_POLY, W.poly, no_tiles)))
+    return B.st;
+  if (L.tile_u != NS_TILE && !(L.tile_u == 64 ? check_mid<64>(B, PH_UPDATE, W.upd, no_tiles)
+                                              : check_mid<128>(B, PH_UPDATE, W.upd, no_tiles)))
+    return B.st;
   // fp32 Newton-Schulz of short sides <= 32: chunk and partial-slot indices.
   for (const Tile& t : smg) {
     if (!B.mat_ok("sm_gram", t)) return B.st;
@@ -806,7 +1140,8 @@ malt_status_t malt_state_size(const malt_shape_t* shapes, int32_t n, malt_varian
   if (!state_bytes || !workspace_bytes) return fail(MALT_ERR_INVALID_ARG, "output pointer is NULL");
   malt_status_t st = check_shapes(shapes, n);
   if (st != MALT_OK) return st;
-  const Layout L = make_layout(shapes, n, variant);
+  Lists T;
+  const Layout L = make_layout(shapes, n, variant, T);
   *state_bytes = L.state_bytes;
   *workspace_bytes = L.ws_bytes;
   return MALT_OK;
@@ -823,8 +1158,9 @@ malt_status_t malt_init_state(malt_plan_t** out, const malt_shape_t* shapes, int
   if (reinterpret_cast<uintptr_t>(workspace_mem) % 256 != 0)
     return fail(MALT_ERR_ALIGNMENT, "workspace_mem must be 256-byte aligned");
   malt_plan* p = new malt_plan();
-  p->L = make_layout(shapes, n, variant);
-  st = init_plan(p, shapes, n, variant, state_mem, static_cast<char*>(workspace_mem), from_existing, step, stream);
+  Lists T;
+  p->L = make_layout(shapes, n, variant, T);
+  st = init_plan(p, shapes, n, variant, T, state_mem, static_cast<char*>(workspace_mem), from_existing, step, stream);
   if (st != MALT_OK) { delete p; return st; }
   *out = p;
   return MALT_OK;
@@ -837,7 +1173,8 @@ malt_status_t malt_init_state_scratch(malt_plan_t** out, const malt_shape_t* sha
   *out = nullptr;
   malt_status_t st = check_init_args(shapes, n, variant, state_mem, from_existing, step);
   if (st != MALT_OK) return st;
-  Layout L = make_layout(shapes, n, variant);
+  Lists T;
+  Layout L = make_layout(shapes, n, variant, T);
   if (L.ws_bytes > MALT_SCRATCH_BYTES)
     return fail(MALT_ERR_SCRATCH_SIZE, "these shapes need a %zu-byte workspace; the static scratch holds %llu bytes "
                 "(use malt_init_state with a caller-allocated workspace)", L.ws_bytes,
@@ -852,7 +1189,7 @@ malt_status_t malt_init_state_scratch(malt_plan_t** out, const malt_shape_t* sha
   p->scratch = true;
   p->device = dev;
   p->scratch_gen = gen;
-  st = init_plan(p, shapes, n, variant, state_mem, ws, from_existing, step, stream);
+  st = init_plan(p, shapes, n, variant, T, state_mem, ws, from_existing, step, stream);
   if (st != MALT_OK) { delete p; return st; }
   *out = p;
   return MALT_OK;
@@ -985,16 +1322,18 @@ malt_status_t malt_step(malt_plan_t* p, float* const* params, const float* const
       na.first = it == 0;
       na.last = it == hp->ns_steps - 1;
       na.src = it & 1;
-      if (p->L.n_sym > 0) {   // matrix-core path
-        na.tiles = tiles_at(p->L.ws_t_gram); na.ntiles = int32_t(p->L.n_gram);
-        na.phase = PH_GRAM;
-        MALT_LAUNCH(4, launch_ns_gemm(na, s));
-        na.tiles = tiles_at(p->L.ws_t_poly); na.ntiles = int32_t(p->L.n_poly);
-        na.phase = PH_POLY;
-        MALT_LAUNCH(5, launch_ns_gemm(na, s));
-        na.tiles = tiles_at(p->L.ws_t_upd); na.ntiles = int32_t(p->L.n_updd);
-        na.phase = PH_UPDATE;
-        MALT_LAUNCH(6, launch_ns_gemm(na, s));
+      if (p->L.n_poly > 0) {   // matrix-core path
+        auto ns = [&](int phase, int tile, size_t off, int64_t count) {
+          na.phase = phase;
+          na.tiles = tiles_at(off);
+          na.ntiles = int32_t(count);
+          return tile == NS_TILE ? launch_ns_gemm(na, s) : launch_ns_mid(na, tile, s);
+        };
+        if (p->L.n_gram > 0) MALT_LAUNCH(4, ns(PH_GRAM, p->L.tile_g, p->L.ws_t_gram, p->L.n_gram));
+        if (p->L.n_gmid > 0) MALT_LAUNCH(4, ns(PH_GRAM, p->L.tile_gm, p->L.ws_t_gmid, p->L.n_gmid));
+        if (p->L.n_gred > 0) MALT_LAUNCH(4, ns(PH_REDUCE, p->L.tile_gm, p->L.ws_t_gred, p->L.n_gred));
+        MALT_LAUNCH(5, ns(PH_POLY, p->L.tile_p, p->L.ws_t_poly, p->L.n_poly));
+        MALT_LAUNCH(6, ns(PH_UPDATE, p->L.tile_u, p->L.ws_t_upd, p->L.n_updd));
       }
       if (p->L.n_smp > 0) {   // fp32 path of the small matrices
         na.tiles = tiles_at(p->L.ws_t_smg); na.ntiles = int32_t(p->L.n_smg);
@@ -1038,8 +1377,9 @@ malt_status_t malt_check_bounds(const malt_shape_t* shapes, int32_t n, malt_vari
   *ranges_checked = 0;
   malt_status_t st = check_shapes(shapes, n);
   if (st != MALT_OK) return st;
-  const Layout L = make_layout(shapes, n, variant);
-  return check_bounds(L, shrink_bytes, ranges_checked);
+  Lists T;
+  const Layout L = make_layout(shapes, n, variant, T);
+  return check_bounds(L, T, shrink_bytes, ranges_checked);
 }
 
 malt_status_t malt_state_layout(const malt_plan_t* p, int32_t i, malt_state_layout_t* out) {

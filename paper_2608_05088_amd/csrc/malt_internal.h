@@ -110,6 +110,10 @@ struct MatDesc {
   // fp32 Newton-Schulz (short side <= NS_SMALL_MAX); null otherwise
   int32_t small;       // 1: this matrix takes the fp32 path
   int32_t sm_gchunks;  // Gram partial count
+  // Newton-Schulz domain: canonical dims rounded up to the plan's largest
+  // Newton-Schulz tile (<= mp, np); no Newton-Schulz kernel works past it
+  int32_t dm, dn;
+  int32_t gsplit;      // parts of the Gram's contraction (1: not cut)
   float* Xs[2];        // canonical mc x np fp32 iterate (row pitch np)
   float* Ap;           // [sm_gchunks][32][32] Gram partials
   float* Bs;           // [32][32] B'
@@ -129,13 +133,15 @@ struct PtrPair {
 //   scale+convert: (mat, row tile, col tile, partial slot)
 //   NS: (mat, tile row, tile col, partial slot), stored in dispatch order:
 //       entry b runs on XCD b % 8; mat = -1 pads the shorter XCD runs
+//       On the smaller tiles a Gram's idx is its part of the contraction;
+//       reduction of the parts: (mat, tile row, tile col, 16-row piece)
 //   fp32 NS: Gram (mat, chunk, -, -), polynomial (mat, -, -, -),
 //            update (mat, chunk, -, partial slot)
 struct Tile {
   int32_t mat, ti, tj, idx;
 };
 
-enum { PH_GRAM = 0, PH_POLY = 1, PH_UPDATE = 2 };
+enum { PH_GRAM = 0, PH_POLY = 1, PH_UPDATE = 2, PH_REDUCE = 3 };
 
 struct EwArgs {
   const MatDesc* desc;
@@ -188,6 +194,7 @@ hipError_t ns_gemm_setup();   // once per plan, on the plan's device
 hipError_t launch_ns_gemm(const NsArgs& a, hipStream_t s);
 hipError_t ns_update_setup();   // the update kernel (ns_update.hip), called by ns_gemm_setup
 hipError_t launch_ns_update(const NsArgs& a, hipStream_t s);
+hipError_t launch_ns_mid(const NsArgs& a, int tile, hipStream_t s);   // 64 or 128 tiles, all phases (ns_mid.hip)
 hipError_t launch_small_ns(const NsArgs& a, hipStream_t s);
 
 // XCDs of the chip; workgroups are dispatched to them round-robin.

@@ -2,9 +2,10 @@
 // cores (bf16 operands, fp32 accumulation): the tile geometry, operand
 // addressing, direct-to-LDS loads and the software pipeline.  The symmetric
 // Gram / polynomial kernel (ns_sym.hip) and the update kernel (ns_update.hip)
-// each instantiate the pipeline with their own stage geometry (NsGeom).
+// each instantiate the pipeline with their own stage geometry (NsGeom); the
+// kernels of smaller tiles (ns_mid.hip) have a pipeline of their own.
 //
-// Every kernel: one 256 x 256 output tile per workgroup of 8 waves (2 per
+// The two 256-tile kernels: one 256 x 256 output tile per workgroup of 8 waves (2 per
 // SIMD), each wave owning a 128 x 64 sub-tile as 16x16 blocks of
 // v_mfma_f32_16x16x32_bf16 (under the chip's power budget this shape sustains
 // a higher rate than 32x32x16 with random operands).  Operand stages of BK
@@ -110,6 +111,48 @@ using SymGeom = NsGeom<64, 2, 32>;    // Gram (ns_sym.hip)
 using PolyGeom = NsGeom<64, 2, 32>;   // polynomial (ns_sym.hip)
 using UpdGeom = NsGeom<64, 2, 32>;   // update (ns_update.hip)
 
+// Stage geometry of the smaller tiles (ns_mid.hip): one T x T output tile (T =
+// 64 or 128) per workgroup of 4 waves in a 2 x 2 grid, 64-k stages (128-byte
+// row pieces: with 32-k stages, 64-byte pieces, the 128-tile ran 15% slower).
+// The ring is as deep as keeps WPE workgroups on a CU: three 16 KB slots and
+// three workgroups for the 64-tile (five slots and two: 6% slower), two 32 KB
+// slots and two workgroups for the 128-tile.
+template <int T_>
+struct MidGeom {
+  static constexpr int T = T_;
+  static constexpr int NW = 4, NT = 64 * NW;                  // waves, threads per workgroup
+  static constexpr int WT = T / 2;                            // wave sub-tile edge
+  static constexpr int BK = 64;
+  static constexpr int STAGES = T == 128 ? 2 : 3;
+  static constexpr int WPE = T == 128 ? 2 : 3;                // workgroups per CU, waves per SIMD
+  static constexpr int H = BK / 32;                           // MFMA sub-steps per stage
+  static constexpr int NMMA = (WT / 16) * (WT / 16);          // MFMAs per wave per sub-step
+  static constexpr int RB = BK * 2;
+  static constexpr int CPR = BK / 8;
+  static constexpr int RPP = 256 / RB;
+  static constexpr int OPER_BYTES = T * BK * 2;
+  static constexpr int STAGE_BYTES = 2 * OPER_BYTES;
+  static constexpr int RING_BYTES = STAGES * STAGE_BYTES;
+  static constexpr int LOADS = STAGE_BYTES / 1024 / NW;       // 1 KB direct loads per wave per stage
+  static_assert(WPE * RING_BYTES <= 160 * 1024 && RING_BYTES <= 64 * 1024, "LDS of the workgroups of a CU");
+  static_assert(T == 64 || T == 128, "tile sizes of the mid kernels");
+  static_assert(LOADS * NW * 1024 == STAGE_BYTES, "loads must split evenly over the waves");
+  // [row][k] tile, as NsGeom::swz_rk.
+  __host__ __device__ static constexpr int swz_rk(int row, int kc) {
+    return row * RB + ((kc ^ ((row / RPP) % CPR)) << 4);
+  }
+  // [k][n] tile: rows of T bf16.  As swz_chunk for T = 128, whose 256-byte row
+  // spans every bank.  Two rows of a 64-tile share the banks' period: rows k
+  // and k + 1 differ by half of it by themselves, rows k and k + 2 through bit
+  // 1 of k, the second 16-lane group (8 rows on) through bit 3.
+  __host__ __device__ static constexpr int swz_chunk_kn(int k, int c) {
+    return T == 128 ? c ^ (4 * (k & 3)) ^ (2 * ((k >> 3) & 1)) : c ^ (4 * ((k >> 1) & 1)) ^ (2 * ((k >> 3) & 1));
+  }
+  __host__ __device__ static constexpr int swz_kn(int k, int n) {
+    return k * T * 2 + (swz_chunk_kn(k, n >> 3) << 4) + ((n & 7) << 1);
+  }
+};
+
 // ---------------------------------------------------------------------------
 // Operand addressing of the direct loads, shared by the kernels and the
 // host-side bounds check.  A stage's 1 KB loads are numbered g = wave + q NW;
@@ -174,9 +217,63 @@ struct UpdLoads {
   }
 };
 
+// The same for the smaller tiles.  [row][k] operand panels (both panels of the
+// symmetric products, B' of the update).
+template <int T>
+struct MidLoads {
+  using G = MidGeom<T>;
+  static constexpr int PER_OPER = G::OPER_BYTES / 1024;        // loads per operand and stage
+  static constexpr int ROWS_PER_LOAD = 1024 / G::RB;
+  static constexpr int KROWS_PER_LOAD = 1024 / (T * 2);
+  static_assert(PER_OPER == (G::LOADS / 2) * G::NW, "each wave's first half of loads is the row panel");
+  __host__ __device__ static constexpr uint64_t voff_rk(int g, int lane, int row0, int ld) {
+    return ((uint64_t)(row0 + g * ROWS_PER_LOAD + lane / G::CPR) * (uint64_t)ld +
+            (uint64_t)(((lane % G::CPR) ^ (((g * ROWS_PER_LOAD + lane / G::CPR) / G::RPP) % G::CPR)) * 8)) *
+           2;
+  }
+  __host__ __device__ static constexpr uint64_t voff_kn(int g, int lane, int col0, int np) {
+    return ((uint64_t)(g * KROWS_PER_LOAD + lane / (T / 8)) * (uint64_t)np + col0 +
+            (uint64_t)G::swz_chunk_kn(g * KROWS_PER_LOAD + lane / (T / 8), lane % (T / 8)) * 8) *
+           2;
+  }
+  __host__ __device__ static constexpr uint64_t soff_rk(int kt) { return (uint64_t)kt * G::BK * 2; }
+  // Update: stage kt of KH stages of B'_hi, then (split) KH stages of B'_lo,
+  // mp columns to the right; X's k starts over for the second half.
+  __host__ __device__ static constexpr uint64_t soff_b(int kt, int KH, int mp) {
+    return (uint64_t)(kt < KH ? kt * G::BK : mp + (kt - KH) * G::BK) * 2;
+  }
+  __host__ __device__ static constexpr uint64_t soff_x(int kt, int KH, int np) {
+    return (uint64_t)((kt < KH ? kt : kt - KH) * G::BK) * (uint64_t)np * 2;
+  }
+};
+
+// Gram of a matrix cut along k: split s of S takes stages [mid_k0(s), mid_k0(s + 1)).
+__host__ __device__ constexpr int mid_k0(int s, int S, int KT) { return (int)((int64_t)KT * s / S); }
+// Its fp32 partial tiles lie in the iterate buffer that the next update will
+// overwrite: tile (ti <= tj) of a Tn x Tn grid, split s, T * T floats each.
+__host__ __device__ constexpr uint64_t mid_part(int ti, int tj, int s, int Tn, int S, int T) {
+  return (uint64_t)((ti * Tn - ti * (ti - 1) / 2 + (tj - ti)) * S + s) * (uint64_t)(T * T);
+}
+
 typedef __attribute__((address_space(3))) i16x4 lds_i16x4_t;
 
 __device__ __forceinline__ float bf2f_(bf16_t h) { return __uint_as_float(((uint32_t)h) << 16); }
+
+// 4 x 4 transpose of 16-bit values inside each lane quad: in, lane p holds four
+// consecutive rows of column p of a 4 x 4 block (hv.x rows 0, 1; hv.y rows 2,
+// 3); out, row p's four columns.
+__device__ __forceinline__ uint2 quad_transpose(uint2 hv, int p) {
+  const uint32_t A0 = hv.x, B0 = hv.y;   // rows (0,1), (2,3) of column p
+  const uint32_t A1 = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)A0, 0xB1, 0xF, 0xF, true);   // lane p ^ 1
+  const uint32_t B1 = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)B0, 0xB1, 0xF, 0xF, true);
+  // Even lanes: row 0 (A) / row 2 (B) at columns p, p+1; odd lanes: row 1 /
+  // row 3 at columns p-1, p.
+  const uint32_t nA = (p & 1) ? ((A1 >> 16) | (A0 & 0xffff0000u)) : ((A0 & 0xffffu) | (A1 << 16));
+  const uint32_t nB = (p & 1) ? ((B1 >> 16) | (B0 & 0xffff0000u)) : ((B0 & 0xffffu) | (B1 << 16));
+  const uint32_t S = (p < 2) ? nB : nA;
+  const uint32_t S2 = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)S, 0x4E, 0xF, 0xF, true);   // lane p ^ 2
+  return (p < 2) ? make_uint2(nA, S2) : make_uint2(S2, nB);
+}
 
 __device__ __forceinline__ float wsum(float v) {
 #pragma unroll
@@ -361,6 +458,85 @@ template <class G, int RPM, class Issue, class Read, class Mma>
 __device__ __forceinline__ void pipeline(const int KT, const int nl, char* lds, Issue&& issue, Read&& read,
                                          Mma&& mma) {
   pipeline<G, RPM, 0>(KT, nl, lds, issue, read, [](int, int, const char*) {}, mma);
+}
+
+// Software pipeline of the smaller tiles, over KT stages in G::STAGES slots.
+// A tile's MFMAs of one stage take a fraction of the time its loads need to
+// arrive, so the loads run as far ahead as the ring allows: a stage's
+// fragments are in registers (read while the stage before it multiplies) when
+// the barrier frees its slot, which then receives stage kt + STAGES.  Callbacks
+// as for pipeline(); sub-steps alternate between two fragment buffers across
+// stages.
+template <class G, int RPM, class Issue, class Read, class Mma>
+__device__ __forceinline__ void mid_pipeline(const int KT, const int nl, char* lds, Issue&& issue, Read&& read,
+                                             Mma&& mma) {
+  constexpr int STAGES = G::STAGES, H = G::H, LOADS = G::LOADS, NMMA = G::NMMA;
+  constexpr int LPM = (LOADS + NMMA - 1) / NMMA;   // a stage's loads behind each MFMA
+#pragma unroll
+  for (int s = 0; s < STAGES; ++s)
+    if (s < KT)
+#pragma unroll
+      for (int i = 0; i < LOADS; ++i)
+        if (i < nl) issue(s, lds + s * G::STAGE_BYTES, i);
+  wait_vm(min(STAGES - 1, KT - 1) * nl);   // stage 0 has landed
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+  read(0, lds, 0);
+  char* st = lds;
+  auto body = [&](const int kt, auto steady_tag, auto c_tag) {
+    constexpr bool steady = decltype(steady_tag)::value;   // stage kt + STAGES exists
+    constexpr int C = decltype(c_tag)::value;              // fragment buffer of the stage's first sub-step
+    char* const nx = st + G::STAGE_BYTES == lds + G::RING_BYTES ? lds : st + G::STAGE_BYTES;
+#pragma unroll
+    for (int h = 0; h < H; ++h) {
+      const int c = (C + h) & 1;
+      const bool last = h + 1 == H;
+      if (!last) {
+        read(c ^ 1, st, h + 1);
+      } else if (steady || kt + 1 < KT) {
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // this wave's reads of stage kt are done
+        // Stage kt + 1 has landed; in flight: stages kt + 2 .. kt + STAGES - 1.
+        if constexpr (steady) wait_vm((STAGES - 2) * nl);
+        else wait_vm((min(kt + STAGES - 1, KT - 1) - (kt + 1)) * nl);
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        read(c ^ 1, nx, 0);
+      }
+      mma(c, [&](int j) {
+        if constexpr (steady) {
+          if (last) {
+#pragma unroll
+            for (int i = j * LPM; i < (j + 1) * LPM; ++i)
+              if (i < LOADS && i < nl) issue(kt + STAGES, st, i);
+          }
+        }
+      });
+#pragma unroll
+      for (int j = 0; j < NMMA; ++j) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);     // one MFMA
+        __builtin_amdgcn_sched_group_barrier(0x100, RPM, 0);   // RPM LDS reads
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    st = nx;
+  };
+  using C0 = std::integral_constant<int, 0>;
+  using C1 = std::integral_constant<int, H & 1>;
+  int kt = 0;
+  for (; kt + 1 < KT - STAGES; kt += 2) {
+    body(kt, std::true_type{}, C0{});
+    body(kt + 1, std::true_type{}, C1{});
+  }
+  // An even number of stages left behind: the tail starts in buffer 0 again.
+  if (kt < KT - STAGES) {
+    body(kt, std::true_type{}, C0{});
+    if (kt + 1 < KT) body(kt + 1, std::false_type{}, C1{});
+    kt += 2;
+  }
+  for (; kt < KT; kt += 2) {
+    body(kt, std::false_type{}, C0{});
+    if (kt + 1 < KT) body(kt + 1, std::false_type{}, C1{});
+  }
 }
 
 }  // namespace ns

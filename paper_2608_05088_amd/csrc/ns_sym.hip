@@ -305,18 +305,7 @@ void ns_gemm_sym_kernel(NsArgs args) {
   // 16-bit values inside each lane quad, after which lane p of the quad holds
   // row p of the quad's four rows, its four columns.
   const int p = lane & 3;
-  auto quad_rows = [&](int i, int j) {
-    const uint32_t A0 = hv[i][j].x, B0 = hv[i][j].y;   // rows (0,1), (2,3) of column p
-    const uint32_t A1 = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)A0, 0xB1, 0xF, 0xF, true);   // lane p ^ 1
-    const uint32_t B1 = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)B0, 0xB1, 0xF, 0xF, true);
-    // Even lanes: row 0 (A) / row 2 (B) at columns p, p+1; odd lanes:
-    // row 1 / row 3 at columns p-1, p.
-    const uint32_t nA = (p & 1) ? ((A1 >> 16) | (A0 & 0xffff0000u)) : ((A0 & 0xffffu) | (A1 << 16));
-    const uint32_t nB = (p & 1) ? ((B1 >> 16) | (B0 & 0xffff0000u)) : ((B0 & 0xffffu) | (B1 << 16));
-    const uint32_t S = (p < 2) ? nB : nA;
-    const uint32_t S2 = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)S, 0x4E, 0xF, 0xF, true);   // lane p ^ 2
-    return (p < 2) ? make_uint2(nA, S2) : make_uint2(S2, nB);
-  };
+  auto quad_rows = [&](int i, int j) { return quad_transpose(hv[i][j], p); };
   // Writes one set of values (hi, or the split low part at column offset
   // off): the transposed staging first, then the row-wise one.
   auto emit = [&](int off) {

@@ -1,0 +1,61 @@
+"""The Newton-Schulz tile edges (64, 128, 256) and the cut Gram against the
+fp64 oracle, at the sizes where a tile, a remainder or a part of a contraction
+begins or ends.  The plan chooses the edges from the whole set, so each case is
+a set; which edges it is meant to reach stands beside it."""
+import pytest
+
+from gpu_harness import compare, run_gpu, run_oracle, say
+from paper_2608_05088_amd import libmalt as lm
+from paper_2608_05088_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+CASES = {
+    # 64-tiles: one tile, one past it, a remainder on each side, tall and wide
+    "edges_64": [(64, 64), (65, 129), (127, 128), (129, 191), (320, 65), (33, 40)],
+    # 64-tiles, Gram cut along k: contractions of 141 and 313 stages, one of them
+    # of a hi/lo-split matrix, a tall one, and one whose parts are uneven
+    "cut_64": [(64, 9001), (200, 20000), (15001, 70)],
+    # 128-tiles in the update, 64 elsewhere
+    "edges_128": [(512, 1536), (512, 512), (513, 2048), (2048, 511)] * 2,
+    # 128-tiles in the polynomial, 256 elsewhere
+    "poly_128": [(768, 2304), (768, 768), (700, 3072), (3072, 768)] * 12,
+    # a long matrix beside a small model: its Gram cut on 128-tiles
+    "long_beside_model": [(20000, 348)] + [(348, 1044), (348, 348), (348, 1392), (1392, 348)] * 4,
+}
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    lm.lib()
+
+
+@pytest.mark.parametrize("name", sorted(CASES))
+@pytest.mark.parametrize("abc", [(3.4445, -4.7750, 2.0315), (1.5, -0.5, 0.0)])
+def test_tile_edges(name, abc):
+    shapes = CASES[name]
+    keep = sorted(set(list(range(min(4, len(shapes)))) + [len(shapes) - 1]))
+    say(f"[tiles] {name} {len(shapes)} matrices abc={abc} malter x2")
+    W0 = [wl.weight(87, i, s) for i, s in enumerate(shapes)]
+    grads = [[wl.grad(87, t, i, s, "row_loguniform") for i, s in enumerate(shapes)] for t in (1, 2)]
+    hp = dict(lr=3e-3, ns_a=abc[0], ns_b=abc[1], ns_c=abc[2])
+    g = run_gpu(shapes, "malter", W0, grads, hp, collect=keep)
+    o = run_oracle(shapes, "malter", W0, grads, hp, collect=keep)
+    worst = compare(g, o, "malter", label=name)
+    say(f"[tiles] {name} worst {worst}")
+
+
+def test_cubic_iteration_on_256_tiles():
+    # c = 0 takes the 256-tile polynomial's reload path, which only sets large
+    # enough for 256-tiles reach.
+    shapes = [(1280, 1280)] * 36
+    say(f"[tiles] cubic {len(shapes)} matrices")
+    W0 = [wl.weight(86, i, s) for i, s in enumerate(shapes)]
+    grads = [[wl.grad(86, 1, i, s) for i, s in enumerate(shapes)]]
+    hp = dict(lr=3e-3, ns_a=1.5, ns_b=-0.5, ns_c=0.0)
+    g = run_gpu(shapes, "malt", W0, grads, hp, collect=[0, 35])
+    o = run_oracle(shapes, "malt", W0, grads, hp, collect=[0, 35])
+    say(f"[tiles] cubic worst {compare(g, o, 'malt', label='cubic')}")
