@@ -59,48 +59,6 @@ __device__ __forceinline__ void store4(MALT_GLOBAL float* __restrict__ p, int c,
   }
 }
 
-// One matrix's descriptor fields and caller pointers, as the tile passes use
-// them, read in one place before any branch: the compiler then issues them as
-// one batch of scalar loads, not a chain of load-and-wait behind each test.
-struct EwView {
-  int m, n, np, tall;
-  bool vec;
-  MALT_GLOBAL float* W;
-  const MALT_GLOBAL float* G;
-  MALT_GLOBAL float* M;
-  const MALT_GLOBAL float* Lv;
-  const MALT_GLOBAL float* Rv;
-  MALT_GLOBAL float* rowpart;
-  MALT_GLOBAL float* colpart;
-  MALT_GLOBAL float* k2part;
-  MALT_GLOBAL bf16_t* X0;
-  const MALT_GLOBAL bf16_t* O;   // back-map: the buffer holding the final iterate
-  const MALT_GLOBAL double* scal;
-};
-
-__device__ __forceinline__ EwView ew_view(const EwArgs& a, int mat) {
-  const MatDesc& d = a.desc[mat];
-  const PtrPair& p = a.ptrs[mat];
-  EwView v;
-  v.m = d.m;
-  v.n = d.n;
-  v.np = d.np;
-  v.tall = d.tall;
-  v.vec = p.vec != 0;
-  v.W = gptr(p.W);
-  v.G = gptr(p.G);
-  v.M = gptr(d.M);
-  v.Lv = gptr(d.Lv);
-  v.Rv = gptr(d.Rv);
-  v.rowpart = gptr(d.rowpart);
-  v.colpart = gptr(d.colpart);
-  v.k2part = gptr(d.k2part);
-  v.X0 = gptr(d.X[0]);
-  v.O = gptr(d.X[a.o_parity]);
-  v.scal = gptr(d.scal);
-  return v;
-}
-
 // ---------------------------------------------------------------------------
 // Momentum EMA (Alg. 1/2, momentum line) fused with the per-tile row and
 // column sums of G^2 that feed the l, r EMAs (Eq. dp_preconditioner).
@@ -464,6 +422,7 @@ __device__ void block_sum_pairs(const float* __restrict__ p, int count, double o
 // ||Mt||_F, sigma = 1/(s+ns_eps), nu_t and alpha_t (Alg. 2; displayed alpha_t).
 __global__ __launch_bounds__(NTHREADS) void norm_scalars_kernel(EwArgs a) {
   const MatDesc& d = a.desc[blockIdx.x];
+  if (d.tiny) return;   // stepped whole by tiny_step_kernel
   double sums[2];
   block_sum_pairs(d.k2part, d.k2_tiles, sums);
   if (threadIdx.x != 0) return;
@@ -545,6 +504,7 @@ __global__ __launch_bounds__(NTHREADS) void precond_cond_kernel(const MatDesc* d
 // ||O||, ||D|| = ||L O R|| from the update-tile partials; graft and coefficient.
 __global__ __launch_bounds__(NTHREADS) void graft_scalars_kernel(EwArgs a) {
   const MatDesc& d = a.desc[blockIdx.x];
+  if (d.tiny) return;
   double sums[2];
   block_sum_pairs(d.gpart, d.upd_tiles, sums);
   if (threadIdx.x != 0) return;

@@ -48,8 +48,9 @@ inline size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
 struct MatPlan {
   int64_t m, n, mc, nc, mp, np;
-  bool tall, split, small;
-  int64_t sm_gchunks;                  // fp32 path: Gram partials
+  bool tall, split, small, tiny;       // small: short side <= NS_SMALL_MAX; tiny: its step in one workgroup
+  int32_t tiny_rows;                   // rows a thread of that workgroup holds per column
+  int64_t sm_gchunks, sm_chunk;        // small, not tiny: Gram partials, columns of each
   int64_t dm, dn;                      // Newton-Schulz domain: mc, nc padded to the largest tile in use
   int32_t gsplit;                      // parts of the Gram's contraction
   bool gmid;                           // Gram on the smaller tiles (Layout::tile_gm)
@@ -58,7 +59,7 @@ struct MatPlan {
   int64_t st_M, st_l, st_r, st_nu;     // floats from state base
   size_t ws_scal, ws_Lv, ws_Rv, ws_rowpart, ws_colpart, ws_k2part, ws_gpart;
   size_t ws_X[2], ws_A, ws_B;
-  size_t ws_Xs[2], ws_Ap, ws_Bs;       // fp32 path only
+  size_t ws_Ap, ws_Bs;                 // small, not tiny
   // algorithmic cost
   double ns_flops_sym_per_iter;        // 3 mc^2 nc + mc^3 (symmetric minimum)
 };
@@ -68,7 +69,7 @@ struct Layout {
   size_t state_bytes = 0, ws_bytes = 0;
   size_t ws_desc = 0, ws_ptrs = 0;
   size_t ws_t_ew = 0, ws_t_fin = 0, ws_t_k2 = 0, ws_t_gram = 0, ws_t_poly = 0, ws_t_upd = 0;
-  size_t ws_t_smg = 0, ws_t_smp = 0, ws_t_smu = 0;
+  size_t ws_t_smg = 0, ws_t_smp = 0, ws_t_smu = 0, ws_t_tiny = 0;
   int64_t n_ew = 0, n_fin = 0, n_k2 = 0;
   int64_t n_k2w = 0;   // scale+convert tiles of wide matrices, listed before those of tall ones
   int64_t n_gram = 0, n_poly = 0, n_updd = 0;   // dispatch-ordered NS lists (padded)
@@ -77,7 +78,7 @@ struct Layout {
   int tile_g = NS_TILE, tile_gm = 0, tile_p = NS_TILE, tile_u = NS_TILE;
   size_t ws_t_gmid = 0, ws_t_gred = 0;
   int64_t n_gmid = 0, n_gred = 0;   // smaller-tile Gram list (dispatch order), reduction of the cut ones
-  int64_t n_smg = 0, n_smp = 0, n_smu = 0;   // fp32 Newton-Schulz lists
+  int64_t n_smg = 0, n_smp = 0, n_smu = 0, n_tiny = 0;   // short sides
 };
 
 malt_status_t check_shapes(const malt_shape_t* shapes, int32_t n) {
@@ -171,7 +172,7 @@ std::vector<Tile> xcd_order(const std::vector<Tile>& list, const std::vector<dou
 // Every work list of a plan. The Newton-Schulz lists gram, gmid, poly and upd
 // are in dispatch order (padded with mat = -1).
 struct Lists {
-  std::vector<Tile> ew, fin, k2, gram, gmid, gred, poly, upd, smg, smp, smu;
+  std::vector<Tile> ew, fin, k2, gram, gmid, gred, poly, upd, smg, smp, smu, tiny;
 };
 
 // Upper tiles (ti <= tj) of matrix i's symmetric products on tile edge T.
@@ -189,6 +190,10 @@ void build_tiles(const Layout& L, Lists& O) {
   std::vector<double> cg, cgm, cp, cu;
   for (int32_t i : ord) {
     const MatPlan& q = L.mats[i];
+    if (q.tiny) {
+      O.tiny.push_back({i, q.tiny_rows, 0, 0});
+      continue;
+    }
     for (int32_t ti = 0; ti < q.k1_rt; ++ti)
       for (int32_t tj = 0; tj < q.k1_ct; ++tj) O.ew.push_back({i, ti, tj, 0});
     for (int32_t c = 0; c < cdiv(q.m, FIN_W); ++c) O.fin.push_back({i, 0, c, 0});
@@ -231,7 +236,7 @@ void build_tiles(const Layout& L, Lists& O) {
   for (int pass = 0; pass < 2; ++pass)
     for (int32_t i : ord) {
       const MatPlan& q = L.mats[i];
-      if (q.tall != (pass == 1)) continue;
+      if (q.tiny || q.tall != (pass == 1)) continue;
       int32_t idx = 0;
       for (int32_t ti = 0; ti < q.k2_tr; ++ti)
         for (int32_t tj = 0; tj < q.k2_tc; ++tj) O.k2.push_back({i, ti, tj, idx++});
@@ -473,13 +478,18 @@ Layout make_layout(const malt_shape_t* shapes, int32_t n, malt_variant_t variant
     p.mp = pad_to(p.mc, NS_TILE); p.np = pad_to(p.nc, NS_TILE);
     p.small = p.mc <= NS_SMALL_MAX;
     p.split = !p.small && p.mc <= NS_SPLIT_MAX;
-    p.sm_gchunks = p.small ? cdiv(p.np, SM_CH_G) : 0;
+    // A thread holds 8, 16 or 32 rows per column, TINY_VALUES values in all.
+    p.tiny_rows = p.mc <= 8 ? 8 : p.mc <= 16 ? 16 : 32;
+    p.tiny = p.small && p.nc <= int64_t(TINY_THREADS) * (TINY_VALUES / p.tiny_rows);
+    p.sm_chunk = std::max<int64_t>(SM_CH_G, pad_to(cdiv(p.nc, SM_CHUNKS), NTHREADS));
+    p.sm_gchunks = p.small && !p.tiny ? cdiv(p.nc, p.sm_chunk) : 0;
     p.k1_ct = cdiv(p.n, EW_TC); p.k1_rt = cdiv(p.m, EW_TR);
     // Scale+convert tiles over the padded W-oriented domain.
     if (p.tall) { p.k2_tr = p.np / K2_T; p.k2_tc = p.mp / K2_T; }
     else { p.k2_tr = p.mp / K2W_R; p.k2_tc = p.np / EW_TC; }
     p.k2_tiles = p.k2_tr * p.k2_tc;
     p.ns_flops_sym_per_iter = 3.0 * double(p.mc) * p.mc * p.nc + double(p.mc) * p.mc * p.mc;
+    if (p.tiny) continue;
     L.n_ew += p.k1_rt * p.k1_ct;
     L.n_fin += cdiv(p.m, FIN_W) + cdiv(p.n, FIN_W);
     L.n_k2 += p.k2_tiles;
@@ -487,9 +497,9 @@ Layout make_layout(const malt_shape_t* shapes, int32_t n, malt_variant_t variant
   }
   choose_tiles(L);
   for (MatPlan& p : L.mats)
-    // fp32 path: no matrix-core tiles; the update's partial slots are its
+    // Short sides: no matrix-core tiles; the product's partial slots are its
     // column chunks.
-    p.upd_tiles = p.small ? p.np / SM_CH_U : (p.dm / L.tile_u) * (p.dn / L.tile_u);
+    p.upd_tiles = p.tiny ? 0 : p.small ? cdiv(p.nc, SM_CH_U) : (p.dm / L.tile_u) * (p.dn / L.tile_u);
   size_t off = 0;
   auto take = [&](size_t bytes) { const size_t o = off; off = align256(off + bytes); return o; };
   L.ws_desc = take(sizeof(MatDesc) * n);
@@ -508,6 +518,7 @@ Layout make_layout(const malt_shape_t* shapes, int32_t n, malt_variant_t variant
     L.n_smg = int64_t(T.smg.size());
     L.n_smp = int64_t(T.smp.size());
     L.n_smu = int64_t(T.smu.size());
+    L.n_tiny = int64_t(T.tiny.size());
   }
   L.ws_t_gram = take(sizeof(Tile) * L.n_gram);
   L.ws_t_gmid = take(sizeof(Tile) * L.n_gmid);
@@ -517,25 +528,24 @@ Layout make_layout(const malt_shape_t* shapes, int32_t n, malt_variant_t variant
   L.ws_t_smg = take(sizeof(Tile) * L.n_smg);
   L.ws_t_smp = take(sizeof(Tile) * L.n_smp);
   L.ws_t_smu = take(sizeof(Tile) * L.n_smu);
+  L.ws_t_tiny = take(sizeof(Tile) * L.n_tiny);
   for (int32_t i = 0; i < n; ++i) {
     MatPlan& p = L.mats[i];
     p.ws_scal = take(sizeof(double) * MAT_SCALARS);
     p.ws_Lv = take(4 * p.m);
     p.ws_Rv = take(4 * p.n);
-    p.ws_rowpart = take(4 * size_t(p.k1_ct) * p.m);
-    p.ws_colpart = take(4 * size_t(p.k1_rt) * p.n);
-    p.ws_k2part = take(8 * size_t(p.k2_tiles));
+    // Partials of the elementwise passes and of the product, and the
+    // Newton-Schulz buffers, for the matrices whose route has them.
+    const bool pass = !p.tiny, core = !p.small, chunked = p.small && !p.tiny;
+    p.ws_rowpart = take(pass ? 4 * size_t(p.k1_ct) * p.m : 0);
+    p.ws_colpart = take(pass ? 4 * size_t(p.k1_rt) * p.n : 0);
+    p.ws_k2part = take(pass ? 8 * size_t(p.k2_tiles) : 0);
     p.ws_gpart = take(8 * size_t(p.upd_tiles));
     for (int b = 0; b < 2; ++b) p.ws_X[b] = take(2 * size_t(p.mp) * p.np);
-    p.ws_A = take(2 * size_t(p.mp) * p.mp);
-    p.ws_B = take(2 * size_t(p.mp) * p.mp * (p.split ? 2 : 1));
-    if (p.small) {
-      for (int b = 0; b < 2; ++b) p.ws_Xs[b] = take(4 * size_t(p.mc) * p.np);
-      p.ws_Ap = take(4 * size_t(p.sm_gchunks) * NS_SMALL_MAX * NS_SMALL_MAX);
-      p.ws_Bs = take(4 * size_t(NS_SMALL_MAX) * NS_SMALL_MAX);
-    } else {
-      p.ws_Xs[0] = p.ws_Xs[1] = p.ws_Ap = p.ws_Bs = 0;
-    }
+    p.ws_A = take(core ? 2 * size_t(p.mp) * p.mp : 0);
+    p.ws_B = take(core ? 2 * size_t(p.mp) * p.mp * (p.split ? 2 : 1) : 0);
+    p.ws_Ap = take(chunked ? sizeof(double) * SM_PART * size_t(p.sm_gchunks) : 0);
+    p.ws_Bs = take(chunked ? sizeof(double) * NS_SMALL_MAX * NS_SMALL_MAX : 0);
   }
   L.ws_bytes = off;
   return L;
@@ -691,9 +701,10 @@ void fill_desc(const malt_plan* p, std::vector<MatDesc>& D) {
     d.sm_gchunks = int32_t(q.sm_gchunks);
     d.dm = int32_t(q.dm); d.dn = int32_t(q.dn);
     d.gsplit = q.gsplit;
-    for (int b = 0; b < 2; ++b) d.Xs[b] = q.small ? reinterpret_cast<float*>(w + q.ws_Xs[b]) : nullptr;
-    d.Ap = q.small ? reinterpret_cast<float*>(w + q.ws_Ap) : nullptr;
-    d.Bs = q.small ? reinterpret_cast<float*>(w + q.ws_Bs) : nullptr;
+    d.sm_chunk = int32_t(q.sm_chunk);
+    d.tiny = q.tiny ? 1 : 0;
+    d.Ap = q.sm_gchunks ? reinterpret_cast<double*>(w + q.ws_Ap) : nullptr;
+    d.Bs = q.sm_gchunks ? reinterpret_cast<double*>(w + q.ws_Bs) : nullptr;
   }
 }
 
@@ -735,7 +746,7 @@ malt_status_t init_plan(malt_plan* p, const malt_shape_t* shapes, int32_t n, mal
   std::vector<MatDesc> D;
   fill_desc(p, D);
   // Every table in one host image of the workspace head.
-  const size_t head = p->L.ws_t_smu + sizeof(Tile) * T.smu.size();
+  const size_t head = p->L.ws_t_tiny + sizeof(Tile) * T.tiny.size();
   std::vector<char> h(head, 0);
   char* hc = h.data();
   auto put = [&](size_t off, const std::vector<Tile>& v) { memcpy(hc + off, v.data(), sizeof(Tile) * v.size()); };
@@ -751,6 +762,7 @@ malt_status_t init_plan(malt_plan* p, const malt_shape_t* shapes, int32_t n, mal
   put(p->L.ws_t_smg, T.smg);
   put(p->L.ws_t_smp, T.smp);
   put(p->L.ws_t_smu, T.smu);
+  put(p->L.ws_t_tiny, T.tiny);
 
   e = launch_zero_fill(p->ws, p->L.ws_bytes, s);
   if (e == hipSuccess) e = hipMemcpyAsync(p->ws, hc, head, hipMemcpyHostToDevice, s);
@@ -904,27 +916,21 @@ malt_status_t check_bounds(const Layout& L, const Lists& W, int64_t shrink, int6
   // Workspace regions lie inside the workspace, in order, without overlap.
   {
     const Tile none{-1, 0, 0, 0};
-    uint64_t end = L.ws_t_smu + sizeof(Tile) * smu.size();
+    uint64_t end = L.ws_t_tiny + sizeof(Tile) * W.tiny.size();
     for (const MatPlan& q : L.mats) {
       const std::pair<size_t, uint64_t> regions[] = {
           {q.ws_scal, 8 * MAT_SCALARS}, {q.ws_Lv, 4 * q.m}, {q.ws_Rv, 4 * q.n},
-          {q.ws_rowpart, 4 * uint64_t(q.k1_ct) * q.m}, {q.ws_colpart, 4 * uint64_t(q.k1_rt) * q.n},
-          {q.ws_k2part, 8 * uint64_t(q.k2_tiles)}, {q.ws_gpart, 8 * uint64_t(q.upd_tiles)},
+          {q.ws_rowpart, q.tiny ? 0 : 4 * uint64_t(q.k1_ct) * q.m},
+          {q.ws_colpart, q.tiny ? 0 : 4 * uint64_t(q.k1_rt) * q.n},
+          {q.ws_k2part, q.tiny ? 0 : 8 * uint64_t(q.k2_tiles)}, {q.ws_gpart, 8 * uint64_t(q.upd_tiles)},
           {q.ws_X[0], 2 * uint64_t(q.mp) * q.np}, {q.ws_X[1], 2 * uint64_t(q.mp) * q.np},
-          {q.ws_A, 2 * uint64_t(q.mp) * q.mp}, {q.ws_B, 2 * uint64_t(q.mp) * q.mp * (q.split ? 2 : 1)}};
+          {q.ws_A, q.small ? 0 : 2 * uint64_t(q.mp) * q.mp},
+          {q.ws_B, q.small ? 0 : 2 * uint64_t(q.mp) * q.mp * (q.split ? 2 : 1)},
+          {q.ws_Ap, 8 * uint64_t(SM_PART) * q.sm_gchunks},
+          {q.ws_Bs, q.sm_gchunks ? 8 * uint64_t(NS_SMALL_MAX) * NS_SMALL_MAX : 0}};
       for (const auto& r : regions) {
         if (!B.cond(r.first >= end, "layout", none, "workspace regions overlap")) return B.st;
         end = r.first + r.second;
-      }
-      if (q.small) {
-        const std::pair<size_t, uint64_t> sm[] = {{q.ws_Xs[0], 4 * uint64_t(q.mc) * q.np},
-                                                  {q.ws_Xs[1], 4 * uint64_t(q.mc) * q.np},
-                                                  {q.ws_Ap, 4 * uint64_t(q.sm_gchunks) * NS_SMALL_MAX * NS_SMALL_MAX},
-                                                  {q.ws_Bs, 4 * uint64_t(NS_SMALL_MAX) * NS_SMALL_MAX}};
-        for (const auto& r : sm) {
-          if (!B.cond(r.first >= end, "layout", none, "workspace regions overlap")) return B.st;
-          end = r.first + r.second;
-        }
       }
     }
     if (!B.range("layout", "workspace", none, 0, end, L.ws_bytes, false, true)) return B.st;
@@ -1091,23 +1097,35 @@ malt_status_t check_bounds(const Layout& L, const Lists& W, int64_t shrink, int6
   if (L.tile_u != NS_TILE && !(L.tile_u == 64 ? check_mid<64>(B, PH_UPDATE, W.upd, no_tiles)
                                               : check_mid<128>(B, PH_UPDATE, W.upd, no_tiles)))
     return B.st;
-  // fp32 Newton-Schulz of short sides <= 32: chunk and partial-slot indices.
+  // Short sides <= 32: chunk and partial-slot indices; the whole-step matrices'
+  // columns fit their workgroup's registers.
   for (const Tile& t : smg) {
     if (!B.mat_ok("sm_gram", t)) return B.st;
     const MatPlan& q = L.mats[t.mat];
-    if (!B.cond(q.small && t.ti >= 0 && t.ti < q.sm_gchunks && int64_t(t.ti) * SM_CH_G < q.np, "sm_gram", t,
-                "chunk out of range"))
+    if (!B.cond(q.small && !q.tiny && t.ti >= 0 && t.ti < q.sm_gchunks && t.ti * q.sm_chunk < q.nc &&
+                    q.sm_gchunks * q.sm_chunk >= q.nc,
+                "sm_gram", t, "chunk out of range"))
       return B.st;
   }
   for (const Tile& t : smp) {
-    if (!B.mat_ok("sm_poly", t)) return B.st;
-    if (!B.cond(L.mats[t.mat].small, "sm_poly", t, "matrix is not on the fp32 path")) return B.st;
+    if (!B.mat_ok("sm_iterate", t)) return B.st;
+    if (!B.cond(L.mats[t.mat].small && !L.mats[t.mat].tiny, "sm_iterate", t, "matrix is not on the short-side route"))
+      return B.st;
   }
   for (const Tile& t : smu) {
-    if (!B.mat_ok("sm_update", t)) return B.st;
+    if (!B.mat_ok("sm_apply", t)) return B.st;
     const MatPlan& q = L.mats[t.mat];
-    if (!B.cond(q.small && t.ti >= 0 && int64_t(t.ti + 1) * SM_CH_U <= q.np && t.idx >= 0 && t.idx < q.upd_tiles,
-                "sm_update", t, "chunk or partial slot out of range"))
+    if (!B.cond(q.small && !q.tiny && t.ti >= 0 && int64_t(t.ti + 1) * SM_CH_U <= q.np && t.idx >= 0 &&
+                    t.idx < q.upd_tiles,
+                "sm_apply", t, "chunk or partial slot out of range"))
+      return B.st;
+  }
+  for (const Tile& t : W.tiny) {
+    if (!B.mat_ok("tiny_step", t)) return B.st;
+    const MatPlan& q = L.mats[t.mat];
+    if (!B.cond(q.tiny && (t.ti == 8 || t.ti == 16 || t.ti == 32) && q.mc <= t.ti && q.mc <= q.mp &&
+                    q.nc <= int64_t(TINY_THREADS) * (TINY_VALUES / t.ti) && q.nc <= q.np,
+                "tiny_step", t, "matrix does not fit a whole-step workgroup"))
       return B.st;
   }
   *checked = B.checked;
@@ -1302,54 +1320,64 @@ malt_status_t malt_step(malt_plan_t* p, float* const* params, const float* const
     if ((e = (call)) != hipSuccess) goto hip_error;         \
   } while (0)
   {
-    ea.tiles = tiles_at(p->L.ws_t_ew); ea.ntiles = int32_t(p->L.n_ew);
-    MALT_LAUNCH(0, launch_momentum_rowcol(ea, s));
-    ea.tiles = tiles_at(p->L.ws_t_fin); ea.ntiles = int32_t(p->L.n_fin);
-    MALT_LAUNCH(1, launch_precond_finalize(ea, s));
-    if (p->L.n_k2w > 0) {
-      ea.tiles = tiles_at(p->L.ws_t_k2); ea.ntiles = int32_t(p->L.n_k2w);
-      MALT_LAUNCH(2, launch_scale_convert(ea, false, s));
+    SmallArgs sa;
+    sa.a = hp->ns_a; sa.b = hp->ns_b; sa.c = hp->ns_c;
+    sa.steps = hp->ns_steps;
+    if (p->L.n_tiny > 0) {   // matrices whose step is one workgroup's
+      sa.e = ea;
+      sa.e.tiles = tiles_at(p->L.ws_t_tiny); sa.e.ntiles = int32_t(p->L.n_tiny);
+      MALT_LAUNCH(6, launch_tiny_step(sa, s));
     }
-    if (p->L.n_k2 > p->L.n_k2w) {
-      ea.tiles = tiles_at(p->L.ws_t_k2) + p->L.n_k2w; ea.ntiles = int32_t(p->L.n_k2 - p->L.n_k2w);
-      MALT_LAUNCH(2, launch_scale_convert(ea, true, s));
-    }
-    MALT_LAUNCH(3, launch_norm_scalars(ea, n, s));
-    NsArgs na;
-    na.desc = ea.desc;
-    na.a = float(hp->ns_a); na.b = float(hp->ns_b); na.c = float(hp->ns_c);
-    for (int32_t it = 0; it < hp->ns_steps; ++it) {
-      na.first = it == 0;
-      na.last = it == hp->ns_steps - 1;
-      na.src = it & 1;
-      if (p->L.n_poly > 0) {   // matrix-core path
-        auto ns = [&](int phase, int tile, size_t off, int64_t count) {
-          na.phase = phase;
-          na.tiles = tiles_at(off);
-          na.ntiles = int32_t(count);
-          return tile == NS_TILE ? launch_ns_gemm(na, s) : launch_ns_mid(na, tile, s);
+    if (p->L.n_ew > 0) {
+      ea.tiles = tiles_at(p->L.ws_t_ew); ea.ntiles = int32_t(p->L.n_ew);
+      MALT_LAUNCH(0, launch_momentum_rowcol(ea, s));
+      ea.tiles = tiles_at(p->L.ws_t_fin); ea.ntiles = int32_t(p->L.n_fin);
+      MALT_LAUNCH(1, launch_precond_finalize(ea, s));
+      if (p->L.n_k2w > 0) {
+        ea.tiles = tiles_at(p->L.ws_t_k2); ea.ntiles = int32_t(p->L.n_k2w);
+        MALT_LAUNCH(2, launch_scale_convert(ea, false, s));
+      }
+      if (p->L.n_k2 > p->L.n_k2w) {
+        ea.tiles = tiles_at(p->L.ws_t_k2) + p->L.n_k2w; ea.ntiles = int32_t(p->L.n_k2 - p->L.n_k2w);
+        MALT_LAUNCH(2, launch_scale_convert(ea, true, s));
+      }
+      MALT_LAUNCH(3, launch_norm_scalars(ea, n, s));
+      NsArgs na;
+      na.desc = ea.desc;
+      na.a = float(hp->ns_a); na.b = float(hp->ns_b); na.c = float(hp->ns_c);
+      for (int32_t it = 0; it < hp->ns_steps; ++it) {
+        na.first = it == 0;
+        na.last = it == hp->ns_steps - 1;
+        na.src = it & 1;
+        if (p->L.n_poly > 0) {   // matrix-core path
+          auto ns = [&](int phase, int tile, size_t off, int64_t count) {
+            na.phase = phase;
+            na.tiles = tiles_at(off);
+            na.ntiles = int32_t(count);
+            return tile == NS_TILE ? launch_ns_gemm(na, s) : launch_ns_mid(na, tile, s);
+          };
+          if (p->L.n_gram > 0) MALT_LAUNCH(4, ns(PH_GRAM, p->L.tile_g, p->L.ws_t_gram, p->L.n_gram));
+          if (p->L.n_gmid > 0) MALT_LAUNCH(4, ns(PH_GRAM, p->L.tile_gm, p->L.ws_t_gmid, p->L.n_gmid));
+          if (p->L.n_gred > 0) MALT_LAUNCH(4, ns(PH_REDUCE, p->L.tile_gm, p->L.ws_t_gred, p->L.n_gred));
+          MALT_LAUNCH(5, ns(PH_POLY, p->L.tile_p, p->L.ws_t_poly, p->L.n_poly));
+          MALT_LAUNCH(6, ns(PH_UPDATE, p->L.tile_u, p->L.ws_t_upd, p->L.n_updd));
+        }
+      }
+      if (p->L.n_smp > 0) {   // short sides: the whole iteration in three launches
+        sa.e = ea;
+        auto small = [&](int phase, size_t off, int64_t count) {
+          sa.e.tiles = tiles_at(off);
+          sa.e.ntiles = int32_t(count);
+          return launch_small_ns(sa, phase, s);
         };
-        if (p->L.n_gram > 0) MALT_LAUNCH(4, ns(PH_GRAM, p->L.tile_g, p->L.ws_t_gram, p->L.n_gram));
-        if (p->L.n_gmid > 0) MALT_LAUNCH(4, ns(PH_GRAM, p->L.tile_gm, p->L.ws_t_gmid, p->L.n_gmid));
-        if (p->L.n_gred > 0) MALT_LAUNCH(4, ns(PH_REDUCE, p->L.tile_gm, p->L.ws_t_gred, p->L.n_gred));
-        MALT_LAUNCH(5, ns(PH_POLY, p->L.tile_p, p->L.ws_t_poly, p->L.n_poly));
-        MALT_LAUNCH(6, ns(PH_UPDATE, p->L.tile_u, p->L.ws_t_upd, p->L.n_updd));
+        MALT_LAUNCH(4, small(PH_GRAM, p->L.ws_t_smg, p->L.n_smg));
+        MALT_LAUNCH(5, small(PH_POLY, p->L.ws_t_smp, p->L.n_smp));
+        MALT_LAUNCH(6, small(PH_UPDATE, p->L.ws_t_smu, p->L.n_smu));
       }
-      if (p->L.n_smp > 0) {   // fp32 path of the small matrices
-        na.tiles = tiles_at(p->L.ws_t_smg); na.ntiles = int32_t(p->L.n_smg);
-        na.phase = PH_GRAM;
-        MALT_LAUNCH(4, launch_small_ns(na, s));
-        na.tiles = tiles_at(p->L.ws_t_smp); na.ntiles = int32_t(p->L.n_smp);
-        na.phase = PH_POLY;
-        MALT_LAUNCH(5, launch_small_ns(na, s));
-        na.tiles = tiles_at(p->L.ws_t_smu); na.ntiles = int32_t(p->L.n_smu);
-        na.phase = PH_UPDATE;
-        MALT_LAUNCH(6, launch_small_ns(na, s));
-      }
+      MALT_LAUNCH(7, launch_graft_scalars(ea, n, s));
+      ea.tiles = tiles_at(p->L.ws_t_ew); ea.ntiles = int32_t(p->L.n_ew);
+      MALT_LAUNCH(8, launch_backmap_write(ea, s));
     }
-    MALT_LAUNCH(7, launch_graft_scalars(ea, n, s));
-    ea.tiles = tiles_at(p->L.ws_t_ew); ea.ntiles = int32_t(p->L.n_ew);
-    MALT_LAUNCH(8, launch_backmap_write(ea, s));
     if ((e = mark(-1)) != hipSuccess) goto hip_error;
   }
 #undef MALT_LAUNCH

@@ -38,12 +38,19 @@ constexpr int NS_SPLIT_MAX = 128;
 constexpr int NTHREADS = 256;
 // Preconditioner finalise: rows or columns per workgroup (4 threads each).
 constexpr int FIN_W = 64;
-// Matrices whose short side is at most this run Newton-Schulz in fp32 (X, A
-// and B' kept in fp32): Gram partials over SM_CH_G columns per workgroup,
-// updates over SM_CH_U columns (one per thread).
+// Matrices whose short side is at most this run Newton-Schulz in the Gram space
+// in float64 (small_ns.hip).  Those of at most TINY_VALUES columns per thread of
+// TINY_THREADS at 8, 16 or 32 rows each (a thread's columns lie in its
+// registers) take their whole step in one workgroup; the others a Gram over
+// chunks of at least SM_CH_G columns, at most SM_CHUNKS of them, and the final
+// product over SM_CH_U columns (one per thread).
 constexpr int NS_SMALL_MAX = 32;
-constexpr int SM_CH_G = 4096;
+constexpr int TINY_THREADS = 512;
+constexpr int TINY_VALUES = 128;
+constexpr int SM_CH_G = 1024;
+constexpr int SM_CHUNKS = 128;
 constexpr int SM_CH_U = 256;
+constexpr int SM_PART = 3 * 256;   // values of one chunk's Gram: three upper 16 x 16 blocks
 
 typedef uint16_t bf16_t;   // bf16 storage
 
@@ -107,16 +114,17 @@ struct MatDesc {
   bf16_t* A;           // mp x mp  (Gram / A)
   bf16_t* B;           // mp x mp, or mp x 2mp [hi | lo] when split (b A + c A^2)
   double* scal;        // MAT_SCALARS
-  // fp32 Newton-Schulz (short side <= NS_SMALL_MAX); null otherwise
-  int32_t small;       // 1: this matrix takes the fp32 path
+  // short side <= NS_SMALL_MAX; null otherwise
+  int32_t small;       // 1: Newton-Schulz in the Gram space (small_ns.hip)
+  int32_t tiny;        // 1: the whole step in one workgroup; the other passes skip this matrix
   int32_t sm_gchunks;  // Gram partial count
+  int32_t sm_chunk;    // columns per Gram partial
+  double* Ap;          // [sm_gchunks][SM_PART] Gram partials
+  double* Bs;          // [32][32] sigma B_{s-1} ... B_0
   // Newton-Schulz domain: canonical dims rounded up to the plan's largest
   // Newton-Schulz tile (<= mp, np); no Newton-Schulz kernel works past it
   int32_t dm, dn;
   int32_t gsplit;      // parts of the Gram's contraction (1: not cut)
-  float* Xs[2];        // canonical mc x np fp32 iterate (row pitch np)
-  float* Ap;           // [sm_gchunks][32][32] Gram partials
-  float* Bs;           // [32][32] B'
 };
 
 // Per-step caller pointers; vec = 1 when W, G and M rows allow 16-byte access.
@@ -135,8 +143,8 @@ struct PtrPair {
 //       entry b runs on XCD b % 8; mat = -1 pads the shorter XCD runs
 //       On the smaller tiles a Gram's idx is its part of the contraction;
 //       reduction of the parts: (mat, tile row, tile col, 16-row piece)
-//   fp32 NS: Gram (mat, chunk, -, -), polynomial (mat, -, -, -),
-//            update (mat, chunk, -, partial slot)
+//   short sides: Gram (mat, chunk, -, -), iteration (mat, -, -, -), product
+//            (mat, chunk, -, partial slot); whole step (mat, rows per column, -, -)
 struct Tile {
   int32_t mat, ti, tj, idx;
 };
@@ -157,6 +165,13 @@ struct EwArgs {
   int32_t malter;
   int32_t identity;
   int32_t o_parity;      // which X buffer holds the final O
+};
+
+// Short sides: the step's arguments and the Newton-Schulz coefficients.
+struct SmallArgs {
+  EwArgs e;
+  double a, b, c;
+  int32_t steps;
 };
 
 struct NsArgs {
@@ -195,7 +210,51 @@ hipError_t launch_ns_gemm(const NsArgs& a, hipStream_t s);
 hipError_t ns_update_setup();   // the update kernel (ns_update.hip), called by ns_gemm_setup
 hipError_t launch_ns_update(const NsArgs& a, hipStream_t s);
 hipError_t launch_ns_mid(const NsArgs& a, int tile, hipStream_t s);   // 64 or 128 tiles, all phases (ns_mid.hip)
-hipError_t launch_small_ns(const NsArgs& a, hipStream_t s);
+hipError_t small_ns_setup();   // the whole-step kernel (small_ns.hip), called by ns_gemm_setup
+hipError_t launch_small_ns(const SmallArgs& a, int phase, hipStream_t s);
+hipError_t launch_tiny_step(const SmallArgs& a, hipStream_t s);
+
+// One matrix's descriptor fields and caller pointers, as the tile passes use
+// them, read in one place before any branch: the compiler then issues them as
+// one batch of scalar loads, not a chain of load-and-wait behind each test.
+struct EwView {
+  int m, n, np, tall;
+  bool vec;
+  MALT_GLOBAL float* W;
+  const MALT_GLOBAL float* G;
+  MALT_GLOBAL float* M;
+  const MALT_GLOBAL float* Lv;
+  const MALT_GLOBAL float* Rv;
+  MALT_GLOBAL float* rowpart;
+  MALT_GLOBAL float* colpart;
+  MALT_GLOBAL float* k2part;
+  MALT_GLOBAL bf16_t* X0;
+  const MALT_GLOBAL bf16_t* O;   // back-map: the buffer holding the final iterate
+  const MALT_GLOBAL double* scal;
+};
+
+__device__ __forceinline__ EwView ew_view(const EwArgs& a, int mat) {
+  const MatDesc& d = a.desc[mat];
+  const PtrPair& p = a.ptrs[mat];
+  EwView v;
+  v.m = d.m;
+  v.n = d.n;
+  v.np = d.np;
+  v.tall = d.tall;
+  v.vec = p.vec != 0;
+  v.W = gptr(p.W);
+  v.G = gptr(p.G);
+  v.M = gptr(d.M);
+  v.Lv = gptr(d.Lv);
+  v.Rv = gptr(d.Rv);
+  v.rowpart = gptr(d.rowpart);
+  v.colpart = gptr(d.colpart);
+  v.k2part = gptr(d.k2part);
+  v.X0 = gptr(d.X[0]);
+  v.O = gptr(d.X[a.o_parity]);
+  v.scal = gptr(d.scal);
+  return v;
+}
 
 // XCDs of the chip; workgroups are dispatched to them round-robin.
 constexpr int NXCD = 8;

@@ -436,6 +436,7 @@ hipError_t ns_gemm_setup() {
     e = hipFuncSetAttribute(reinterpret_cast<const void*>(&ns_gemm_sym_kernel<PolyGeom, PH_POLY>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, SymLds<PolyGeom>::BYTES);
   if (e == hipSuccess) e = ns_update_setup();
+  if (e == hipSuccess) e = small_ns_setup();
   return e;
 }
 

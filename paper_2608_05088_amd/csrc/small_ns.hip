@@ -1,186 +1,621 @@
-// Newton-Schulz in fp32 for matrices whose short side m' is at most
-// NS_SMALL_MAX (32).
+// Matrices whose short side m' is at most NS_SMALL_MAX (32): Newton-Schulz in
+// the Gram space, in float64.
 //
-// The bf16 matrix-core path pads such a matrix to a 256 x 256 tile, and with
+// The bf16 matrix-core path would pad such a matrix to a whole tile, and with
 // few singular values its rounding is not averaged away: the quintic is still
-// far from converged on the small ones, and it magnifies the bf16 rounding of
-// X there. These matrices instead keep X, A and B' in fp32. The work is
-// m'^2 n' per product, which the chip does in microseconds.
+// far from converged on the small ones and magnifies the rounding of X there.
+// Every B_k = a I + b A_k + c A_k^2 is a polynomial in A_0 = X_0 X_0^T, so
+//     A_{k+1} = B_k A_k B_k,   O = (B_{s-1} ... B_0) X_0,
+// and X is read twice, once for A_0 and once for the product with P = B_{s-1}
+// ... B_0, whatever the number of iterations.  In float64 the m' x m' matrices
+// lose nothing that matters: a relative error of 1e-16 of the largest entry of
+// A_0 grows by a^2 = 12 per iteration, as the small eigenvalues themselves do.
+// Products run on v_mfma_f64_16x16x4 (lane l holds A(l % 16, l / 16),
+// B(l / 16, l % 16); result register r holds C(l / 16 + 4 r, l % 16)); only the
+// final O is rounded to bf16.
 //
-// One iteration is three grouped launches over the small matrices of a step:
-//   Gram      each workgroup takes SM_CH_G columns of X and sums X_c X_c^T
-//             with v_mfma_f32_32x32x2f32 (the 32 x 32 output is the whole
-//             Gram); per-chunk partials go to the workspace
-//   Poly      one workgroup per matrix sums the partials in chunk order and
-//             forms B' = a I + b A + c A A in fp32
-//   Update    one thread per column: X'_c = B' X_c; the last iteration writes
-//             O rounded to bf16 (for the back-map) and per-chunk sums of O^2
-//             and (L O R)^2 from the rounded values
-// Iteration 0 reads X0 = sigma L M R straight from the fp32 momentum, in the
-// canonical orientation (rows <= columns).
+// Two routes:
+//   whole step   a matrix of at most 8192 columns in canonical orientation for
+//                m' <= 8, 4096 for m' <= 16, 2048 for m' <= 32 takes its whole
+//                step in one workgroup (tiny_step_kernel), its columns in
+//                registers: one launch for all such matrices of a plan, in
+//                place of 21.  What bounds it is the chain of its phases.
+//   three launches   larger ones take the plan's elementwise passes, and here
+//                a Gram over column chunks, one workgroup per matrix for the
+//                iteration, and the product with P over column chunks.
+// Measured (us per step): one 5 x 5 matrix 108 -> 46; 96 matrices of rank 16
+// (16 x 1024, 1024 x 16, 3072 x 16) 580 -> 60.
 #include "malt_internal.h"
 
 namespace malt {
 
-typedef float f32x16 __attribute__((ext_vector_type(16)));
+namespace {
 
-constexpr int SM_M = NS_SMALL_MAX;     // 32: one MFMA output tile
-constexpr int SM_SUB = 256;            // columns staged in LDS at a time
-static_assert(SM_CH_U == NTHREADS, "one update column per thread");
-static_assert(SM_CH_G % SM_SUB == 0 && SM_SUB % 8 == 0, "Gram chunk layout");
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+typedef float sm_f32x4 __attribute__((ext_vector_type(4)));
 
-// Canonical X (rows i < mc, columns c < nc; zero elsewhere) at column c for
-// rows 0..SM_M-1, from the momentum (first iteration) or the fp32 iterate.
-__device__ __forceinline__ float sm_x(const MatDesc& d, bool first, const float* Xs, int i, int c, float sig) {
-  if (i >= d.mc || c >= d.nc) return 0.f;
-  if (!first) return gptr(Xs)[(size_t)i * d.np + c];
-  // canonical (i, c) is W(i, c) for wide and W(c, i) for tall matrices
-  if (!d.tall) return sig * gptr(d.Lv)[i] * gptr(d.M)[(size_t)i * d.n + c] * gptr(d.Rv)[c];
-  return sig * gptr(d.Lv)[c] * gptr(d.M)[(size_t)c * d.n + i] * gptr(d.Rv)[i];
+constexpr int SM_M = NS_SMALL_MAX;          // 32
+constexpr int SM_LD = SM_M + 1;             // row pitch of an m' x m' matrix in LDS (doubles)
+constexpr int SM_PITCH = 64 + 1;            // row pitch of a wave's 64 staged columns (floats)
+constexpr int SM_WAVE = SM_M * SM_PITCH;    // one wave's staged columns (floats)
+
+// Blocks of 16 rows, and of 16 x 16 upper blocks, of m' <= MC.
+template <int MC>
+struct SmDim {
+  static constexpr int NB = MC > 16 ? 2 : 1;
+  static constexpr int NBLK = NB * (NB + 1) / 2;
+};
+
+// The iteration's matrices (five of them), and what shares their memory.
+struct SmCore {
+  double A[SM_M * SM_LD], B[SM_M * SM_LD], T[SM_M * SM_LD], P[2][SM_M * SM_LD];
+};
+
+__device__ __forceinline__ f64x4 sm_zero() { return f64x4{0.0, 0.0, 0.0, 0.0}; }
+
+// A wave's 64 columns (one per lane, rows >= MC absent) into its staging rows.
+template <int MC>
+__device__ __forceinline__ void sm_stage(float* buf, const float (&x)[MC], int lane) {
+#pragma unroll
+  for (int i = 0; i < MC; ++i) buf[i * SM_PITCH + lane] = x[i];
 }
 
-__global__ __launch_bounds__(NTHREADS) void sm_gram_kernel(NsArgs args) {
-  const Tile t = args.tiles[blockIdx.x];   // (mat, chunk, -, -)
-  const MatDesc& d = args.desc[t.mat];
-  __shared__ float tile[SM_M][SM_SUB + 1];
-  __shared__ float red[4][SM_M * SM_M];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const bool first = args.first != 0;
-  const float sig = first ? (float)d.scal[SC_SIGMA] : 1.f;
-  const float* Xs = d.Xs[args.src];
-  f32x16 acc;
+// Element (row, col) of the staged columns, 0 past MC rows.
+template <int MC>
+__device__ __forceinline__ double sm_at(const float* buf, int row, int col) {
+  return MC >= 16 || row < MC ? (double)buf[row * SM_PITCH + col] : 0.0;
+}
+
+// acc += X X^T over the staged columns, upper 16 x 16 blocks (0,0), (0,1), (1,1).
+template <int MC>
+__device__ __forceinline__ void sm_gram(const float* buf, f64x4 (&acc)[SmDim<MC>::NBLK], int lane) {
+#pragma unroll 4
+  for (int k = 0; k < 16; ++k) {
+    const int col = 4 * k + (lane >> 4);
+    const double a0 = sm_at<MC>(buf, lane & 15, col);
+    acc[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, a0, acc[0], 0, 0, 0);
+    if constexpr (SmDim<MC>::NB == 2) {
+      const double a1 = sm_at<MC>(buf, 16 + (lane & 15), col);
+      acc[1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, a1, acc[1], 0, 0, 0);
+      acc[2] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, a1, acc[2], 0, 0, 0);
+    }
+  }
+}
+
+// Block (bi, bj) of S1 S2, K = 16 NB.
+__device__ __forceinline__ f64x4 sm_mul(const double* S1, const double* S2, int bi, int bj, int NB, int lane) {
+  f64x4 c = sm_zero();
+  for (int k = 0; k < 4 * NB; ++k) {
+    const int kk = 4 * k + (lane >> 4);
+    c = __builtin_amdgcn_mfma_f64_16x16x4f64(S1[(16 * bi + (lane & 15)) * SM_LD + kk],
+                                             S2[kk * SM_LD + 16 * bj + (lane & 15)], c, 0, 0, 0);
+  }
+  return c;
+}
+
+__device__ __forceinline__ void sm_put(double* D, const f64x4& c, int bi, int bj, int lane) {
 #pragma unroll
-  for (int e = 0; e < 16; ++e) acc[e] = 0.f;
-  for (int sub = 0; sub < SM_CH_G / SM_SUB; ++sub) {
-    const int c0 = t.ti * SM_CH_G + sub * SM_SUB;
-    if (c0 >= d.np) break;   // uniform over the workgroup
-    __syncthreads();
-    for (int q = tid; q < SM_M * SM_SUB; q += NTHREADS) {
-      const int i = q / SM_SUB, c = q % SM_SUB;
-      tile[i][c] = sm_x(d, first, Xs, i, c0 + c, sig);
+  for (int r = 0; r < 4; ++r) D[(16 * bi + (lane >> 4) + 4 * r) * SM_LD + 16 * bj + (lane & 15)] = c[r];
+}
+
+// The iteration on s.A = A_0 (16 NB rows and columns); returns P.  Every thread
+// of the workgroup of NWAVES waves calls it; it ends with a barrier.
+template <int NWAVES>
+__device__ __forceinline__ const double* sm_iterate(SmCore& s, int NB, const SmallArgs& ns) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nblk = NB * NB;
+  int cur = 0;
+  for (int it = 0; it < ns.steps; ++it) {
+    for (int w = wave; w < nblk; w += NWAVES) {   // B = a I + b A + c A A
+      const int bi = w / NB, bj = w % NB;
+      f64x4 v = sm_mul(s.A, s.A, bi, bj, NB, lane);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int i = 16 * bi + (lane >> 4) + 4 * r, j = 16 * bj + (lane & 15);
+        v[r] = ns.b * s.A[i * SM_LD + j] + ns.c * v[r] + (i == j ? ns.a : 0.0);
+      }
+      sm_put(s.B, v, bi, bj, lane);
+      if (it == 0) sm_put(s.P[0], v, bi, bj, lane);
     }
     __syncthreads();
-    // A(m, n) += sum_k X(m, k) X(n, k): lane l supplies X(l % 32, k + l / 32)
-    // as both operands. Each wave takes a quarter of the staged columns.
-    constexpr int PER = SM_SUB / 4;
-    for (int k = wave * PER; k < (wave + 1) * PER; k += 2) {
-      const float v = tile[lane & 31][k + (lane >> 5)];
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(v, v, acc, 0, 0, 0);
+    if (it > 0) {   // P <- B P
+      for (int w = wave; w < nblk; w += NWAVES)
+        sm_put(s.P[cur ^ 1], sm_mul(s.B, s.P[cur], w / NB, w % NB, NB, lane), w / NB, w % NB, lane);
+      cur ^= 1;
     }
+    if (it + 1 < ns.steps) {   // A <- B A B, on the waves the product above left free first
+      for (int w = (wave + NWAVES - (it > 0 ? nblk % NWAVES : 0)) % NWAVES; w < nblk; w += NWAVES)
+        sm_put(s.T, sm_mul(s.B, s.A, w / NB, w % NB, NB, lane), w / NB, w % NB, lane);
+      __syncthreads();
+      for (int w = wave; w < nblk; w += NWAVES)
+        sm_put(s.A, sm_mul(s.T, s.B, w / NB, w % NB, NB, lane), w / NB, w % NB, lane);
+    }
+    __syncthreads();
   }
-  // acc[4g + e] = A(8g + 4 (lane >> 5) + e, lane & 31); the four waves' sums
-  // are combined in a fixed order.
-  __syncthreads();
-#pragma unroll
-  for (int e = 0; e < 16; ++e) {
-    const int r = 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3), c = lane & 31;
-    red[wave][r * SM_M + c] = acc[e];
-  }
-  __syncthreads();
-  float* out = d.Ap + (size_t)t.ti * SM_M * SM_M;
-  for (int q = tid; q < SM_M * SM_M; q += NTHREADS) out[q] = (red[0][q] + red[1][q]) + (red[2][q] + red[3][q]);
+  return s.P[cur];
 }
 
-__global__ __launch_bounds__(NTHREADS) void sm_poly_kernel(NsArgs args) {
-  const MatDesc& d = args.desc[args.tiles[blockIdx.x].mat];
-  __shared__ float A[SM_M][SM_M + 1];
-  const int tid = threadIdx.x;
-  for (int q = tid; q < SM_M * SM_M; q += NTHREADS) {
-    float s = 0.f;
-    for (int ch = 0; ch < d.sm_gchunks; ++ch) s += d.Ap[(size_t)ch * SM_M * SM_M + q];
-    A[q / SM_M][q % SM_M] = s;
-  }
-  __syncthreads();
-  for (int q = tid; q < SM_M * SM_M; q += NTHREADS) {
-    const int i = q / SM_M, j = q % SM_M;
-    float s2 = 0.f;
-#pragma unroll 8
-    for (int k = 0; k < SM_M; ++k) s2 += A[i][k] * A[k][j];
-    d.Bs[q] = (i == j ? args.a : 0.f) + args.b * A[i][j] + args.c * s2;
-  }
-}
-
-__global__ __launch_bounds__(NTHREADS) void sm_update_kernel(NsArgs args) {
-  const Tile t = args.tiles[blockIdx.x];   // (mat, chunk, -, partial slot)
-  const MatDesc& d = args.desc[t.mat];
-  __shared__ float B[SM_M][SM_M];
-  __shared__ float red[2][NTHREADS / 64];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  for (int q = tid; q < SM_M * SM_M; q += NTHREADS) B[q / SM_M][q % SM_M] = gptr(d.Bs)[q];
-  const bool first = args.first != 0;
-  const float sig = first ? (float)d.scal[SC_SIGMA] : 1.f;
-  const int c = t.ti * SM_CH_U + tid;      // canonical column (< np)
-  float x[SM_M];
+// Sums of (o^2, (Lm o Ln)^2) of the product with P for a wave's 64 staged
+// columns c0 .. c0 + 63; writes O rounded to bf16 (rows < mc, columns < nc).
+// rowf: canonical row factors; colf: the 64 columns' factors.
+template <int MC>
+__device__ __forceinline__ void sm_apply(const float* buf, const double (&pa)[SmDim<MC>::NB][MC > 16 ? 8 : 4],
+                                         const float* rowf, const float* colf, MALT_GLOBAL bf16_t* O, int np, int mc,
+                                         int nc, int c0, int lane, double& o2, double& d2) {
+  constexpr int NB = SmDim<MC>::NB, KS = MC > 16 ? 8 : 4;
+#pragma unroll 1
+  for (int g = 0; g < 4; ++g) {
+    const int cl = 16 * g + (lane & 15), c = c0 + cl;
+    if (c0 + 16 * g >= nc) break;   // uniform over the wave
+    f64x4 y[NB];
 #pragma unroll
-  for (int i = 0; i < SM_M; ++i) x[i] = sm_x(d, first, d.Xs[args.src], i, c, sig);
-  __syncthreads();
-  float y[SM_M];
+    for (int b = 0; b < NB; ++b) y[b] = sm_zero();
 #pragma unroll
-  for (int i = 0; i < SM_M; ++i) {
-    float s = 0.f;
+    for (int k = 0; k < KS; ++k) {
+      const double xb = sm_at<MC>(buf, 4 * k + (lane >> 4), cl);
 #pragma unroll
-    for (int j = 0; j < SM_M; ++j) s += B[i][j] * x[j];
-    y[i] = s;
-  }
-  const int mc = d.mc;
-  if (!args.last) {
-    MALT_GLOBAL float* Xn = gptr(d.Xs[args.src ^ 1]);
-#pragma unroll
-    for (int i = 0; i < SM_M; ++i)
-      if (i < mc) Xn[(size_t)i * d.np + c] = y[i];
-    return;
-  }
-  // Last iteration: O in bf16 where the back-map reads it, and the norms of
-  // the rounded values (canonical row i carries the row factor of W for wide
-  // and the column factor for tall matrices).
-  MALT_GLOBAL bf16_t* O = gptr(d.X[args.src ^ 1]);
-  const MALT_GLOBAL float* const Lm = gptr(d.tall ? d.Rv : d.Lv);
-  const MALT_GLOBAL float* const Ln = gptr(d.tall ? d.Lv : d.Rv);
-  const float ln = c < d.nc ? Ln[c] : 0.f;
-  float o2 = 0.f, d2 = 0.f;
-#pragma unroll
-  for (int i = 0; i < SM_M; ++i) {
-    if (i >= mc) continue;
-    const uint32_t pk = pack_bf16x2(y[i], 0.f);
-    O[(size_t)i * d.np + c] = (bf16_t)(pk & 0xffffu);
-    const float o = bf16_lo(pk);
-    if (c < d.nc) {
-      const float q = o * o;
-      const float lm = Lm[i];
-      o2 += q;
-      d2 += lm * lm * ln * ln * q;
+      for (int b = 0; b < NB; ++b) y[b] = __builtin_amdgcn_mfma_f64_16x16x4f64(pa[b][k], xb, y[b], 0, 0, 0);
     }
-  }
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    o2 += __shfl_xor(o2, off, 64);
-    d2 += __shfl_xor(d2, off, 64);
-  }
-  if (lane == 0) {
-    red[0][wave] = o2;
-    red[1][wave] = d2;
-  }
-  __syncthreads();
-  if (tid == 0) {
+    const float ln = colf[cl];
     float so = 0.f, sd = 0.f;
 #pragma unroll
-    for (int w = 0; w < NTHREADS / 64; ++w) {
-      so += red[0][w];
-      sd += red[1][w];
-    }
-    gptr(d.gpart)[2 * (size_t)t.idx + 0] = so;
-    gptr(d.gpart)[2 * (size_t)t.idx + 1] = sd;
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int i = 16 * b + (lane >> 4) + 4 * r;
+        const uint32_t pk = pack_bf16x2((float)y[b][r], 0.f);
+        if (i < mc && c < nc) {
+          O[(size_t)i * np + c] = (bf16_t)(pk & 0xffffu);
+          const float o = bf16_lo(pk), lm = rowf[i];
+          so += o * o;
+          sd += lm * lm * ln * ln * (o * o);
+        }
+      }
+    o2 += (double)so;
+    d2 += (double)sd;
   }
 }
 
-hipError_t launch_small_ns(const NsArgs& a, hipStream_t s) {
-  if (a.ntiles == 0) return hipSuccess;
-  if (a.phase == PH_GRAM)
-    hipLaunchKernelGGL(sm_gram_kernel, dim3(a.ntiles), dim3(NTHREADS), 0, s, a);
-  else if (a.phase == PH_POLY)
-    hipLaunchKernelGGL(sm_poly_kernel, dim3(a.ntiles), dim3(NTHREADS), 0, s, a);
+// MFMA operand of P scaled by sigma: pa[b][k] = sigma P(16 b + l % 16, 4 k + l / 16).
+template <int MC>
+__device__ __forceinline__ void sm_operand(const double* P, double sigma, double (&pa)[SmDim<MC>::NB][MC > 16 ? 8 : 4],
+                                           int lane) {
+#pragma unroll
+  for (int b = 0; b < SmDim<MC>::NB; ++b)
+#pragma unroll
+    for (int k = 0; k < (MC > 16 ? 8 : 4); ++k)
+      pa[b][k] = sigma * P[(16 * b + (lane & 15)) * SM_LD + 4 * k + (lane >> 4)];
+}
+
+__device__ __forceinline__ double sm_wave_sum(double v) {
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+  return v;
+}
+
+// Fixed-order sums of (v0, v1) over the workgroup, given to every thread.
+template <int NWAVES>
+__device__ __forceinline__ void sm_block_sum(double& v0, double& v1, double (*red)[2]) {
+  v0 = sm_wave_sum(v0);
+  v1 = sm_wave_sum(v1);
+  __syncthreads();   // red is free
+  if ((threadIdx.x & 63) == 0) {
+    red[threadIdx.x >> 6][0] = v0;
+    red[threadIdx.x >> 6][1] = v1;
+  }
+  __syncthreads();
+  v0 = v1 = 0.0;
+#pragma unroll
+  for (int w = 0; w < NWAVES; ++w) {
+    v0 += red[w][0];
+    v1 += red[w][1];
+  }
+}
+
+// (v + eps)^(-1/8): three square roots and a quotient, each correctly rounded.
+__device__ __forceinline__ float sm_inv_eighth(double v) { return (float)(1.0 / sqrt(sqrt(sqrt(v)))); }
+
+// ---------------------------------------------------------------------------
+// The whole step of one matrix.
+// ---------------------------------------------------------------------------
+constexpr int TY_NW = TINY_THREADS / 64;
+
+struct TinyLds {
+  union {
+    float stage[TY_NW * SM_WAVE];
+    double red[TY_NW][3][64 * 4];   // Gram blocks of the waves
+  };
+  SmCore core;
+  float colf[TY_NW][64];
+  float rowf[SM_M];
+  float rows[TY_NW][SM_M];
+  double red2[TY_NW][2];
+};
+static_assert(sizeof(TinyLds) <= 160 * 1024, "LDS of a whole-step workgroup");
+
+// Canonical column c of a W-shaped array: W(i, c) of a wide, W(c, i) of a tall
+// matrix (n = its column count).  Rows past mc and columns past nc read 0.
+template <int MC>
+__device__ __forceinline__ void tiny_load(const MALT_GLOBAL float* __restrict__ p, const EwView& v, int mc, int nc,
+                                          int c, float (&x)[MC]) {
+  if (c >= nc) {
+#pragma unroll
+    for (int i = 0; i < MC; ++i) x[i] = 0.f;
+  } else if (!v.tall) {
+#pragma unroll
+    for (int i = 0; i < MC; ++i) x[i] = i < mc ? p[(size_t)i * v.n + c] : 0.f;
+  } else if (v.vec) {
+#pragma unroll
+    for (int i = 0; i < MC; i += 4) {
+      sm_f32x4 q = {0.f, 0.f, 0.f, 0.f};
+      if (i < mc) q = *reinterpret_cast<const MALT_GLOBAL sm_f32x4*>(p + (size_t)c * v.n + i);   // n % 4 == 0
+#pragma unroll
+      for (int e = 0; e < 4; ++e) x[i + e] = q[e];
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < MC; ++i) x[i] = i < mc ? p[(size_t)c * v.n + i] : 0.f;
+  }
+}
+
+template <int MC>
+__device__ __forceinline__ void tiny_store(MALT_GLOBAL float* __restrict__ p, const EwView& v, int mc, int nc, int c,
+                                           const float (&x)[MC]) {
+  if (c >= nc) return;
+  if (!v.tall) {
+#pragma unroll
+    for (int i = 0; i < MC; ++i)
+      if (i < mc) p[(size_t)i * v.n + c] = x[i];
+  } else if (v.vec) {
+#pragma unroll
+    for (int i = 0; i < MC; i += 4)
+      if (i < mc)
+        *reinterpret_cast<MALT_GLOBAL sm_f32x4*>(p + (size_t)c * v.n + i) = sm_f32x4{x[i], x[i + 1], x[i + 2], x[i + 3]};
+  } else {
+#pragma unroll
+    for (int i = 0; i < MC; ++i)
+      if (i < mc) p[(size_t)c * v.n + i] = x[i];
+  }
+}
+
+// Adds v over the wave's lanes; afterwards lane l holds the sum of entry
+// l >> (6 - log2 N) (halves exchanged: N - 1 shuffles, not 6 N).
+template <int N>
+__device__ __forceinline__ float tiny_reduce(float (&v)[N], int lane) {
+  int off = 32;
+#pragma unroll
+  for (int n = N / 2; n >= 1; n /= 2) {
+    const bool up = lane & off;
+#pragma unroll
+    for (int k = 0; k < n; ++k) {
+      const float send = up ? v[k] : v[k + n], keep = up ? v[k + n] : v[k];
+      v[k] = keep + __shfl_xor(send, off, 64);
+    }
+    off >>= 1;
+  }
+  float s = v[0];
+  for (; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+  return s;
+}
+
+// CPT columns per thread, m' <= MC rows of each in registers.
+template <bool MALTER, int MC, int CPT>
+__device__ __forceinline__ void tiny_step(const SmallArgs& ns, int mat, TinyLds& S) {
+  constexpr int NB = SmDim<MC>::NB;
+  constexpr int LOG = MC == 32 ? 5 : MC == 16 ? 4 : 3;
+  const EwArgs& a = ns.e;
+  const MatDesc& d = a.desc[mat];
+  const EwView v = ew_view(a, mat);
+  const int mc = d.mc, nc = d.nc, np = v.np;
+  const bool tall = v.tall != 0;
+  MALT_GLOBAL float* const l = gptr(d.l);
+  MALT_GLOBAL float* const r = gptr(d.r);
+  MALT_GLOBAL float* const nu_p = gptr(d.nu);
+  MALT_GLOBAL double* const scal = gptr(d.scal);
+  MALT_GLOBAL bf16_t* const O = gptr(d.X[a.o_parity]);
+  MALT_GLOBAL float* const Lw = gptr(d.Lv);
+  MALT_GLOBAL float* const Rw = gptr(d.Rv);
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  float* const buf = S.stage + wave * SM_WAVE;
+
+  // Momentum, and the row and column sums of G^2.
+  float x[CPT][MC], colf[CPT];
+  {
+    float rs[MC];
+#pragma unroll
+    for (int i = 0; i < MC; ++i) rs[i] = 0.f;
+    MALT_GLOBAL float* const cema = tall ? l : r;
+    MALT_GLOBAL float* const cinv = tall ? Lw : Rw;
+#pragma unroll
+    for (int q = 0; q < CPT; ++q) {
+      const int c = tid + q * TINY_THREADS;
+      if (q * TINY_THREADS >= nc) {   // uniform
+#pragma unroll
+        for (int i = 0; i < MC; ++i) x[q][i] = 0.f;
+        colf[q] = 0.f;
+        continue;
+      }
+      float g[MC];
+      tiny_load<MC>(v.G, v, mc, nc, c, g);
+      tiny_load<MC>(v.M, v, mc, nc, c, x[q]);
+      float cs = 0.f;
+#pragma unroll
+      for (int i = 0; i < MC; ++i) {
+        x[q][i] = a.mu1 * x[q][i] + a.one_minus_mu1 * g[i];
+        const float g2 = g[i] * g[i];
+        cs += g2;
+        rs[i] += g2;
+      }
+      tiny_store<MC>(v.M, v, mc, nc, c, x[q]);
+      colf[q] = 0.f;
+      if (c < nc) {
+        const double e = a.mu2 * (double)cema[c] + (1.0 - a.mu2) * (double)cs;
+        cema[c] = (float)e;
+        colf[q] = a.identity ? 1.f : sm_inv_eighth(e + a.eps);
+        cinv[c] = colf[q];
+      }
+    }
+    const float s = tiny_reduce<MC>(rs, lane);
+    if ((lane & ((64 >> LOG) - 1)) == 0) S.rows[wave][lane >> (6 - LOG)] = s;
+  }
+  __syncthreads();
+  if (tid < SM_M) {
+    float f = 0.f;
+    if (tid < mc) {
+      MALT_GLOBAL float* const rema = tall ? r : l;
+      double s = 0.0;
+#pragma unroll
+      for (int w = 0; w < TY_NW; ++w) s += (double)S.rows[w][tid];
+      const double e = a.mu2 * (double)rema[tid] + (1.0 - a.mu2) * s;
+      rema[tid] = (float)e;
+      f = a.identity ? 1.f : sm_inv_eighth(e + a.eps);
+      (tall ? Rw : Lw)[tid] = f;
+    }
+    S.rowf[tid] = f;
+  }
+  __syncthreads();
+
+  // L M R (X0 before its normalisation), its norm and MALTER's ||L G R||.
+  double s2 = 0.0, q2 = 0.0;
+#pragma unroll
+  for (int q = 0; q < CPT; ++q) {
+    const int c = tid + q * TINY_THREADS;
+    if (q * TINY_THREADS >= nc) continue;
+    float g[MALTER ? MC : 1];
+    if constexpr (MALTER) tiny_load<MC>(v.G, v, mc, nc, c, g);
+    float sx = 0.f, sg = 0.f;
+#pragma unroll
+    for (int i = 0; i < MC; ++i) {
+      const float f = S.rowf[i];
+      x[q][i] = tall ? colf[q] * x[q][i] * f : f * x[q][i] * colf[q];
+      sx += x[q][i] * x[q][i];
+      if constexpr (MALTER) {
+        const float y = tall ? colf[q] * g[i] * f : f * g[i] * colf[q];
+        sg += y * y;
+      }
+      if (i < mc && c < nc) v.X0[(size_t)i * np + c] = (bf16_t)(pack_bf16x2(x[q][i], 0.f) & 0xffffu);
+    }
+    s2 += (double)sx;
+    q2 += (double)sg;
+  }
+  sm_block_sum<TY_NW>(s2, q2, S.red2);
+  const double s = sqrt(s2), sigma = 1.0 / (s + a.ns_eps);
+  double nu = 0.0, alpha = 1.0;
+  if constexpr (MALTER) {
+    nu = a.mu2 * (double)nu_p[0] + (1.0 - a.mu2) * q2;
+    alpha = a.bc * s / (sqrt(nu) + a.eps);
+  }
+
+  // A_0 = sigma^2 (L M R)(L M R)^T.
+  {
+    f64x4 acc[SmDim<MC>::NBLK];
+#pragma unroll
+    for (int b = 0; b < SmDim<MC>::NBLK; ++b) acc[b] = sm_zero();
+#pragma unroll
+    for (int q = 0; q < CPT; ++q) {
+      if (q * TINY_THREADS + wave * 64 >= nc) continue;   // uniform over the wave
+      sm_stage<MC>(buf, x[q], lane);
+      sm_gram<MC>(buf, acc, lane);
+    }
+    __syncthreads();   // the staging rows become the waves' blocks
+#pragma unroll
+    for (int b = 0; b < SmDim<MC>::NBLK; ++b)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) S.red[wave][b][lane * 4 + e] = acc[b][e];
+    __syncthreads();
+    const double sg2 = sigma * sigma;
+    for (int t = tid; t < SmDim<MC>::NBLK * 256; t += TINY_THREADS) {
+      const int b = t >> 8, ln = (t & 255) >> 2, e = t & 3;
+      double sum = 0.0;
+#pragma unroll
+      for (int w = 0; w < TY_NW; ++w) sum += S.red[w][b][t & 255];
+      sum *= sg2;
+      const int i = (b == 2 ? 16 : 0) + (ln >> 4) + 4 * e, j = (b > 0 ? 16 : 0) + (ln & 15);
+      S.core.A[i * SM_LD + j] = sum;
+      if (b == 1) S.core.A[j * SM_LD + i] = sum;
+    }
+    __syncthreads();
+  }
+  const double* const P = sm_iterate<TY_NW>(S.core, NB, ns);
+
+  // O = sigma P (L M R), its norm and ||L O R||.
+  double o2 = 0.0, d2 = 0.0;
+  {
+    double pa[NB][MC > 16 ? 8 : 4];
+    sm_operand<MC>(P, sigma, pa, lane);
+#pragma unroll
+    for (int q = 0; q < CPT; ++q) {
+      const int c0 = q * TINY_THREADS + wave * 64;
+      if (c0 >= nc) continue;
+      sm_stage<MC>(buf, x[q], lane);
+      S.colf[wave][lane] = colf[q];
+      sm_apply<MC>(buf, pa, S.rowf, S.colf[wave], O, np, mc, nc, c0, lane, o2, d2);
+    }
+  }
+  sm_block_sum<TY_NW>(o2, d2, S.red2);   // its barriers also order O's writes before the reads below
+  const double graft = sqrt(o2) / (sqrt(d2) + a.eps), coef_d = a.lr * alpha * graft;
+  if (tid == 0) {
+    if constexpr (MALTER) nu_p[0] = (float)nu;
+    scal[SC_S] = s;
+    scal[SC_SIGMA] = sigma;
+    scal[SC_NU] = nu;
+    scal[SC_Q] = q2;
+    scal[SC_ALPHA] = alpha;
+    scal[SC_O2] = o2;
+    scal[SC_D2] = d2;
+    scal[SC_GRAFT] = graft;
+    scal[SC_COEF] = coef_d;
+  }
+
+  // W <- decay W - coef L O R.
+  const float coef = (float)coef_d;
+#pragma unroll
+  for (int q = 0; q < CPT; ++q) {
+    const int c = tid + q * TINY_THREADS;
+    if (q * TINY_THREADS >= nc) continue;
+    float w[MC];
+    tiny_load<MC>(v.W, v, mc, nc, c, w);
+#pragma unroll
+    for (int i = 0; i < MC; ++i) {
+      const float o = i < mc && c < nc ? bf16_lo(O[(size_t)i * np + c]) : 0.f;
+      const float f = S.rowf[i];
+      w[i] = tall ? a.decay * w[i] - coef * colf[q] * o * f : a.decay * w[i] - coef * f * o * colf[q];
+    }
+    tiny_store<MC>(v.W, v, mc, nc, c, w);
+  }
+}
+
+template <bool MALTER>
+__global__ __launch_bounds__(TINY_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void tiny_step_kernel(SmallArgs ns) {
+  extern __shared__ __attribute__((aligned(16))) char lds[];
+  TinyLds& S = *reinterpret_cast<TinyLds*>(lds);
+  const Tile t = ns.e.tiles[blockIdx.x];   // (mat, rows held per column, -, -)
+  if (t.ti == 8) tiny_step<MALTER, 8, TINY_VALUES / 8>(ns, t.mat, S);
+  else if (t.ti == 16) tiny_step<MALTER, 16, TINY_VALUES / 16>(ns, t.mat, S);
+  else tiny_step<MALTER, 32, TINY_VALUES / 32>(ns, t.mat, S);
+}
+
+// ---------------------------------------------------------------------------
+// The three launches of larger matrices.
+// ---------------------------------------------------------------------------
+constexpr int SL_NW = NTHREADS / 64;
+static_assert(SM_CH_U == NTHREADS, "one column per thread in the product");
+
+// Column c of L M R in the canonical orientation (rows < SM_M).
+__device__ __forceinline__ void sm_column(const MatDesc& d, int c, float (&x)[SM_M]) {
+  const float cf = c < d.nc ? gptr(d.tall ? d.Lv : d.Rv)[c] : 0.f;
+  const MALT_GLOBAL float* const rf = gptr(d.tall ? d.Rv : d.Lv);
+  const MALT_GLOBAL float* const M = gptr(d.M);
+#pragma unroll
+  for (int i = 0; i < SM_M; ++i) {
+    if (i >= d.mc || c >= d.nc) x[i] = 0.f;
+    else if (!d.tall) x[i] = rf[i] * M[(size_t)i * d.n + c] * cf;
+    else x[i] = cf * M[(size_t)c * d.n + i] * rf[i];
+  }
+}
+
+__global__ __launch_bounds__(NTHREADS) void sm_gram_kernel(SmallArgs ns) {
+  __shared__ union { float stage[SL_NW * SM_WAVE]; double red[SL_NW][3][64 * 4]; } S;
+  const Tile t = ns.e.tiles[blockIdx.x];   // (mat, chunk, -, -)
+  const MatDesc& d = ns.e.desc[t.mat];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  float* const buf = S.stage + wave * SM_WAVE;
+  f64x4 acc[3] = {sm_zero(), sm_zero(), sm_zero()};
+  const int c0 = t.ti * d.sm_chunk, c1 = min(c0 + d.sm_chunk, d.nc);
+  for (int c = c0 + wave * 64; c < c1; c += NTHREADS) {
+    float x[SM_M];
+    sm_column(d, c + lane < c1 ? c + lane : d.nc, x);
+    sm_stage<SM_M>(buf, x, lane);
+    sm_gram<SM_M>(buf, acc, lane);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int b = 0; b < 3; ++b)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) S.red[wave][b][lane * 4 + e] = acc[b][e];
+  __syncthreads();
+  // Blocks as they lie in the accumulators; the iteration unpacks them.
+  MALT_GLOBAL double* const out = gptr(d.Ap) + (size_t)t.ti * SM_PART;
+  for (int q = threadIdx.x; q < SM_PART; q += NTHREADS)
+    out[q] = (S.red[0][q >> 8][q & 255] + S.red[1][q >> 8][q & 255]) + (S.red[2][q >> 8][q & 255] + S.red[3][q >> 8][q & 255]);
+}
+
+__global__ __launch_bounds__(SM_PART) void sm_iterate_kernel(SmallArgs ns) {
+  __shared__ SmCore s;
+  const MatDesc& d = ns.e.desc[ns.e.tiles[blockIdx.x].mat];
+  const int tid = threadIdx.x;
+  const double sg = gptr(d.scal)[SC_SIGMA];
+  {
+    const MALT_GLOBAL double* const Ap = gptr(d.Ap);
+    double sum = 0.0;
+#pragma unroll 8
+    for (int ch = 0; ch < d.sm_gchunks; ++ch) sum += Ap[(size_t)ch * SM_PART + tid];
+    sum *= sg * sg;
+    const int b = tid >> 8, ln = (tid & 255) >> 2, e = tid & 3;
+    const int i = (b == 2 ? 16 : 0) + (ln >> 4) + 4 * e, j = (b > 0 ? 16 : 0) + (ln & 15);
+    s.A[i * SM_LD + j] = sum;
+    if (b == 1) s.A[j * SM_LD + i] = sum;
+  }
+  __syncthreads();
+  const double* const P = sm_iterate<SM_PART / 64>(s, 2, ns);
+  for (int q = tid; q < SM_M * SM_M; q += SM_PART) gptr(d.Bs)[q] = sg * P[(q / SM_M) * SM_LD + q % SM_M];
+}
+
+__global__ __launch_bounds__(NTHREADS) void sm_apply_kernel(SmallArgs ns) {
+  __shared__ float stage[SL_NW * SM_WAVE];
+  __shared__ double P[SM_M * SM_LD];
+  __shared__ float rowf[SM_M], colf[NTHREADS];
+  __shared__ double red[SL_NW][2];
+  const Tile t = ns.e.tiles[blockIdx.x];   // (mat, chunk, -, partial slot)
+  const MatDesc& d = ns.e.desc[t.mat];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int mc = d.mc, nc = d.nc, c = t.ti * SM_CH_U + tid;
+  for (int q = tid; q < SM_M * SM_M; q += NTHREADS) P[(q / SM_M) * SM_LD + q % SM_M] = gptr(d.Bs)[q];
+  if (tid < SM_M) rowf[tid] = tid < mc ? gptr(d.tall ? d.Rv : d.Lv)[tid] : 0.f;
+  colf[tid] = c < nc ? gptr(d.tall ? d.Lv : d.Rv)[c] : 0.f;
+  float x[SM_M];
+  sm_column(d, c, x);
+  sm_stage<SM_M>(stage + wave * SM_WAVE, x, lane);
+  __syncthreads();
+  double pa[2][8], o2 = 0.0, d2 = 0.0;
+  sm_operand<SM_M>(P, 1.0, pa, lane);
+  sm_apply<SM_M>(stage + wave * SM_WAVE, pa, rowf, colf + wave * 64, gptr(d.X[ns.e.o_parity]), d.np, mc, nc,
+                 t.ti * SM_CH_U + wave * 64, lane, o2, d2);
+  sm_block_sum<SL_NW>(o2, d2, red);
+  if (tid == 0) {
+    gptr(d.gpart)[2 * (size_t)t.idx + 0] = (float)o2;
+    gptr(d.gpart)[2 * (size_t)t.idx + 1] = (float)d2;
+  }
+}
+
+}  // namespace
+
+hipError_t small_ns_setup() {
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&tiny_step_kernel<false>),
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, sizeof(TinyLds));
+  if (e == hipSuccess)
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&tiny_step_kernel<true>),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, sizeof(TinyLds));
+  return e;
+}
+
+hipError_t launch_tiny_step(const SmallArgs& a, hipStream_t s) {
+  if (a.e.ntiles == 0) return hipSuccess;
+  if (a.e.malter)
+    hipLaunchKernelGGL(tiny_step_kernel<true>, dim3(a.e.ntiles), dim3(TINY_THREADS), sizeof(TinyLds), s, a);
   else
-    hipLaunchKernelGGL(sm_update_kernel, dim3(a.ntiles), dim3(NTHREADS), 0, s, a);
+    hipLaunchKernelGGL(tiny_step_kernel<false>, dim3(a.e.ntiles), dim3(TINY_THREADS), sizeof(TinyLds), s, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_small_ns(const SmallArgs& a, int phase, hipStream_t s) {
+  if (a.e.ntiles == 0) return hipSuccess;
+  if (phase == PH_GRAM)
+    hipLaunchKernelGGL(sm_gram_kernel, dim3(a.e.ntiles), dim3(NTHREADS), 0, s, a);
+  else if (phase == PH_POLY)
+    hipLaunchKernelGGL(sm_iterate_kernel, dim3(a.e.ntiles), dim3(SM_PART), 0, s, a);
+  else
+    hipLaunchKernelGGL(sm_apply_kernel, dim3(a.e.ntiles), dim3(NTHREADS), 0, s, a);
   return hipGetLastError();
 }
 
