@@ -478,9 +478,8 @@ Layout make_layout(const malt_shape_t* shapes, int32_t n, malt_variant_t variant
     p.mp = pad_to(p.mc, NS_TILE); p.np = pad_to(p.nc, NS_TILE);
     p.small = p.mc <= NS_SMALL_MAX;
     p.split = !p.small && p.mc <= NS_SPLIT_MAX;
-    // A thread holds 8, 16 or 32 rows per column, TINY_VALUES values in all.
     p.tiny_rows = p.mc <= 8 ? 8 : p.mc <= 16 ? 16 : 32;
-    p.tiny = p.small && p.nc <= int64_t(TINY_THREADS) * (TINY_VALUES / p.tiny_rows);
+    p.tiny = p.small && p.m * p.n <= TINY_ELEMS;
     p.sm_chunk = std::max<int64_t>(SM_CH_G, pad_to(cdiv(p.nc, SM_CHUNKS), NTHREADS));
     p.sm_gchunks = p.small && !p.tiny ? cdiv(p.nc, p.sm_chunk) : 0;
     p.k1_ct = cdiv(p.n, EW_TC); p.k1_rt = cdiv(p.m, EW_TR);
@@ -1098,7 +1097,7 @@ malt_status_t check_bounds(const Layout& L, const Lists& W, int64_t shrink, int6
                                               : check_mid<128>(B, PH_UPDATE, W.upd, no_tiles)))
     return B.st;
   // Short sides <= 32: chunk and partial-slot indices; the whole-step matrices'
-  // columns fit their workgroup's registers.
+  // rows fit their workgroup's registers.
   for (const Tile& t : smg) {
     if (!B.mat_ok("sm_gram", t)) return B.st;
     const MatPlan& q = L.mats[t.mat];
@@ -1124,7 +1123,7 @@ malt_status_t check_bounds(const Layout& L, const Lists& W, int64_t shrink, int6
     if (!B.mat_ok("tiny_step", t)) return B.st;
     const MatPlan& q = L.mats[t.mat];
     if (!B.cond(q.tiny && (t.ti == 8 || t.ti == 16 || t.ti == 32) && q.mc <= t.ti && q.mc <= q.mp &&
-                    q.nc <= int64_t(TINY_THREADS) * (TINY_VALUES / t.ti) && q.nc <= q.np,
+                    q.nc <= q.np,
                 "tiny_step", t, "matrix does not fit a whole-step workgroup"))
       return B.st;
   }

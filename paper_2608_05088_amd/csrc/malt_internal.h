@@ -39,14 +39,13 @@ constexpr int NTHREADS = 256;
 // Preconditioner finalise: rows or columns per workgroup (4 threads each).
 constexpr int FIN_W = 64;
 // Matrices whose short side is at most this run Newton-Schulz in the Gram space
-// in float64 (small_ns.hip).  Those of at most TINY_VALUES columns per thread of
-// TINY_THREADS at 8, 16 or 32 rows each (a thread's columns lie in its
-// registers) take their whole step in one workgroup; the others a Gram over
-// chunks of at least SM_CH_G columns, at most SM_CHUNKS of them, and the final
-// product over SM_CH_U columns (one per thread).
+// in float64 (small_ns.hip).  Those of at most TINY_ELEMS elements take their
+// whole step in one workgroup; the others a Gram over chunks of at least SM_CH_G
+// columns, at most SM_CHUNKS of them, and the final product over SM_CH_U columns
+// (one per thread).
 constexpr int NS_SMALL_MAX = 32;
 constexpr int TINY_THREADS = 512;
-constexpr int TINY_VALUES = 128;
+constexpr int TINY_ELEMS = 65536;
 constexpr int SM_CH_G = 1024;
 constexpr int SM_CHUNKS = 128;
 constexpr int SM_CH_U = 256;

@@ -15,16 +15,16 @@
 // final O is rounded to bf16.
 //
 // Two routes:
-//   whole step   a matrix of at most 8192 columns in canonical orientation for
-//                m' <= 8, 4096 for m' <= 16, 2048 for m' <= 32 takes its whole
-//                step in one workgroup (tiny_step_kernel), its columns in
-//                registers: one launch for all such matrices of a plan, in
-//                place of 21.  What bounds it is the chain of its phases.
+//   whole step   a matrix of at most TINY_ELEMS elements takes its whole step
+//                in one workgroup (tiny_step_kernel): one launch for all such
+//                matrices of a plan, in place of 21.  What bounds it is the
+//                chain of its phases, and for the larger ones what one CU can
+//                read.
 //   three launches   larger ones take the plan's elementwise passes, and here
 //                a Gram over column chunks, one workgroup per matrix for the
 //                iteration, and the product with P over column chunks.
-// Measured (us per step): one 5 x 5 matrix 108 -> 46; 96 matrices of rank 16
-// (16 x 1024, 1024 x 16, 3072 x 16) 580 -> 60.
+// Measured (us per step): one 5 x 5 matrix 108 -> 16; 96 matrices of rank 16
+// (16 x 1024, 1024 x 16, 3072 x 16) 580 -> 107, of which the GPU 65.
 #include "malt_internal.h"
 
 namespace malt {
@@ -37,7 +37,9 @@ typedef float sm_f32x4 __attribute__((ext_vector_type(4)));
 constexpr int SM_M = NS_SMALL_MAX;          // 32
 constexpr int SM_LD = SM_M + 1;             // row pitch of an m' x m' matrix in LDS (doubles)
 constexpr int SM_PITCH = 64 + 1;            // row pitch of a wave's 64 staged columns (floats)
-constexpr int SM_WAVE = SM_M * SM_PITCH;    // one wave's staged columns (floats)
+constexpr int SM_TALL = SM_M + 1;           // pitch of the same columns as rows of a tall W
+constexpr int SM_WAVE = 64 * SM_TALL + 1;   // one wave's staging area (floats)
+static_assert(SM_M * SM_PITCH <= SM_WAVE, "columns staged by row");
 
 // Blocks of 16 rows, and of 16 x 16 upper blocks, of m' <= MC.
 template <int MC>
@@ -134,18 +136,19 @@ __device__ __forceinline__ const double* sm_iterate(SmCore& s, int NB, const Sma
   return s.P[cur];
 }
 
-// Sums of (o^2, (Lm o Ln)^2) of the product with P for a wave's 64 staged
-// columns c0 .. c0 + 63; writes O rounded to bf16 (rows < mc, columns < nc).
-// rowf: canonical row factors; colf: the 64 columns' factors.
+// The product with P for a wave's 64 columns: x becomes O rounded to bf16 (0
+// past mc rows and past the matrix), (o2, d2) gain its sums of o^2 and (Lm o
+// Ln)^2.  rowf: canonical row factors (0 past mc); cf: this lane's column
+// factor; in: its column lies in the matrix.
 template <int MC>
-__device__ __forceinline__ void sm_apply(const float* buf, const double (&pa)[SmDim<MC>::NB][MC > 16 ? 8 : 4],
-                                         const float* rowf, const float* colf, MALT_GLOBAL bf16_t* O, int np, int mc,
-                                         int nc, int c0, int lane, double& o2, double& d2) {
+__device__ __forceinline__ void sm_apply(float* buf, const double (&pa)[SmDim<MC>::NB][MC > 16 ? 8 : 4],
+                                         const float* rowf, float cf, bool in, int mc, int lane, float (&x)[MC],
+                                         double& o2, double& d2) {
   constexpr int NB = SmDim<MC>::NB, KS = MC > 16 ? 8 : 4;
-#pragma unroll 1
+  sm_stage<MC>(buf, x, lane);
+#pragma unroll
   for (int g = 0; g < 4; ++g) {
-    const int cl = 16 * g + (lane & 15), c = c0 + cl;
-    if (c0 + 16 * g >= nc) break;   // uniform over the wave
+    const int cl = 16 * g + (lane & 15);
     f64x4 y[NB];
 #pragma unroll
     for (int b = 0; b < NB; ++b) y[b] = sm_zero();
@@ -155,24 +158,35 @@ __device__ __forceinline__ void sm_apply(const float* buf, const double (&pa)[Sm
 #pragma unroll
       for (int b = 0; b < NB; ++b) y[b] = __builtin_amdgcn_mfma_f64_16x16x4f64(pa[b][k], xb, y[b], 0, 0, 0);
     }
-    const float ln = colf[cl];
-    float so = 0.f, sd = 0.f;
+    // Back in place: this group's columns have been read.
 #pragma unroll
     for (int b = 0; b < NB; ++b)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int i = 16 * b + (lane >> 4) + 4 * r;
-        const uint32_t pk = pack_bf16x2((float)y[b][r], 0.f);
-        if (i < mc && c < nc) {
-          O[(size_t)i * np + c] = (bf16_t)(pk & 0xffffu);
-          const float o = bf16_lo(pk), lm = rowf[i];
-          so += o * o;
-          sd += lm * lm * ln * ln * (o * o);
-        }
+        if (MC >= 16 || i < MC) buf[i * SM_PITCH + cl] = (float)y[b][r];
       }
-    o2 += (double)so;
-    d2 += (double)sd;
   }
+  float so = 0.f, sd = 0.f;
+#pragma unroll
+  for (int i = 0; i < MC; ++i) {
+    const float o = in && i < mc ? bf16_lo(pack_bf16x2(buf[i * SM_PITCH + lane], 0.f)) : 0.f;
+    const float lm = rowf[i];
+    x[i] = o;
+    so += o * o;
+    sd += lm * lm * (o * o);
+  }
+  o2 += (double)so;
+  d2 += (double)(cf * cf * sd);
+}
+
+// Column c of the canonical O, already rounded (rows < mc).
+template <int MC>
+__device__ __forceinline__ void sm_store_o(MALT_GLOBAL bf16_t* O, int np, int mc, int c, bool in, const float (&x)[MC]) {
+  if (!in) return;
+#pragma unroll
+  for (int i = 0; i < MC; ++i)
+    if (i < mc) O[(size_t)i * np + c] = (bf16_t)(__float_as_uint(x[i]) >> 16);
 }
 
 // MFMA operand of P scaled by sigma: pa[b][k] = sigma P(16 b + l % 16, 4 k + l / 16).
@@ -222,58 +236,121 @@ constexpr int TY_NW = TINY_THREADS / 64;
 struct TinyLds {
   union {
     float stage[TY_NW * SM_WAVE];
-    double red[TY_NW][3][64 * 4];   // Gram blocks of the waves
+    struct {
+      double red[TY_NW][3][64 * 4];   // Gram blocks of the waves
+      SmCore core;
+    };
   };
-  SmCore core;
-  float colf[TY_NW][64];
   float rowf[SM_M];
   float rows[TY_NW][SM_M];
   double red2[TY_NW][2];
 };
 static_assert(sizeof(TinyLds) <= 160 * 1024, "LDS of a whole-step workgroup");
 
-// Canonical column c of a W-shaped array: W(i, c) of a wide, W(c, i) of a tall
-// matrix (n = its column count).  Rows past mc and columns past nc read 0.
-template <int MC>
-__device__ __forceinline__ void tiny_load(const MALT_GLOBAL float* __restrict__ p, const EwView& v, int mc, int nc,
-                                          int c, float (&x)[MC]) {
-  if (c >= nc) {
+// The columns of a wave in memory: canonical columns c0 .. c0 + 63 of a W-shaped
+// array.  Of a wide matrix (canonical (i, c) = W(i, c)) lane l takes column c0 +
+// l row by row.  Of a tall one (W(c, i), n = mc columns) the 64 columns are 64 n
+// consecutive floats: they are read in that order, so that every access is
+// whole cache lines, and change places through the wave's staging area.
+struct TinyCols {
+  bool tall;
+  int n, mc, nc, c0, lane;
+  uint32_t inv;   // floor(e / n) = (e * inv) >> 16 for e < 64 n <= 2048
+};
+
+// FULL: m' = MC rows and whole rounds of 64 columns, nothing to test.  Otherwise
+// loads stay unconditional, at clamped positions (behind a bounds branch each,
+// the compiler waits for one before it issues the next), and tiny_mask zeroes
+// what lies past the matrix.
+template <int MC, bool FULL>
+__device__ __forceinline__ void tiny_load(const MALT_GLOBAL float* p, const TinyCols& t, float (&x)[MC]) {
+  if constexpr (FULL) {
+    if (!t.tall) {
 #pragma unroll
-    for (int i = 0; i < MC; ++i) x[i] = 0.f;
-  } else if (!v.tall) {
+      for (int i = 0; i < MC; ++i) x[i] = p[i * t.n + (t.c0 + t.lane)];
+    } else {
 #pragma unroll
-    for (int i = 0; i < MC; ++i) x[i] = i < mc ? p[(size_t)i * v.n + c] : 0.f;
-  } else if (v.vec) {
-#pragma unroll
-    for (int i = 0; i < MC; i += 4) {
-      sm_f32x4 q = {0.f, 0.f, 0.f, 0.f};
-      if (i < mc) q = *reinterpret_cast<const MALT_GLOBAL sm_f32x4*>(p + (size_t)c * v.n + i);   // n % 4 == 0
-#pragma unroll
-      for (int e = 0; e < 4; ++e) x[i + e] = q[e];
+      for (int i = 0; i < MC; ++i) x[i] = p[t.c0 * MC + t.lane + i * 64];
     }
   } else {
+    const int c = t.c0 + t.lane, total = (t.nc - t.c0) * t.n;
+    const int cc = min(c, t.nc - 1), base = t.c0 * t.n;
 #pragma unroll
-    for (int i = 0; i < MC; ++i) x[i] = i < mc ? p[(size_t)c * v.n + i] : 0.f;
+    for (int i = 0; i < MC; ++i)
+      x[i] = p[t.tall ? base + min(i * 64 + t.lane, total - 1) : min(i, t.mc - 1) * t.n + cc];
   }
 }
 
-template <int MC>
-__device__ __forceinline__ void tiny_store(MALT_GLOBAL float* __restrict__ p, const EwView& v, int mc, int nc, int c,
-                                           const float (&x)[MC]) {
-  if (c >= nc) return;
-  if (!v.tall) {
+template <int MC, bool FULL>
+__device__ __forceinline__ void tiny_mask(const TinyCols& t, float (&x)[MC]) {
+  if constexpr (FULL) return;
+  const int c = t.c0 + t.lane, total = (t.nc - t.c0) * t.n;
 #pragma unroll
-    for (int i = 0; i < MC; ++i)
-      if (i < mc) p[(size_t)i * v.n + c] = x[i];
-  } else if (v.vec) {
+  for (int i = 0; i < MC; ++i) {
+    const bool in = i < t.mc && (t.tall ? i * 64 + t.lane < total : c < t.nc);
+    x[i] = in ? x[i] : 0.f;
+  }
+}
+
+// Place in the staging area of the i-th value a lane reads of a tall matrix;
+// the spare element past the columns where there is none.
+template <int MC, bool FULL>
+__device__ __forceinline__ int tiny_place(const TinyCols& t, int i) {
+  const uint32_t e = i * 64 + t.lane;
+  if constexpr (FULL) return (e / MC) * SM_TALL + e % MC;
+  const uint32_t c = (e * t.inv) >> 16;
+  return i < t.mc ? c * SM_TALL + (e - c * t.n) : 64 * SM_TALL;
+}
+
+// What tiny_load read, as this lane's column.
+template <int MC, bool FULL>
+__device__ __forceinline__ void tiny_own(float* buf, const TinyCols& t, float (&x)[MC]) {
+  if (!t.tall) return;
 #pragma unroll
-    for (int i = 0; i < MC; i += 4)
-      if (i < mc)
-        *reinterpret_cast<MALT_GLOBAL sm_f32x4*>(p + (size_t)c * v.n + i) = sm_f32x4{x[i], x[i + 1], x[i + 2], x[i + 3]};
+  for (int i = 0; i < MC; ++i) buf[tiny_place<MC, FULL>(t, i)] = x[i];
+#pragma unroll
+  for (int i = 0; i < MC; ++i) x[i] = FULL || i < t.mc ? buf[t.lane * SM_TALL + i] : 0.f;
+}
+
+// The opposite: this lane's column, in the order of memory.
+template <int MC, bool FULL>
+__device__ __forceinline__ void tiny_give(float* buf, const TinyCols& t, float (&x)[MC]) {
+  if (!t.tall) return;
+#pragma unroll
+  for (int i = 0; i < MC; ++i) buf[t.lane * SM_TALL + i] = x[i];
+#pragma unroll
+  for (int i = 0; i < MC; ++i) x[i] = buf[tiny_place<MC, FULL>(t, i)];
+}
+
+// Stores values in the order tiny_load reads them.
+template <int MC, bool FULL>
+__device__ __forceinline__ void tiny_put(MALT_GLOBAL float* p, const TinyCols& t, const float (&x)[MC]) {
+  if constexpr (FULL) {
+    if (!t.tall) {
+#pragma unroll
+      for (int i = 0; i < MC; ++i) p[i * t.n + (t.c0 + t.lane)] = x[i];
+    } else {
+#pragma unroll
+      for (int i = 0; i < MC; ++i) p[t.c0 * MC + t.lane + i * 64] = x[i];
+    }
   } else {
+    const int c = t.c0 + t.lane, total = (t.nc - t.c0) * t.n;
 #pragma unroll
-    for (int i = 0; i < MC; ++i)
-      if (i < mc) p[(size_t)c * v.n + i] = x[i];
+    for (int i = 0; i < MC; ++i) {
+      const bool in = i < t.mc && (t.tall ? i * 64 + t.lane < total : c < t.nc);
+      if (in) p[t.tall ? t.c0 * t.n + i * 64 + t.lane : i * t.n + c] = x[i];
+    }
+  }
+}
+
+// Canonical bf16 column c of X0 or O.
+template <int MC, bool FULL>
+__device__ __forceinline__ void tiny_put16(MALT_GLOBAL bf16_t* p, const TinyCols& t, int np, const float (&x)[MC]) {
+  const int c = t.c0 + t.lane;
+#pragma unroll
+  for (int i = 0; i < MC; ++i) {
+    const bf16_t h = (bf16_t)(pack_bf16x2(x[i], 0.f) & 0xffffu);
+    if (FULL || (i < t.mc && c < t.nc)) p[i * np + c] = h;
   }
 }
 
@@ -297,8 +374,16 @@ __device__ __forceinline__ float tiny_reduce(float (&v)[N], int lane) {
   return s;
 }
 
-// CPT columns per thread, m' <= MC rows of each in registers.
-template <bool MALTER, int MC, int CPT>
+// m' <= MC. Four passes over the matrix's columns, 64 per wave and round: the
+// momentum and sums, L M R with its norms and Gram, the product with P, the
+// update of W. The rounds are loops, not unrolled: with L M R in registers
+// between the passes, every round unrolled, the code ran to hundreds of
+// kilobytes executed once, and the step of a 3072 x 16 matrix took 98 us.  A
+// round's loads are issued before the previous round is worked on, so that
+// waiting for them does not wait for that round's stores.  us of a step: 16 x
+// 1024 27 (55 with a bounds branch per row, 39 with clamped positions only),
+// 3072 x 16 62, 32 x 1024 63, 8 x 4096 54.
+template <bool MALTER, int MC, bool FULL>
 __device__ __forceinline__ void tiny_step(const SmallArgs& ns, int mat, TinyLds& S) {
   constexpr int NB = SmDim<MC>::NB;
   constexpr int LOG = MC == 32 ? 5 : MC == 16 ? 4 : 3;
@@ -307,51 +392,66 @@ __device__ __forceinline__ void tiny_step(const SmallArgs& ns, int mat, TinyLds&
   const EwView v = ew_view(a, mat);
   const int mc = d.mc, nc = d.nc, np = v.np;
   const bool tall = v.tall != 0;
-  MALT_GLOBAL float* const l = gptr(d.l);
-  MALT_GLOBAL float* const r = gptr(d.r);
-  MALT_GLOBAL float* const nu_p = gptr(d.nu);
   MALT_GLOBAL double* const scal = gptr(d.scal);
+  MALT_GLOBAL float* const nu_p = gptr(d.nu);
   MALT_GLOBAL bf16_t* const O = gptr(d.X[a.o_parity]);
-  MALT_GLOBAL float* const Lw = gptr(d.Lv);
-  MALT_GLOBAL float* const Rw = gptr(d.Rv);
+  // Column and row factors of the canonical orientation, and their EMAs.
+  MALT_GLOBAL float* const cema = gptr(tall ? d.l : d.r);
+  MALT_GLOBAL float* const cinv = gptr(tall ? d.Lv : d.Rv);
+  MALT_GLOBAL float* const rema = gptr(tall ? d.r : d.l);
+  MALT_GLOBAL float* const rinv = gptr(tall ? d.Rv : d.Lv);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   float* const buf = S.stage + wave * SM_WAVE;
+  TinyCols t{tall, v.n, mc, nc, 0, lane, 65536u / (uint32_t)v.n + 1u};
+
+  auto next = [](TinyCols q) {
+    q.c0 += TINY_THREADS;
+    return q;
+  };
+  auto copy = [](float (&to)[MC], const float (&from)[MC]) {
+#pragma unroll
+    for (int i = 0; i < MC; ++i) to[i] = from[i];
+  };
 
   // Momentum, and the row and column sums of G^2.
-  float x[CPT][MC], colf[CPT];
   {
     float rs[MC];
 #pragma unroll
     for (int i = 0; i < MC; ++i) rs[i] = 0.f;
-    MALT_GLOBAL float* const cema = tall ? l : r;
-    MALT_GLOBAL float* const cinv = tall ? Lw : Rw;
+    float gn[MC], mn[MC], en;
+    auto fetch = [&](const TinyCols& t) {
+      tiny_load<MC, FULL>(v.G, t, gn);
+      tiny_load<MC, FULL>(v.M, t, mn);
+      en = cema[min(t.c0 + lane, nc - 1)];
+    };
+    t.c0 = wave * 64;
+    if (t.c0 < nc) fetch(t);
+#pragma unroll 1
+    for (; t.c0 < nc; t.c0 += TINY_THREADS) {
+      const int c = t.c0 + lane;
+      float g[MC], m[MC];
+      copy(g, gn);
+      copy(m, mn);
+      const double old = (double)en;
+      if (const TinyCols nx = next(t); nx.c0 < nc) fetch(nx);
+      tiny_mask<MC, FULL>(t, g);
 #pragma unroll
-    for (int q = 0; q < CPT; ++q) {
-      const int c = tid + q * TINY_THREADS;
-      if (q * TINY_THREADS >= nc) {   // uniform
-#pragma unroll
-        for (int i = 0; i < MC; ++i) x[q][i] = 0.f;
-        colf[q] = 0.f;
-        continue;
+      for (int i = 0; i < MC; ++i) {
+        m[i] = a.mu1 * m[i] + a.one_minus_mu1 * g[i];
+        g[i] *= g[i];
       }
-      float g[MC];
-      tiny_load<MC>(v.G, v, mc, nc, c, g);
-      tiny_load<MC>(v.M, v, mc, nc, c, x[q]);
+      tiny_put<MC, FULL>(v.M, t, m);
+      tiny_own<MC, FULL>(buf, t, g);
       float cs = 0.f;
 #pragma unroll
       for (int i = 0; i < MC; ++i) {
-        x[q][i] = a.mu1 * x[q][i] + a.one_minus_mu1 * g[i];
-        const float g2 = g[i] * g[i];
-        cs += g2;
-        rs[i] += g2;
+        cs += g[i];
+        rs[i] += g[i];
       }
-      tiny_store<MC>(v.M, v, mc, nc, c, x[q]);
-      colf[q] = 0.f;
-      if (c < nc) {
-        const double e = a.mu2 * (double)cema[c] + (1.0 - a.mu2) * (double)cs;
+      if (FULL || c < nc) {
+        const double e = a.mu2 * old + (1.0 - a.mu2) * (double)cs;
         cema[c] = (float)e;
-        colf[q] = a.identity ? 1.f : sm_inv_eighth(e + a.eps);
-        cinv[c] = colf[q];
+        cinv[c] = a.identity ? 1.f : sm_inv_eighth(e + a.eps);
       }
     }
     const float s = tiny_reduce<MC>(rs, lane);
@@ -361,97 +461,115 @@ __device__ __forceinline__ void tiny_step(const SmallArgs& ns, int mat, TinyLds&
   if (tid < SM_M) {
     float f = 0.f;
     if (tid < mc) {
-      MALT_GLOBAL float* const rema = tall ? r : l;
       double s = 0.0;
 #pragma unroll
       for (int w = 0; w < TY_NW; ++w) s += (double)S.rows[w][tid];
       const double e = a.mu2 * (double)rema[tid] + (1.0 - a.mu2) * s;
       rema[tid] = (float)e;
       f = a.identity ? 1.f : sm_inv_eighth(e + a.eps);
-      (tall ? Rw : Lw)[tid] = f;
+      rinv[tid] = f;
     }
     S.rowf[tid] = f;
   }
   __syncthreads();
 
-  // L M R (X0 before its normalisation), its norm and MALTER's ||L G R||.
-  double s2 = 0.0, q2 = 0.0;
+  // Column c of L M R (or L G R) from M (G), in W's order of the two products.
+  auto scale = [&](float (&x)[MC], float cf) {
 #pragma unroll
-  for (int q = 0; q < CPT; ++q) {
-    const int c = tid + q * TINY_THREADS;
-    if (q * TINY_THREADS >= nc) continue;
-    float g[MALTER ? MC : 1];
-    if constexpr (MALTER) tiny_load<MC>(v.G, v, mc, nc, c, g);
+    for (int i = 0; i < MC; ++i) x[i] = tall ? cf * x[i] * S.rowf[i] : S.rowf[i] * x[i] * cf;
+  };
+
+  // L M R (X0 before its normalisation), its Gram and norm, MALTER's ||L G R||.
+  double s2 = 0.0, q2 = 0.0;
+  f64x4 acc[SmDim<MC>::NBLK];
+#pragma unroll
+  for (int b = 0; b < SmDim<MC>::NBLK; ++b) acc[b] = sm_zero();
+  float xn[MC], gn[MC], cn;
+  auto fetch = [&](const MALT_GLOBAL float* p, const TinyCols& t) {
+    tiny_load<MC, FULL>(p, t, xn);
+    cn = cinv[min(t.c0 + lane, nc - 1)];
+  };
+  t.c0 = wave * 64;
+  if (t.c0 < nc) {
+    fetch(v.M, t);
+    if constexpr (MALTER) tiny_load<MC, FULL>(v.G, t, gn);
+  }
+#pragma unroll 1
+  for (; t.c0 < nc; t.c0 += TINY_THREADS) {
+    const int c = t.c0 + lane;
+    float x[MC], g[MC];
+    copy(x, xn);
+    if constexpr (MALTER) copy(g, gn);
+    const float cf = FULL || c < nc ? cn : 0.f;
+    if (const TinyCols nx = next(t); nx.c0 < nc) {
+      fetch(v.M, nx);
+      if constexpr (MALTER) tiny_load<MC, FULL>(v.G, nx, gn);
+    }
+    tiny_mask<MC, FULL>(t, x);
+    tiny_own<MC, FULL>(buf, t, x);
+    scale(x, cf);
     float sx = 0.f, sg = 0.f;
 #pragma unroll
-    for (int i = 0; i < MC; ++i) {
-      const float f = S.rowf[i];
-      x[q][i] = tall ? colf[q] * x[q][i] * f : f * x[q][i] * colf[q];
-      sx += x[q][i] * x[q][i];
-      if constexpr (MALTER) {
-        const float y = tall ? colf[q] * g[i] * f : f * g[i] * colf[q];
-        sg += y * y;
-      }
-      if (i < mc && c < nc) v.X0[(size_t)i * np + c] = (bf16_t)(pack_bf16x2(x[q][i], 0.f) & 0xffffu);
+    for (int i = 0; i < MC; ++i) sx += x[i] * x[i];
+    if constexpr (MALTER) {
+      tiny_mask<MC, FULL>(t, g);
+      tiny_own<MC, FULL>(buf, t, g);
+      scale(g, cf);
+#pragma unroll
+      for (int i = 0; i < MC; ++i) sg += g[i] * g[i];
     }
     s2 += (double)sx;
     q2 += (double)sg;
+    tiny_put16<MC, FULL>(v.X0, t, np, x);
+    sm_stage<MC>(buf, x, lane);
+    sm_gram<MC>(buf, acc, lane);
   }
-  sm_block_sum<TY_NW>(s2, q2, S.red2);
+  sm_block_sum<TY_NW>(s2, q2, S.red2);   // its barriers also free the staging rows for the blocks
   const double s = sqrt(s2), sigma = 1.0 / (s + a.ns_eps);
   double nu = 0.0, alpha = 1.0;
   if constexpr (MALTER) {
     nu = a.mu2 * (double)nu_p[0] + (1.0 - a.mu2) * q2;
     alpha = a.bc * s / (sqrt(nu) + a.eps);
   }
-
+#pragma unroll
+  for (int b = 0; b < SmDim<MC>::NBLK; ++b)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) S.red[wave][b][lane * 4 + e] = acc[b][e];
+  __syncthreads();
   // A_0 = sigma^2 (L M R)(L M R)^T.
-  {
-    f64x4 acc[SmDim<MC>::NBLK];
+  for (int q = tid; q < SmDim<MC>::NBLK * 256; q += TINY_THREADS) {
+    const int b = q >> 8, ln = (q & 255) >> 2, e = q & 3;
+    double sum = 0.0;
 #pragma unroll
-    for (int b = 0; b < SmDim<MC>::NBLK; ++b) acc[b] = sm_zero();
-#pragma unroll
-    for (int q = 0; q < CPT; ++q) {
-      if (q * TINY_THREADS + wave * 64 >= nc) continue;   // uniform over the wave
-      sm_stage<MC>(buf, x[q], lane);
-      sm_gram<MC>(buf, acc, lane);
-    }
-    __syncthreads();   // the staging rows become the waves' blocks
-#pragma unroll
-    for (int b = 0; b < SmDim<MC>::NBLK; ++b)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) S.red[wave][b][lane * 4 + e] = acc[b][e];
-    __syncthreads();
-    const double sg2 = sigma * sigma;
-    for (int t = tid; t < SmDim<MC>::NBLK * 256; t += TINY_THREADS) {
-      const int b = t >> 8, ln = (t & 255) >> 2, e = t & 3;
-      double sum = 0.0;
-#pragma unroll
-      for (int w = 0; w < TY_NW; ++w) sum += S.red[w][b][t & 255];
-      sum *= sg2;
-      const int i = (b == 2 ? 16 : 0) + (ln >> 4) + 4 * e, j = (b > 0 ? 16 : 0) + (ln & 15);
-      S.core.A[i * SM_LD + j] = sum;
-      if (b == 1) S.core.A[j * SM_LD + i] = sum;
-    }
-    __syncthreads();
+    for (int w = 0; w < TY_NW; ++w) sum += S.red[w][b][q & 255];
+    sum *= sigma * sigma;
+    const int i = (b == 2 ? 16 : 0) + (ln >> 4) + 4 * e, j = (b > 0 ? 16 : 0) + (ln & 15);
+    S.core.A[i * SM_LD + j] = sum;
+    if (b == 1) S.core.A[j * SM_LD + i] = sum;
   }
-  const double* const P = sm_iterate<TY_NW>(S.core, NB, ns);
+  __syncthreads();
+  double pa[NB][MC > 16 ? 8 : 4];
+  sm_operand<MC>(sm_iterate<TY_NW>(S.core, NB, ns), sigma, pa, lane);
+  __syncthreads();   // P is in registers; the staging rows are free again
 
   // O = sigma P (L M R), its norm and ||L O R||.
   double o2 = 0.0, d2 = 0.0;
-  {
-    double pa[NB][MC > 16 ? 8 : 4];
-    sm_operand<MC>(P, sigma, pa, lane);
-#pragma unroll
-    for (int q = 0; q < CPT; ++q) {
-      const int c0 = q * TINY_THREADS + wave * 64;
-      if (c0 >= nc) continue;
-      sm_stage<MC>(buf, x[q], lane);
-      S.colf[wave][lane] = colf[q];
-      sm_apply<MC>(buf, pa, S.rowf, S.colf[wave], O, np, mc, nc, c0, lane, o2, d2);
-    }
+  t.c0 = wave * 64;
+  if (t.c0 < nc) fetch(v.M, t);
+#pragma unroll 1
+  for (; t.c0 < nc; t.c0 += TINY_THREADS) {
+    const int c = t.c0 + lane;
+    float x[MC];
+    copy(x, xn);
+    const float cf = FULL || c < nc ? cn : 0.f;
+    if (const TinyCols nx = next(t); nx.c0 < nc) fetch(v.M, nx);
+    tiny_mask<MC, FULL>(t, x);
+    tiny_own<MC, FULL>(buf, t, x);
+    scale(x, cf);
+    sm_apply<MC>(buf, pa, S.rowf, cf, FULL || c < nc, FULL ? MC : mc, lane, x, o2, d2);
+    tiny_put16<MC, FULL>(O, t, np, x);
   }
-  sm_block_sum<TY_NW>(o2, d2, S.red2);   // its barriers also order O's writes before the reads below
+  sm_block_sum<TY_NW>(o2, d2, S.red2);
   const double graft = sqrt(o2) / (sqrt(d2) + a.eps), coef_d = a.lr * alpha * graft;
   if (tid == 0) {
     if constexpr (MALTER) nu_p[0] = (float)nu;
@@ -468,31 +586,56 @@ __device__ __forceinline__ void tiny_step(const SmallArgs& ns, int mat, TinyLds&
 
   // W <- decay W - coef L O R.
   const float coef = (float)coef_d;
+  bf16_t on[MC];
+  auto fetch_o = [&](const TinyCols& t) {
+    const int c = FULL ? t.c0 + lane : min(t.c0 + lane, nc - 1);
 #pragma unroll
-  for (int q = 0; q < CPT; ++q) {
-    const int c = tid + q * TINY_THREADS;
-    if (q * TINY_THREADS >= nc) continue;
-    float w[MC];
-    tiny_load<MC>(v.W, v, mc, nc, c, w);
+    for (int i = 0; i < MC; ++i) on[i] = O[(FULL ? i : min(i, mc - 1)) * np + c];
+  };
+  t.c0 = wave * 64;
+  if (t.c0 < nc) {
+    fetch(v.W, t);
+    fetch_o(t);
+  }
+#pragma unroll 1
+  for (; t.c0 < nc; t.c0 += TINY_THREADS) {
+    float w[MC], o[MC];
+    copy(w, xn);
+#pragma unroll
+    for (int i = 0; i < MC; ++i) o[i] = bf16_lo(on[i]);
+    const float cf = cn;
+    if (const TinyCols nx = next(t); nx.c0 < nc) {
+      fetch(v.W, nx);
+      fetch_o(nx);
+    }
+    tiny_own<MC, FULL>(buf, t, w);
 #pragma unroll
     for (int i = 0; i < MC; ++i) {
-      const float o = i < mc && c < nc ? bf16_lo(O[(size_t)i * np + c]) : 0.f;
       const float f = S.rowf[i];
-      w[i] = tall ? a.decay * w[i] - coef * colf[q] * o * f : a.decay * w[i] - coef * f * o * colf[q];
+      w[i] = tall ? a.decay * w[i] - coef * cf * o[i] * f : a.decay * w[i] - coef * f * o[i] * cf;
     }
-    tiny_store<MC>(v.W, v, mc, nc, c, w);
+    tiny_give<MC, FULL>(buf, t, w);
+    tiny_put<MC, FULL>(v.W, t, w);
   }
 }
 
 template <bool MALTER>
-__global__ __launch_bounds__(TINY_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
-void tiny_step_kernel(SmallArgs ns) {
+__global__ __launch_bounds__(TINY_THREADS) void tiny_step_kernel(SmallArgs ns) {
   extern __shared__ __attribute__((aligned(16))) char lds[];
   TinyLds& S = *reinterpret_cast<TinyLds*>(lds);
   const Tile t = ns.e.tiles[blockIdx.x];   // (mat, rows held per column, -, -)
-  if (t.ti == 8) tiny_step<MALTER, 8, TINY_VALUES / 8>(ns, t.mat, S);
-  else if (t.ti == 16) tiny_step<MALTER, 16, TINY_VALUES / 16>(ns, t.mat, S);
-  else tiny_step<MALTER, 32, TINY_VALUES / 32>(ns, t.mat, S);
+  const MatDesc& d = ns.e.desc[t.mat];
+  const bool full = d.mc == t.ti && d.nc % 64 == 0;
+  if (t.ti == 8) {
+    if (full) tiny_step<MALTER, 8, true>(ns, t.mat, S);
+    else tiny_step<MALTER, 8, false>(ns, t.mat, S);
+  } else if (t.ti == 16) {
+    if (full) tiny_step<MALTER, 16, true>(ns, t.mat, S);
+    else tiny_step<MALTER, 16, false>(ns, t.mat, S);
+  } else {
+    if (full) tiny_step<MALTER, 32, true>(ns, t.mat, S);
+    else tiny_step<MALTER, 32, false>(ns, t.mat, S);
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -564,7 +707,7 @@ __global__ __launch_bounds__(SM_PART) void sm_iterate_kernel(SmallArgs ns) {
 __global__ __launch_bounds__(NTHREADS) void sm_apply_kernel(SmallArgs ns) {
   __shared__ float stage[SL_NW * SM_WAVE];
   __shared__ double P[SM_M * SM_LD];
-  __shared__ float rowf[SM_M], colf[NTHREADS];
+  __shared__ float rowf[SM_M];
   __shared__ double red[SL_NW][2];
   const Tile t = ns.e.tiles[blockIdx.x];   // (mat, chunk, -, partial slot)
   const MatDesc& d = ns.e.desc[t.mat];
@@ -572,15 +715,14 @@ __global__ __launch_bounds__(NTHREADS) void sm_apply_kernel(SmallArgs ns) {
   const int mc = d.mc, nc = d.nc, c = t.ti * SM_CH_U + tid;
   for (int q = tid; q < SM_M * SM_M; q += NTHREADS) P[(q / SM_M) * SM_LD + q % SM_M] = gptr(d.Bs)[q];
   if (tid < SM_M) rowf[tid] = tid < mc ? gptr(d.tall ? d.Rv : d.Lv)[tid] : 0.f;
-  colf[tid] = c < nc ? gptr(d.tall ? d.Lv : d.Rv)[c] : 0.f;
+  const float cf = c < nc ? gptr(d.tall ? d.Lv : d.Rv)[c] : 0.f;
   float x[SM_M];
   sm_column(d, c, x);
-  sm_stage<SM_M>(stage + wave * SM_WAVE, x, lane);
   __syncthreads();
   double pa[2][8], o2 = 0.0, d2 = 0.0;
   sm_operand<SM_M>(P, 1.0, pa, lane);
-  sm_apply<SM_M>(stage + wave * SM_WAVE, pa, rowf, colf + wave * 64, gptr(d.X[ns.e.o_parity]), d.np, mc, nc,
-                 t.ti * SM_CH_U + wave * 64, lane, o2, d2);
+  sm_apply<SM_M>(stage + wave * SM_WAVE, pa, rowf, cf, c < nc, mc, lane, x, o2, d2);
+  sm_store_o<SM_M>(gptr(d.X[ns.e.o_parity]), d.np, mc, c, c < nc, x);
   sm_block_sum<SL_NW>(o2, d2, red);
   if (tid == 0) {
     gptr(d.gpart)[2 * (size_t)t.idx + 0] = (float)o2;
