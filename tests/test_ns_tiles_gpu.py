@@ -59,3 +59,23 @@ def test_cubic_iteration_on_256_tiles():
     g = run_gpu(shapes, "malt", W0, grads, hp, collect=[0, 35])
     o = run_oracle(shapes, "malt", W0, grads, hp, collect=[0, 35])
     say(f"[tiles] cubic worst {compare(g, o, 'malt', label='cubic')}")
+
+
+# Short sides: whole rows and rounds of the whole-step workgroup and their
+# remainders, wide and tall; its largest element count and the first past it
+# (three launches), a contraction of several Gram chunks.
+SHORT = [(8, 64), (64, 8), (16, 1024), (1024, 16), (32, 2048), (2048, 32), (9, 65), (63, 7), (1, 64), (1, 1), (31, 513),
+         (16, 4096), (16, 4097), (4097, 16), (32, 40000)]
+
+
+@pytest.mark.parametrize("variant,ns_steps", [("malt", 5), ("malter", 2), ("malter", 1)])
+def test_short_side_edges(variant, ns_steps):
+    say(f"[tiles] short sides {SHORT} {variant} ns_steps={ns_steps} x2")
+    W0 = [wl.weight(85, i, s) for i, s in enumerate(SHORT)]
+    grads = [[wl.grad(85, t, i, s, "row_loguniform") for i, s in enumerate(SHORT)] for t in (1, 2)]
+    g = run_gpu(SHORT, variant, W0, grads, dict(lr=1e-2, ns_steps=ns_steps))
+    o = run_oracle(SHORT, variant, W0, grads, dict(lr=1e-2, ns_steps=ns_steps))
+    # Only the final rounding of O to bf16 (2^-9 per entry at most) is left:
+    # 4e-3 covers it in norm, in O and in the update.
+    worst = compare(g, o, variant, tol_ns=4e-3, label="short")
+    say(f"[tiles] short worst {worst}")
