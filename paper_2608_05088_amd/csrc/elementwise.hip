@@ -18,12 +18,6 @@ __device__ __forceinline__ float wave_sum(float v) {
   return v;
 }
 
-__device__ __forceinline__ double wave_sum_d(double v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-  return v;
-}
-
 __device__ __forceinline__ float bf2f(bf16_t h) { return __uint_as_float(((uint32_t)h) << 16); }
 
 typedef float ew_f32x4 __attribute__((ext_vector_type(4)));
@@ -399,48 +393,13 @@ __global__ __launch_bounds__(K2T_THREADS) void scale_convert_tall_kernel(EwArgs 
   else scale_convert_tall_group<MALTER, false>(v, t, tsh, red);
 }
 
-// Fixed-order block reduction of count pairs (stride 2) into float64 sums.
-__device__ void block_sum_pairs(const float* __restrict__ p, int count, double out[2]) {
-  __shared__ double sh[2][4];
-  double s0 = 0.0, s1 = 0.0;
-  for (int k = threadIdx.x; k < count; k += NTHREADS) {
-    s0 += (double)p[2 * (size_t)k];
-    s1 += (double)p[2 * (size_t)k + 1];
-  }
-  s0 = wave_sum_d(s0);
-  s1 = wave_sum_d(s1);
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  if (lane == 0) {
-    sh[0][w] = s0;
-    sh[1][w] = s1;
-  }
-  __syncthreads();
-  out[0] = (sh[0][0] + sh[0][1]) + (sh[0][2] + sh[0][3]);
-  out[1] = (sh[1][0] + sh[1][1]) + (sh[1][2] + sh[1][3]);
-}
-
-// ||Mt||_F, sigma = 1/(s+ns_eps), nu_t and alpha_t (Alg. 2; displayed alpha_t).
 __global__ __launch_bounds__(NTHREADS) void norm_scalars_kernel(EwArgs a) {
+  __shared__ double sh[NTHREADS / 64][2];
   const MatDesc& d = a.desc[blockIdx.x];
   if (d.tiny) return;   // stepped whole by tiny_step_kernel
   double sums[2];
-  block_sum_pairs(d.k2part, d.k2_tiles, sums);
-  if (threadIdx.x != 0) return;
-  const double s = sqrt(sums[0]);
-  double* sc = d.scal;
-  sc[SC_S] = s;
-  sc[SC_SIGMA] = 1.0 / (s + a.ns_eps);
-  if (a.malter) {
-    const double nu = a.mu2 * (double)d.nu[0] + (1.0 - a.mu2) * sums[1];
-    d.nu[0] = (float)nu;
-    sc[SC_NU] = nu;
-    sc[SC_Q] = sums[1];
-    sc[SC_ALPHA] = a.bc * s / (sqrt(nu) + a.eps);
-  } else {
-    sc[SC_NU] = 0.0;
-    sc[SC_Q] = 0.0;
-    sc[SC_ALPHA] = 1.0;
-  }
+  block_sum_pairs<NTHREADS>(d.k2part, d.k2_tiles, sh, sums);
+  if (threadIdx.x == 0) norm_scalars(a, d, sums);
 }
 
 // Condition numbers of diag(l) and diag(r) (the quantity the paper's analysis
@@ -501,19 +460,13 @@ __global__ __launch_bounds__(NTHREADS) void precond_cond_kernel(const MatDesc* d
   }
 }
 
-// ||O||, ||D|| = ||L O R|| from the update-tile partials; graft and coefficient.
 __global__ __launch_bounds__(NTHREADS) void graft_scalars_kernel(EwArgs a) {
+  __shared__ double sh[NTHREADS / 64][2];
   const MatDesc& d = a.desc[blockIdx.x];
   if (d.tiny) return;
   double sums[2];
-  block_sum_pairs(d.gpart, d.upd_tiles, sums);
-  if (threadIdx.x != 0) return;
-  double* sc = d.scal;
-  const double g = sqrt(sums[0]) / (sqrt(sums[1]) + a.eps);
-  sc[SC_O2] = sums[0];
-  sc[SC_D2] = sums[1];
-  sc[SC_GRAFT] = g;
-  sc[SC_COEF] = a.lr * sc[SC_ALPHA] * g;
+  block_sum_pairs<NTHREADS>(d.gpart, d.upd_tiles, sh, sums);
+  if (threadIdx.x == 0) graft_scalars(a, gptr(d.scal), sums, true);
 }
 
 // ---------------------------------------------------------------------------
@@ -540,8 +493,12 @@ __device__ __forceinline__ int bm_word(int c, int w) {
 // momentum pass). Every global load is issued before the tall path's LDS
 // staging and its barrier, so W's loads are in flight while O's block makes
 // its round trip.
-template <bool TALL, bool INSIDE>
-__device__ __forceinline__ void backmap_tile(const EwArgs& a, const EwView& v, const Tile& t, uint32_t* osh) {
+// GRAFT: the graft scalars are formed here, from the update's partials, by every
+// workgroup for itself (the matrix's first tile stores them), which saves a
+// small set a launch.
+template <bool TALL, bool INSIDE, bool GRAFT>
+__device__ __forceinline__ void backmap_tile(const EwArgs& a, const EwView& v, const Tile& t, uint32_t* osh,
+                                             double (*sh)[2]) {
   constexpr int NW = EW_THREADS / 64, RPW = EW_TR / NW;   // 16 waves, 2 rows each
   static_assert(NW * RPW == EW_TR && EW_TC * EW_TR == EW_THREADS * 8, "tall fill: 8 bf16 per thread");
   static_assert(RPW == 2 && EW_TC == 256, "tall read: one word holds a wave's two rows; 64 lanes x 4 columns");
@@ -576,7 +533,15 @@ __device__ __forceinline__ void backmap_tile(const EwArgs& a, const EwView& v, c
   }
   float Rv[4];
   load4<false, INSIDE>(v.Rv, c, n, true, Rv);
-  const float coef = (float)v.scal[SC_COEF];
+  float coef;
+  if constexpr (GRAFT) {
+    const MatDesc& d = a.desc[t.mat];
+    double sums[2];
+    block_sum_pairs<EW_THREADS>(d.gpart, d.upd_tiles, sh, sums);
+    coef = (float)graft_scalars(a, v.scal, sums, t.ti == 0 && t.tj == 0 && threadIdx.x == 0);
+  } else {
+    coef = (float)v.scal[SC_COEF];
+  }
   const float decay = a.decay;
   float lv[RPW];   // all read before the first store, which the compiler cannot tell apart from Lv
 #pragma unroll
@@ -612,17 +577,19 @@ __device__ __forceinline__ void backmap_tile(const EwArgs& a, const EwView& v, c
   }
 }
 
+template <bool GRAFT>
 __global__ __launch_bounds__(EW_THREADS) void backmap_write_kernel(EwArgs a) {
   __shared__ uint32_t osh[EW_TR / 2 * EW_TC];   // tall: O^T block as words (see bm_word)
+  __shared__ double sh[GRAFT ? EW_THREADS / 64 : 1][2];
   const Tile t = a.tiles[xcd_remap(blockIdx.x, gridDim.x)];
   const EwView v = ew_view(a, t.mat);
   const bool inside = v.vec & ((t.ti + 1) * EW_TR <= v.m) & ((t.tj + 1) * EW_TC <= v.n);
   if (v.tall) {
-    if (inside) backmap_tile<true, true>(a, v, t, osh);
-    else backmap_tile<true, false>(a, v, t, osh);
+    if (inside) backmap_tile<true, true, GRAFT>(a, v, t, osh, sh);
+    else backmap_tile<true, false, GRAFT>(a, v, t, osh, sh);
   } else {
-    if (inside) backmap_tile<false, true>(a, v, t, osh);
-    else backmap_tile<false, false>(a, v, t, osh);
+    if (inside) backmap_tile<false, true, GRAFT>(a, v, t, osh, sh);
+    else backmap_tile<false, false, GRAFT>(a, v, t, osh, sh);
   }
 }
 
@@ -706,9 +673,10 @@ hipError_t launch_precond_cond(const MatDesc* desc, int32_t nmat, double* out, h
   hipLaunchKernelGGL(precond_cond_kernel, dim3(nmat), dim3(NTHREADS), 0, s, desc, out);
   return hipGetLastError();
 }
-hipError_t launch_backmap_write(const EwArgs& a, hipStream_t s) {
+hipError_t launch_backmap_write(const EwArgs& a, bool graft, hipStream_t s) {
   if (a.ntiles == 0) return hipSuccess;
-  hipLaunchKernelGGL(backmap_write_kernel, dim3(a.ntiles), dim3(EW_THREADS), 0, s, a);
+  if (graft) hipLaunchKernelGGL(backmap_write_kernel<true>, dim3(a.ntiles), dim3(EW_THREADS), 0, s, a);
+  else hipLaunchKernelGGL(backmap_write_kernel<false>, dim3(a.ntiles), dim3(EW_THREADS), 0, s, a);
   return hipGetLastError();
 }
 

@@ -78,6 +78,9 @@ struct Layout {
   int tile_g = NS_TILE, tile_gm = 0, tile_p = NS_TILE, tile_u = NS_TILE;
   size_t ws_t_gmid = 0, ws_t_gred = 0;
   int64_t n_gmid = 0, n_gred = 0;   // smaller-tile Gram list (dispatch order), reduction of the cut ones
+  // The scalar kernels' work done by the passes that use the scalars (see
+  // fuse_scalars).
+  bool fuse_norms = false, fuse_graft = false;
   int64_t n_smg = 0, n_smp = 0, n_smu = 0, n_tiny = 0;   // short sides
 };
 
@@ -457,6 +460,25 @@ void choose_tiles(Layout& L) {
   }
 }
 
+// Each scalar kernel is a launch of 4.7 us in a small step. There the passes that
+// use the scalars form them instead: the back-map from the update's partials,
+// the first Gram (on smaller tiles; the 256-tile kernel has no registers for
+// it) and the short sides' iteration from the convert pass's. Every workgroup
+// sums its matrix's partials again, about 1 us each, so this is for steps of
+// few workgroups (at most 2048 back-map tiles, eight a CU) and of few partials a
+// matrix. us per step: one GPT-2 Small block 315 -> 310, 256 x 512 83.0 -> 80.8,
+// a ragged set 246 -> 243.
+void fuse_scalars(Layout& L) {
+  constexpr int64_t kTiles = 2048, kPartials = 1024;
+  L.fuse_graft = L.n_ew <= kTiles;
+  L.fuse_norms = L.n_ew <= kTiles && L.tile_g != NS_TILE;
+  for (const MatPlan& q : L.mats) {
+    if (q.tiny) continue;
+    if (q.upd_tiles > kPartials) L.fuse_graft = false;
+    if (q.k2_tiles > kPartials) L.fuse_norms = false;
+  }
+}
+
 Layout make_layout(const malt_shape_t* shapes, int32_t n, malt_variant_t variant, Lists& T) {
   Layout L;
   L.mats.resize(n);
@@ -499,6 +521,7 @@ Layout make_layout(const malt_shape_t* shapes, int32_t n, malt_variant_t variant
     // Short sides: no matrix-core tiles; the product's partial slots are its
     // column chunks.
     p.upd_tiles = p.tiny ? 0 : p.small ? cdiv(p.nc, SM_CH_U) : (p.dm / L.tile_u) * (p.dn / L.tile_u);
+  fuse_scalars(L);
   size_t off = 0;
   auto take = [&](size_t bytes) { const size_t o = off; off = align256(off + bytes); return o; };
   L.ws_desc = take(sizeof(MatDesc) * n);
@@ -1322,6 +1345,7 @@ malt_status_t malt_step(malt_plan_t* p, float* const* params, const float* const
     SmallArgs sa;
     sa.a = hp->ns_a; sa.b = hp->ns_b; sa.c = hp->ns_c;
     sa.steps = hp->ns_steps;
+    sa.norms = 0;
     if (p->L.n_tiny > 0) {   // matrices whose step is one workgroup's
       sa.e = ea;
       sa.e.tiles = tiles_at(p->L.ws_t_tiny); sa.e.ntiles = int32_t(p->L.n_tiny);
@@ -1340,9 +1364,11 @@ malt_status_t malt_step(malt_plan_t* p, float* const* params, const float* const
         ea.tiles = tiles_at(p->L.ws_t_k2) + p->L.n_k2w; ea.ntiles = int32_t(p->L.n_k2 - p->L.n_k2w);
         MALT_LAUNCH(2, launch_scale_convert(ea, true, s));
       }
-      MALT_LAUNCH(3, launch_norm_scalars(ea, n, s));
+      if (!p->L.fuse_norms) MALT_LAUNCH(3, launch_norm_scalars(ea, n, s));
       NsArgs na;
       na.desc = ea.desc;
+      na.norms = sa.norms = p->L.fuse_norms;
+      na.ew = ea;
       na.a = float(hp->ns_a); na.b = float(hp->ns_b); na.c = float(hp->ns_c);
       for (int32_t it = 0; it < hp->ns_steps; ++it) {
         na.first = it == 0;
@@ -1373,9 +1399,9 @@ malt_status_t malt_step(malt_plan_t* p, float* const* params, const float* const
         MALT_LAUNCH(5, small(PH_POLY, p->L.ws_t_smp, p->L.n_smp));
         MALT_LAUNCH(6, small(PH_UPDATE, p->L.ws_t_smu, p->L.n_smu));
       }
-      MALT_LAUNCH(7, launch_graft_scalars(ea, n, s));
+      if (!p->L.fuse_graft) MALT_LAUNCH(7, launch_graft_scalars(ea, n, s));
       ea.tiles = tiles_at(p->L.ws_t_ew); ea.ntiles = int32_t(p->L.n_ew);
-      MALT_LAUNCH(8, launch_backmap_write(ea, s));
+      MALT_LAUNCH(8, launch_backmap_write(ea, p->L.fuse_graft, s));
     }
     if ((e = mark(-1)) != hipSuccess) goto hip_error;
   }

@@ -171,6 +171,7 @@ struct SmallArgs {
   EwArgs e;
   double a, b, c;
   int32_t steps;
+  int32_t norms;         // the iteration kernel also forms the norm scalars
 };
 
 struct NsArgs {
@@ -182,6 +183,8 @@ struct NsArgs {
   int32_t last;          // final iteration: write O and graft partials
   int32_t src;           // X[src] is the current iterate, X[src ^ 1] receives the next
   float a, b, c;
+  int32_t norms;         // the first Gram also forms the norm scalars (of ew)
+  EwArgs ew;
 };
 
 // Per-step pointer table written by a kernel whose arguments carry the
@@ -202,7 +205,7 @@ hipError_t launch_precond_finalize(const EwArgs& a, hipStream_t s);
 hipError_t launch_scale_convert(const EwArgs& a, bool tall, hipStream_t s);
 hipError_t launch_norm_scalars(const EwArgs& a, int32_t nmat, hipStream_t s);
 hipError_t launch_graft_scalars(const EwArgs& a, int32_t nmat, hipStream_t s);
-hipError_t launch_backmap_write(const EwArgs& a, hipStream_t s);
+hipError_t launch_backmap_write(const EwArgs& a, bool graft, hipStream_t s);   // graft: forms the graft scalars too
 hipError_t launch_precond_cond(const MatDesc* desc, int32_t nmat, double* out, hipStream_t s);
 hipError_t ns_gemm_setup();   // once per plan, on the plan's device
 hipError_t launch_ns_gemm(const NsArgs& a, hipStream_t s);
@@ -229,7 +232,7 @@ struct EwView {
   MALT_GLOBAL float* k2part;
   MALT_GLOBAL bf16_t* X0;
   const MALT_GLOBAL bf16_t* O;   // back-map: the buffer holding the final iterate
-  const MALT_GLOBAL double* scal;
+  MALT_GLOBAL double* scal;
 };
 
 __device__ __forceinline__ EwView ew_view(const EwArgs& a, int mat) {
@@ -253,6 +256,67 @@ __device__ __forceinline__ EwView ew_view(const EwArgs& a, int mat) {
   v.O = gptr(d.X[a.o_parity]);
   v.scal = gptr(d.scal);
   return v;
+}
+
+// Fixed-order sums in float64 of `count` float pairs (stride 2) over a
+// workgroup of THREADS, given to every thread; sh is free again at the next
+// barrier.  The two scalar kernels and the passes that take their place share
+// it; a thread adds every THREADS-th pair, so the result depends on THREADS.
+template <int THREADS>
+__device__ __forceinline__ void block_sum_pairs(const float* __restrict__ p, int count, double (*sh)[2], double out[2]) {
+  double s0 = 0.0, s1 = 0.0;
+  for (int k = threadIdx.x; k < count; k += THREADS) {
+    s0 += (double)gptr(p)[2 * (size_t)k];
+    s1 += (double)gptr(p)[2 * (size_t)k + 1];
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    s0 += __shfl_xor(s0, off, 64);
+    s1 += __shfl_xor(s1, off, 64);
+  }
+  if ((threadIdx.x & 63) == 0) {
+    sh[threadIdx.x >> 6][0] = s0;
+    sh[threadIdx.x >> 6][1] = s1;
+  }
+  __syncthreads();
+  out[0] = out[1] = 0.0;
+#pragma unroll
+  for (int w = 0; w < THREADS / 64; ++w) {
+    out[0] += sh[w][0];
+    out[1] += sh[w][1];
+  }
+}
+
+// ||Mt||_F, sigma = 1/(s+ns_eps), nu_t and alpha_t (Alg. 2; displayed alpha_t)
+// from the sums of (LMR)^2 and (LGR)^2; one thread writes them.
+__device__ __forceinline__ void norm_scalars(const EwArgs& a, const MatDesc& d, const double sums[2]) {
+  const double s = sqrt(sums[0]);
+  MALT_GLOBAL double* const sc = gptr(d.scal);
+  double nu = 0.0, alpha = 1.0;
+  if (a.malter) {
+    nu = a.mu2 * (double)gptr(d.nu)[0] + (1.0 - a.mu2) * sums[1];
+    gptr(d.nu)[0] = (float)nu;
+    alpha = a.bc * s / (sqrt(nu) + a.eps);
+  }
+  sc[SC_S] = s;
+  sc[SC_SIGMA] = 1.0 / (s + a.ns_eps);
+  sc[SC_NU] = nu;
+  sc[SC_Q] = a.malter ? sums[1] : 0.0;
+  sc[SC_ALPHA] = alpha;
+}
+
+// ||O||^2, ||D||^2, graft and step coefficient from the sums of O^2 and
+// (L O R)^2; returns the coefficient, `write` also stores them.
+__device__ __forceinline__ double graft_scalars(const EwArgs& a, MALT_GLOBAL double* sc, const double sums[2], bool write) {
+  const double g = sqrt(sums[0]) / (sqrt(sums[1]) + a.eps);
+  const double coef = a.lr * sc[SC_ALPHA] * g;
+  if (write) {
+    sc[SC_O2] = sums[0];
+    sc[SC_D2] = sums[1];
+    sc[SC_GRAFT] = g;
+    sc[SC_COEF] = coef;
+  }
+  return coef;
 }
 
 // XCDs of the chip; workgroups are dispatched to them round-robin.

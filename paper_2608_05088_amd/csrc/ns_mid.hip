@@ -54,7 +54,8 @@ void ns_mid_sym_kernel(NsArgs args) {
   bf16_t* const Bm = d->B;
   const bf16_t* P = PHASE == PH_GRAM ? d->X[args.src] : Am;
   float* const part = reinterpret_cast<float*>(d->X[args.src ^ 1]);
-  const float sig = (args.first && PHASE == PH_GRAM) ? (float)d->scal[SC_SIGMA] : 1.f;
+  const bool norms = PHASE == PH_GRAM && args.first && args.norms;
+  float sig = (args.first && PHASE == PH_GRAM && !norms) ? (float)d->scal[SC_SIGMA] : 1.f;
   const int ld = PHASE == PH_GRAM ? np : mp;
   const int row0 = t.ti * T, col0 = t.tj * T;
   const bool diag = t.ti == t.tj;
@@ -138,6 +139,17 @@ void ns_mid_sym_kernel(NsArgs args) {
   // ---------------------------------------------------------------- epilogue
   // acc[i][j][e] = C(r, c), r = rl0 + 16 i + e, c = cl0 + 16 j.
   const bool idle = diag && wr > wc;
+  if constexpr (PHASE == PH_GRAM) {
+    // The norm scalars, by every workgroup for itself; the first tile's stores
+    // them for the kernels after this one.
+    if (norms) {
+      double sums[2];
+      __syncthreads();   // every wave is done reading the operand ring
+      block_sum_pairs<G::NT>(d->k2part, d->k2_tiles, reinterpret_cast<double(*)[2]>(lds), sums);
+      sig = (float)(1.0 / (sqrt(sums[0]) + args.ew.ns_eps));
+      if (t.ti == 0 && t.tj == 0 && t.idx == 0 && tid == 0) norm_scalars(args.ew, *d, sums);
+    }
+  }
   if (PHASE == PH_GRAM && S > 1) {
     // Partial tile, stored transposed ([c][r]): four consecutive r per lane.
     if (idle) return;

@@ -687,7 +687,16 @@ __global__ __launch_bounds__(SM_PART) void sm_iterate_kernel(SmallArgs ns) {
   __shared__ SmCore s;
   const MatDesc& d = ns.e.desc[ns.e.tiles[blockIdx.x].mat];
   const int tid = threadIdx.x;
-  const double sg = gptr(d.scal)[SC_SIGMA];
+  double sg;
+  if (ns.norms) {   // the norm scalars are formed here
+    __shared__ double sh[SM_PART / 64][2];
+    double sums[2];
+    block_sum_pairs<SM_PART>(d.k2part, d.k2_tiles, sh, sums);
+    sg = 1.0 / (sqrt(sums[0]) + ns.e.ns_eps);
+    if (tid == 0) norm_scalars(ns.e, d, sums);
+  } else {
+    sg = gptr(d.scal)[SC_SIGMA];
+  }
   {
     const MALT_GLOBAL double* const Ap = gptr(d.Ap);
     double sum = 0.0;
