@@ -126,22 +126,21 @@ __global__ __launch_bounds__(EW_THREADS) void momentum_rowcol_kernel(EwArgs a) {
 // ---------------------------------------------------------------------------
 // Row / column EMAs and the diagonal preconditioners.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(NTHREADS) void precond_finalize_kernel(EwArgs a) {
-  // Tile (mat, 0 = rows | 1 = columns, chunk): FIN_W rows or columns, each
-  // summed by FIN_SPLIT threads (every FIN_SPLIT-th partial, in order), the
-  // thread sums combined in a fixed order.
-  constexpr int SPLIT = NTHREADS / FIN_W;
-  static_assert(SPLIT == 4, "pairwise combine of four sums");
-  __shared__ double part[SPLIT][FIN_W];
-  const Tile t = a.tiles[blockIdx.x];
+// Tile (mat, 0 = rows | 1 = columns, chunk, W): W rows or columns, each summed
+// by NTHREADS / W threads (every NTHREADS / W-th partial, in order), the thread
+// sums combined in a fixed order.  W is 64, or 8 where each has more than 512
+// partials: 768 columns of a 50257-row embedding have 1571 (34 -> 14 us); the
+// 5120-row matrices of GPT-2 Large, with 160, are faster at 64 (40 against 51).
+template <int W>
+__device__ __forceinline__ void finalize_chunk(const EwArgs& a, const Tile& t, double* part) {
+  constexpr int SPLIT = NTHREADS / W;
   const MatDesc& d = a.desc[t.mat];
   const bool rows = t.ti == 0;
   const int len = rows ? d.m : d.n, nparts = rows ? d.k1_ct : d.k1_rt;
   const MALT_GLOBAL float* const src = gptr(rows ? d.rowpart : d.colpart);
-  const int g = threadIdx.x / FIN_W, j = threadIdx.x % FIN_W;
-  const int i = t.tj * FIN_W + j;
-  // Eight partials in flight per thread, still added one by one in order
-  // (a column of a 5120-row matrix has 160 partials, 40 per thread).
+  const int g = threadIdx.x / W, j = threadIdx.x % W;
+  const int i = t.tj * W + j;
+  // Eight partials in flight per thread, still added one by one in order.
   double s = 0.0;
   if (i < len) {
     int c = g;
@@ -154,15 +153,25 @@ __global__ __launch_bounds__(NTHREADS) void precond_finalize_kernel(EwArgs a) {
     }
     for (; c < nparts; c += SPLIT) s += (double)src[(size_t)c * len + i];
   }
-  part[g][j] = s;
+  part[g * W + j] = s;
   __syncthreads();
   if (g != 0 || i >= len) return;
-  const double sum = (part[0][j] + part[1][j]) + (part[2][j] + part[3][j]);
+  double sum = 0.0;
+#pragma unroll
+  for (int k = 0; k < SPLIT; k += 4)
+    sum += (part[k * W + j] + part[(k + 1) * W + j]) + (part[(k + 2) * W + j] + part[(k + 3) * W + j]);
   float* const ema = rows ? d.l : d.r;
   float* const inv = rows ? d.Lv : d.Rv;
   const double v = a.mu2 * (double)gptr(ema)[i] + (1.0 - a.mu2) * sum;
   gptr(ema)[i] = (float)v;
   gptr(inv)[i] = a.identity ? 1.f : (float)pow(v + a.eps, -0.125);
+}
+
+__global__ __launch_bounds__(NTHREADS) void precond_finalize_kernel(EwArgs a) {
+  __shared__ double part[NTHREADS];
+  const Tile t = a.tiles[blockIdx.x];
+  if (t.idx == FIN_W) finalize_chunk<FIN_W>(a, t, part);
+  else finalize_chunk<FIN_W_LONG>(a, t, part);
 }
 
 // ---------------------------------------------------------------------------

@@ -172,6 +172,9 @@ std::vector<Tile> xcd_order(const std::vector<Tile>& list, const std::vector<dou
   return out;
 }
 
+// Rows or columns per finalise workgroup, by their partials.
+int32_t fin_width(int64_t parts) { return parts > FIN_LONG ? FIN_W_LONG : FIN_W; }
+
 // Every work list of a plan. The Newton-Schulz lists gram, gmid, poly and upd
 // are in dispatch order (padded with mat = -1).
 struct Lists {
@@ -199,8 +202,9 @@ void build_tiles(const Layout& L, Lists& O) {
     }
     for (int32_t ti = 0; ti < q.k1_rt; ++ti)
       for (int32_t tj = 0; tj < q.k1_ct; ++tj) O.ew.push_back({i, ti, tj, 0});
-    for (int32_t c = 0; c < cdiv(q.m, FIN_W); ++c) O.fin.push_back({i, 0, c, 0});
-    for (int32_t c = 0; c < cdiv(q.n, FIN_W); ++c) O.fin.push_back({i, 1, c, 0});
+    const int32_t wr = fin_width(q.k1_ct), wc = fin_width(q.k1_rt);
+    for (int32_t c = 0; c < cdiv(q.m, wr); ++c) O.fin.push_back({i, 0, c, wr});
+    for (int32_t c = 0; c < cdiv(q.n, wc); ++c) O.fin.push_back({i, 1, c, wc});
     if (q.small) {
       for (int32_t c = 0; c < q.sm_gchunks; ++c) O.smg.push_back({i, c, 0, 0});
       O.smp.push_back({i, 0, 0, 0});
@@ -299,7 +303,9 @@ double launch_time(const std::vector<TileSet>& sets, int T, int phase) {
     n += (q.off + q.diag) * q.parts;
   }
   if (n <= kCUs) return n ? alone : 0.0;
-  if (n <= slots) return std::max(sum / kCUs, alone + std::max(0.0, loaded - alone) * double(n - kCUs) / double(slots - kCUs));
+  // One round, some CUs shared: nothing overlaps the tiles' ends there.
+  if (n <= slots)
+    return std::max(sum / kCUs, alone + std::max(0.0, loaded + c.g - alone) * double(n - kCUs) / double(slots - kCUs));
   if (n > 2 * slots) return std::max(alone, sum / kCUs);
   // A few rounds of tiles, each to the slot free first: long contractions
   // first, as in the work lists (where a matrix's last tiles are full ones).
@@ -512,7 +518,7 @@ Layout make_layout(const malt_shape_t* shapes, int32_t n, malt_variant_t variant
     p.ns_flops_sym_per_iter = 3.0 * double(p.mc) * p.mc * p.nc + double(p.mc) * p.mc * p.mc;
     if (p.tiny) continue;
     L.n_ew += p.k1_rt * p.k1_ct;
-    L.n_fin += cdiv(p.m, FIN_W) + cdiv(p.n, FIN_W);
+    L.n_fin += cdiv(p.m, fin_width(p.k1_ct)) + cdiv(p.n, fin_width(p.k1_rt));
     L.n_k2 += p.k2_tiles;
     if (!p.tall) L.n_k2w += p.k2_tiles;
   }
@@ -983,12 +989,14 @@ malt_status_t check_bounds(const Layout& L, const Lists& W, int64_t shrink, int6
         return B.st;
     }
   }
-  // Preconditioner finalise: chunks of FIN_W rows or columns.
+  // Preconditioner finalise: chunks of rows or columns.
   for (const Tile& t : fin) {
     if (!B.mat_ok("precond_finalize", t)) return B.st;
     const MatPlan& q = L.mats[t.mat];
     const int64_t len = t.ti == 0 ? q.m : q.n;
-    if (!B.cond((t.ti == 0 || t.ti == 1) && t.tj >= 0 && int64_t(t.tj) * FIN_W < len, "precond_finalize", t,
+    if (!B.cond((t.ti == 0 || t.ti == 1) && (t.idx == FIN_W || t.idx == FIN_W_LONG) && t.tj >= 0 &&
+                    int64_t(t.tj) * t.idx < len,
+                "precond_finalize", t,
                 "chunk outside the rows / columns"))
       return B.st;
   }
