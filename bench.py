@@ -71,7 +71,7 @@ def recorded_traffic(workload: str):
 
 def small_case_latency(lm, wl, dev, reps: int = 50):
     """Latency of one step on the single 256 x 512 matrix workload (MALT),
-    which is bound by kernel latency (one or two workgroups per launch), not by
+    which is bound by kernel latency (a few workgroups per launch), not by
     bandwidth or matrix-core rate:
     median over `reps` individually timed steps."""
     import statistics
@@ -94,9 +94,12 @@ def small_case_latency(lm, wl, dev, reps: int = 50):
         e.record(stream)
         e.synchronize()
         times.append(s.elapsed_time(e))
+    plan.profile_enable(True)   # one more step, to count its launches
+    plan.step(Wd, Gd, hp, stream=stream)
+    launches = sum(v["launches"] for v in plan.profile_read().values())
     plan.close()
     return {"workload": w.name, "median_ms": round(statistics.median(times), 4), "reps": reps,
-            "launches_per_step": 4 + 3 * 5 + 2}
+            "launches_per_step": launches}
 
 
 def vendor_gemm_reference(w, dev):

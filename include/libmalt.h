@@ -22,8 +22,8 @@
  * coefficients): X = Mt/(||Mt||_F + ns_eps) on the orientation with
  * rows <= cols, then ns_steps times  A = X X^T,  B = ns_b A + ns_c A A,
  * X <- ns_a X + B X.  It runs in bf16 on the matrix cores with fp32
- * accumulation; matrices whose shorter side is at most 32 run it in fp32
- * instead (only the final O is rounded to bf16).  Everything else is fp32
+ * accumulation; matrices whose shorter side is at most 32 run it in fp64 on
+ * the Gram matrix instead (only the final O is rounded to bf16).  Everything else is fp32
  * with fp64 scalar combines.
  *
  * Conventions shared by every entry point
@@ -109,8 +109,8 @@ typedef struct malt_plan malt_plan_t;
  *    M_i row-major rows x cols; malt_state_layout() gives the offsets.
  *  workspace_bytes: scratch for the preconditioner vectors, reduction
  *    partials, the bf16 Newton-Schulz buffers (padded to multiples of 256),
- *    the fp32 Newton-Schulz buffers of matrices with a short side of at most
- *    32, and the per-matrix scalar table.  Must be 256-byte aligned. */
+ *    the Gram partials of matrices with a short side of at most 32, and the
+ *    per-matrix scalar table.  Must be 256-byte aligned. */
 malt_status_t malt_state_size(const malt_shape_t* shapes, int32_t n, malt_variant_t variant,
                               size_t* state_bytes, size_t* workspace_bytes);
 
@@ -185,7 +185,7 @@ malt_status_t malt_state_layout(const malt_plan_t* plan, int32_t i, malt_state_l
  *           + c A A (symmetric, m' x m' padded to AB_pitch = a multiple of 256
  *           rows and columns); B holds [B'_hi | B'_lo] with row pitch
  *           2 AB_pitch when B_split = 1. Unused (0) for matrices with a short
- *           side of at most 32, whose Newton-Schulz runs in fp32. */
+ *           side of at most 32. */
 typedef struct {
   int64_t Lv, Rv, O, X0, scalars;
   int64_t O_pitch;
@@ -239,7 +239,9 @@ int64_t malt_plan_step(const malt_plan_t* plan);
  * summed milliseconds and launch counts since the last reset.
  * Phases: 0 momentum+row/col sums, 1 preconditioner finalise,
  * 2 scale+convert, 3 norm scalars, 4 NS Gram, 5 NS polynomial, 6 NS update,
- * 7 graft scalars, 8 back-map+write. */
+ * 7 graft scalars, 8 back-map+write.  Small steps have no launches in phases 3
+ * and 7 (phases 4 and 8 form the scalars); matrices stepped whole in one launch
+ * count under phase 6. */
 #define MALT_NUM_PHASES 9
 typedef struct {
   double ms[MALT_NUM_PHASES];

@@ -263,20 +263,24 @@ void build_tiles(const Layout& L, Lists& O) {
 //     max(sum over tiles of (a * stages + f) / 256 CUs, longest tile b * stages + g)
 // in microseconds, stages of 64 k, with whole rounds of tiles where there are
 // few, and the plan takes the best edges per phase.  a, f: a CU's time per stage
-// and tile with the chip full; b, g: the time of a tile that has a CU to itself.  Measured on sets of 1 to 96 matrices of 256 to 4096 rows (a GPT-2
-// Small block, us per launch, 64 / 128 / 256 tiles: Gram 16 / 35 / 60,
-// polynomial 9 / 15 / 26, update 24 / 24 / 22; the 48 matrices of GPT-2 Small:
-// 119 / 91 / 78, 45 / 40 / 57, 260 / 180 / 130).
+// and tile with the chip full; b, g: the time of a tile that has a CU to itself;
+// h: added when one round of tiles fills the chip, in part before that.
+// Measured (us per launch, 64 / 128 / 256 tiles): a GPT-2 Small block, Gram 16 /
+// 35 / 60, polynomial 9 / 15 / 26, update 24 / 24 / 22; the 48 matrices of
+// GPT-2 Small, 119 / 91 / 78, 45 / 40 / 57, 260 / 180 / 130.  Over 22 sets from
+// one 576 x 1984 to 24 768-wide matrices the step with the chosen edges was 0.59
+// to 1.01 of the best of the three edges used throughout (one at 1.15), and
+// never behind 256.
 // ---------------------------------------------------------------------------
 struct TileCost {
-  double a, f, b, g;
+  double a, f, b, g, h;
 };
 
 TileCost tile_cost(int T, int phase) {
-  if (T == 64) return {0.20, 0.9, 0.22, 3.5};
-  if (T == 128) return {0.62, phase == PH_GRAM ? 1.6 : 2.5, 0.65, 5.0};
+  if (T == 64) return {0.20, 0.9, 0.22, 3.5, 2.0};
+  if (T == 128) return {phase == PH_UPDATE ? 0.65 : 0.62, phase == PH_UPDATE ? 0.9 : phase == PH_POLY ? 2.5 : 1.6, 0.65, 5.0, 10.0};
   const double f = phase == PH_POLY ? 10.5 : phase == PH_GRAM ? 7.0 : 6.0;
-  return {1.5, f, 1.3, f};
+  return {1.5, f, 1.3, f, 0.0};
 }
 
 constexpr int kCUs = 256;
@@ -293,19 +297,17 @@ double launch_time(const std::vector<TileSet>& sets, int T, int phase) {
   const TileCost c = tile_cost(T, phase);
   const int per_cu = T == 64 ? ns::MidGeom<64>::WPE : T == 128 ? ns::MidGeom<128>::WPE : 1;
   const int64_t slots = int64_t(kCUs) * per_cu;
-  double sum = 0.0, alone = 0.0, loaded = 0.0;   // all tiles; the longest by itself, beside per_cu - 1 others
+  double sum = 0.0, alone = 0.0;   // all tiles; the longest by itself
   int64_t n = 0;
   for (const TileSet& q : sets) {
-    const double work = c.a * q.stages + c.f * q.parts, st = q.stages / q.parts;
-    sum += (q.off + 0.75 * q.diag) * work;
-    alone = std::max(alone, c.b * st + c.g);
-    loaded = std::max(loaded, per_cu * (c.a * st + c.f));
+    sum += (q.off + 0.75 * q.diag) * (c.a * q.stages + c.f * q.parts);
+    alone = std::max(alone, c.b * q.stages / q.parts + c.g);
     n += (q.off + q.diag) * q.parts;
   }
   if (n <= kCUs) return n ? alone : 0.0;
-  // One round, some CUs shared: nothing overlaps the tiles' ends there.
-  if (n <= slots)
-    return std::max(sum / kCUs, alone + std::max(0.0, loaded + c.g - alone) * double(n - kCUs) / double(slots - kCUs));
+  // One round, some CUs shared: the tiles begin and end together, so nothing
+  // overlaps their prologues and epilogues.
+  if (n <= slots) return std::max(alone, sum / kCUs + c.h * double(n - kCUs) / double(slots - kCUs));
   if (n > 2 * slots) return std::max(alone, sum / kCUs);
   // A few rounds of tiles, each to the slot free first: long contractions
   // first, as in the work lists (where a matrix's last tiles are full ones).
@@ -369,7 +371,7 @@ double reduce_time(const std::vector<TileSet>& sets, int T) {
 // long contractions: the combination with the least estimated time, edges of
 // 256 unless the gain is over 5%.  The domain of every matrix is padded to the
 // largest edge in use, so the three largest edges are compared as wholes.
-void choose_tiles(Layout& L) {
+void choose_tiles(Layout& L, bool small_tiles) {
   std::vector<int32_t> mats;
   for (size_t i = 0; i < L.mats.size(); ++i) {
     MatPlan& q = L.mats[i];
@@ -379,7 +381,7 @@ void choose_tiles(Layout& L) {
     q.gmid = false;
     if (!q.small) mats.push_back(int32_t(i));
   }
-  if (mats.empty()) return;
+  if (mats.empty() || !small_tiles) return;
   struct Choice {
     int g = NS_TILE, gm = 128, p = NS_TILE, u = NS_TILE, edge = NS_TILE;
     std::vector<int32_t> parts;   // per entry of mats; 0: not on the smaller Gram tiles
@@ -485,7 +487,7 @@ void fuse_scalars(Layout& L) {
   }
 }
 
-Layout make_layout(const malt_shape_t* shapes, int32_t n, malt_variant_t variant, Lists& T) {
+Layout make_layout(const malt_shape_t* shapes, int32_t n, malt_variant_t variant, Lists& T, bool small_tiles = true) {
   Layout L;
   L.mats.resize(n);
   // State: [M... | l... | r... | nu...], float32, unpadded.
@@ -522,7 +524,7 @@ Layout make_layout(const malt_shape_t* shapes, int32_t n, malt_variant_t variant
     L.n_k2 += p.k2_tiles;
     if (!p.tall) L.n_k2w += p.k2_tiles;
   }
-  choose_tiles(L);
+  choose_tiles(L, small_tiles);
   for (MatPlan& p : L.mats)
     // Short sides: no matrix-core tiles; the product's partial slots are its
     // column chunks.
@@ -576,6 +578,17 @@ Layout make_layout(const malt_shape_t* shapes, int32_t n, malt_variant_t variant
     p.ws_Bs = take(chunked ? sizeof(double) * NS_SMALL_MAX * NS_SMALL_MAX : 0);
   }
   L.ws_bytes = off;
+  // Smaller tiles have longer lists and more partial slots (under 1% of a
+  // workspace).  A set that would fit the static scratch array without them
+  // does without them.
+  if (small_tiles && off > MALT_SCRATCH_BYTES && off < MALT_SCRATCH_BYTES + MALT_SCRATCH_BYTES / 16) {
+    Lists whole;
+    Layout W = make_layout(shapes, n, variant, whole, false);
+    if (W.ws_bytes <= MALT_SCRATCH_BYTES) {
+      T = std::move(whole);
+      return W;
+    }
+  }
   return L;
 }
 
@@ -761,8 +774,12 @@ malt_status_t init_plan(malt_plan* p, const malt_shape_t* shapes, int32_t n, mal
                      p->L.ws_bytes))
     return fail(MALT_ERR_ALIAS, "state and workspace buffers overlap");
   // Device work starts here, after every argument check.
-  hipError_t e = ns_gemm_setup();
-  if (e != hipSuccess) return hip_fail(e, "setting the Newton-Schulz kernels' LDS limit");
+  hipError_t e = hipSuccess;
+  if (p->L.n_gram > 0) e = ns_sym_setup(PH_GRAM);
+  if (e == hipSuccess && p->L.n_poly > 0 && p->L.tile_p == NS_TILE) e = ns_sym_setup(PH_POLY);
+  if (e == hipSuccess && p->L.n_updd > 0 && p->L.tile_u == NS_TILE) e = ns_update_setup();
+  if (e == hipSuccess && p->L.n_tiny > 0) e = tiny_step_setup(variant == MALT_VARIANT_MALTER);
+  if (e != hipSuccess) return hip_fail(e, "setting the kernels' LDS limit");
   p->variant = variant;
   p->n = n;
   p->shapes.assign(shapes, shapes + n);

@@ -210,12 +210,12 @@ hipError_t launch_norm_scalars(const EwArgs& a, int32_t nmat, hipStream_t s);
 hipError_t launch_graft_scalars(const EwArgs& a, int32_t nmat, hipStream_t s);
 hipError_t launch_backmap_write(const EwArgs& a, bool graft, hipStream_t s);   // graft: forms the graft scalars too
 hipError_t launch_precond_cond(const MatDesc* desc, int32_t nmat, double* out, hipStream_t s);
-hipError_t ns_gemm_setup();   // once per plan, on the plan's device
+hipError_t ns_sym_setup(int phase);      // LDS limits, once per plan that launches the kernel, on its device
 hipError_t launch_ns_gemm(const NsArgs& a, hipStream_t s);
-hipError_t ns_update_setup();   // the update kernel (ns_update.hip), called by ns_gemm_setup
+hipError_t ns_update_setup();
 hipError_t launch_ns_update(const NsArgs& a, hipStream_t s);
 hipError_t launch_ns_mid(const NsArgs& a, int tile, hipStream_t s);   // 64 or 128 tiles, all phases (ns_mid.hip)
-hipError_t small_ns_setup();   // the whole-step kernel (small_ns.hip), called by ns_gemm_setup
+hipError_t tiny_step_setup(bool malter);
 hipError_t launch_small_ns(const SmallArgs& a, int phase, hipStream_t s);
 hipError_t launch_tiny_step(const SmallArgs& a, hipStream_t s);
 

@@ -426,18 +426,14 @@ void ns_gemm_sym_kernel(NsArgs args) {
 }
 
 
-// The kernels use more dynamic LDS than the default limit; the attribute is
-// set for the current device (plan set-up calls ns_gemm_setup with the plan's
-// device current, so every device a plan runs on has it).
-hipError_t ns_gemm_setup() {
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&ns_gemm_sym_kernel<SymGeom, PH_GRAM>),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, SymLds<SymGeom>::BYTES);
-  if (e == hipSuccess)
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&ns_gemm_sym_kernel<PolyGeom, PH_POLY>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, SymLds<PolyGeom>::BYTES);
-  if (e == hipSuccess) e = ns_update_setup();
-  if (e == hipSuccess) e = small_ns_setup();
-  return e;
+// The kernel uses more dynamic LDS than the default limit; the attribute is set
+// for the current device by the set-up of each plan that launches it, with the
+// plan's device current, so every device a plan runs on has it.
+hipError_t ns_sym_setup(int phase) {
+  const void* f = phase == PH_GRAM ? reinterpret_cast<const void*>(&ns_gemm_sym_kernel<SymGeom, PH_GRAM>)
+                                   : reinterpret_cast<const void*>(&ns_gemm_sym_kernel<PolyGeom, PH_POLY>);
+  return hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize,
+                             phase == PH_GRAM ? SymLds<SymGeom>::BYTES : SymLds<PolyGeom>::BYTES);
 }
 
 hipError_t launch_ns_gemm(const NsArgs& a, hipStream_t s) {

@@ -261,8 +261,7 @@ void ns_update_kernel(NsArgs args) {
 }
 
 
-// The kernel uses more dynamic LDS than the default limit (set per device by
-// ns_gemm_setup at plan set-up).
+// The kernel uses more dynamic LDS than the default limit (see ns_sym_setup).
 hipError_t ns_update_setup() {
   return hipFuncSetAttribute(reinterpret_cast<const void*>(&ns_update_kernel),
                              hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES);

@@ -741,13 +741,12 @@ __global__ __launch_bounds__(NTHREADS) void sm_apply_kernel(SmallArgs ns) {
 
 }  // namespace
 
-hipError_t small_ns_setup() {
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&tiny_step_kernel<false>),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, sizeof(TinyLds));
-  if (e == hipSuccess)
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&tiny_step_kernel<true>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, sizeof(TinyLds));
-  return e;
+// The whole-step kernel uses more dynamic LDS than the default limit (see
+// ns_sym_setup).
+hipError_t tiny_step_setup(bool malter) {
+  return hipFuncSetAttribute(malter ? reinterpret_cast<const void*>(&tiny_step_kernel<true>)
+                                    : reinterpret_cast<const void*>(&tiny_step_kernel<false>),
+                             hipFuncAttributeMaxDynamicSharedMemorySize, sizeof(TinyLds));
 }
 
 hipError_t launch_tiny_step(const SmallArgs& a, hipStream_t s) {

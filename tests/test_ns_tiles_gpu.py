@@ -16,12 +16,16 @@ CASES = {
     # 64-tiles, Gram cut along k: contractions of 141 and 313 stages, one of them
     # of a hi/lo-split matrix, a tall one, and one whose parts are uneven
     "cut_64": [(64, 9001), (200, 20000), (15001, 70)],
-    # 128-tiles in the update, 64 elsewhere
-    "edges_128": [(512, 1536), (512, 512), (513, 2048), (2048, 511)] * 2,
+    # 128-tiles in Gram and polynomial, remainders of every kind
+    "edges_128": [(512, 1536), (512, 512), (513, 2048), (2048, 511)] * 4,
     # 128-tiles in the polynomial, 256 elsewhere
     "poly_128": [(768, 2304), (768, 768), (700, 3072), (3072, 768)] * 12,
-    # a long matrix beside a small model: its Gram cut on 128-tiles
+    # a long matrix beside a small model: its Gram cut on 64-tiles, 128 in the update
     "long_beside_model": [(20000, 348)] + [(348, 1044), (348, 348), (348, 1392), (1392, 348)] * 4,
+    # a longer one: cut on 128-tiles, every Gram on 128-tiles
+    "cut_128": [(20000, 700)] + [(768, 2304), (768, 768), (768, 3072), (3072, 768)] * 12,
+    # the others' Gram on 256-tiles, the long one's cut on 128-tiles beside them
+    "cut_beside_256": [(30000, 768)] + [(1280, 3840), (1280, 1280), (1280, 5120), (5120, 1280)] * 4,
 }
 
 
