@@ -23,7 +23,8 @@
  * rows <= cols, then ns_steps times  A = X X^T,  B = ns_b A + ns_c A A,
  * X <- ns_a X + B X.  It runs in bf16 on the matrix cores with fp32
  * accumulation; matrices whose shorter side is at most 32 run it in fp64 on
- * the Gram matrix instead (only the final O is rounded to bf16).  Everything else is fp32
+ * the Gram matrix instead, formed anew from an fp32 X after at most 8
+ * iterations (only the final O is rounded to bf16).  Everything else is fp32
  * with fp64 scalar combines.
  *
  * Conventions shared by every entry point

@@ -1166,6 +1166,8 @@ malt_status_t check_bounds(const Layout& L, const Lists& W, int64_t shrink, int6
                     t.idx < q.upd_tiles,
                 "sm_apply", t, "chunk or partial slot out of range"))
       return B.st;
+    if (!B.erange("sm_apply", "float32 iterate", t, 0, u4 * (uint64_t(q.mc - 1) * q.np + q.nc), u2 * q.mp * q.np))
+      return B.st;
   }
   for (const Tile& t : W.tiny) {
     if (!B.mat_ok("tiny_step", t)) return B.st;
@@ -1173,6 +1175,8 @@ malt_status_t check_bounds(const Layout& L, const Lists& W, int64_t shrink, int6
     if (!B.cond(q.tiny && (t.ti == 8 || t.ti == 16 || t.ti == 32) && q.mc <= t.ti && q.mc <= q.mp &&
                     q.nc <= q.np,
                 "tiny_step", t, "matrix does not fit a whole-step workgroup"))
+      return B.st;
+    if (!B.erange("tiny_step", "float32 iterate", t, 0, u4 * (uint64_t(q.mc - 1) * q.np + q.nc), u2 * q.mp * q.np))
       return B.st;
   }
   *checked = B.checked;
@@ -1370,7 +1374,9 @@ malt_status_t malt_step(malt_plan_t* p, float* const* params, const float* const
     SmallArgs sa;
     sa.a = hp->ns_a; sa.b = hp->ns_b; sa.c = hp->ns_c;
     sa.steps = hp->ns_steps;
+    sa.span = small_span(hp->ns_a);
     sa.norms = 0;
+    sa.first = sa.last = 1;
     if (p->L.n_tiny > 0) {   // matrices whose step is one workgroup's
       sa.e = ea;
       sa.e.tiles = tiles_at(p->L.ws_t_tiny); sa.e.ntiles = int32_t(p->L.n_tiny);
@@ -1413,16 +1419,21 @@ malt_status_t malt_step(malt_plan_t* p, float* const* params, const float* const
           MALT_LAUNCH(6, ns(PH_UPDATE, p->L.tile_u, p->L.ws_t_upd, p->L.n_updd));
         }
       }
-      if (p->L.n_smp > 0) {   // short sides: the whole iteration in three launches
+      if (p->L.n_smp > 0) {   // short sides: up to sa.span iterations in three launches
         sa.e = ea;
         auto small = [&](int phase, size_t off, int64_t count) {
           sa.e.tiles = tiles_at(off);
           sa.e.ntiles = int32_t(count);
           return launch_small_ns(sa, phase, s);
         };
-        MALT_LAUNCH(4, small(PH_GRAM, p->L.ws_t_smg, p->L.n_smg));
-        MALT_LAUNCH(5, small(PH_POLY, p->L.ws_t_smp, p->L.n_smp));
-        MALT_LAUNCH(6, small(PH_UPDATE, p->L.ws_t_smu, p->L.n_smu));
+        for (int32_t left = hp->ns_steps; left > 0; left -= sa.steps) {
+          sa.steps = std::min(left, sa.span);
+          sa.first = left == hp->ns_steps;
+          sa.last = left == sa.steps;
+          MALT_LAUNCH(4, small(PH_GRAM, p->L.ws_t_smg, p->L.n_smg));
+          MALT_LAUNCH(5, small(PH_POLY, p->L.ws_t_smp, p->L.n_smp));
+          MALT_LAUNCH(6, small(PH_UPDATE, p->L.ws_t_smu, p->L.n_smu));
+        }
       }
       if (!p->L.fuse_graft) MALT_LAUNCH(7, launch_graft_scalars(ea, n, s));
       ea.tiles = tiles_at(p->L.ws_t_ew); ea.ntiles = int32_t(p->L.n_ew);

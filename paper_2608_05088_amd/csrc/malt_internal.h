@@ -122,7 +122,7 @@ struct MatDesc {
   int32_t sm_gchunks;  // Gram partial count
   int32_t sm_chunk;    // columns per Gram partial
   double* Ap;          // [sm_gchunks][SM_PART] Gram partials
-  double* Bs;          // [32][32] sigma B_{s-1} ... B_0
+  double* Bs;          // [32][32] P = B_{s-1} ... B_0 (times sigma the first time)
   // Newton-Schulz domain: canonical dims rounded up to the plan's largest
   // Newton-Schulz tile (<= mp, np); no Newton-Schulz kernel works past it
   int32_t dm, dn;
@@ -173,8 +173,10 @@ struct EwArgs {
 struct SmallArgs {
   EwArgs e;
   double a, b, c;
-  int32_t steps;
-  int32_t norms;         // the iteration kernel also forms the norm scalars
+  int32_t steps;         // iterations: the step's, or those of these three launches
+  int32_t span;          // iterations before A is formed from X again (small_span)
+  int32_t norms;         // the first iteration kernel also forms the norm scalars
+  int32_t first, last;   // three launches: X is L M R; O follows
 };
 
 struct NsArgs {
@@ -215,6 +217,7 @@ hipError_t launch_ns_gemm(const NsArgs& a, hipStream_t s);
 hipError_t ns_update_setup();
 hipError_t launch_ns_update(const NsArgs& a, hipStream_t s);
 hipError_t launch_ns_mid(const NsArgs& a, int tile, hipStream_t s);   // 64 or 128 tiles, all phases (ns_mid.hip)
+int small_span(double a);
 hipError_t tiny_step_setup(bool malter);
 hipError_t launch_small_ns(const SmallArgs& a, int phase, hipStream_t s);
 hipError_t launch_tiny_step(const SmallArgs& a, hipStream_t s);

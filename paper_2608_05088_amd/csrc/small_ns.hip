@@ -7,9 +7,15 @@
 // Every B_k = a I + b A_k + c A_k^2 is a polynomial in A_0 = X_0 X_0^T, so
 //     A_{k+1} = B_k A_k B_k,   O = (B_{s-1} ... B_0) X_0,
 // and X is read twice, once for A_0 and once for the product with P = B_{s-1}
-// ... B_0, whatever the number of iterations.  In float64 the m' x m' matrices
-// lose nothing that matters: a relative error of 1e-16 of the largest entry of
-// A_0 grows by a^2 = 12 per iteration, as the small eigenvalues themselves do.
+// ... B_0.  That holds for a bounded number of iterations only: rounding moves
+// the eigenvalues of A_0 by about 1e-16 of the largest, either way, and the error
+// grows by a^2 = 12 per iteration.  Where X has a zero singular value (a gradient
+// of low rank) A's eigenvalue can come out negative, and then nothing bounds it:
+// a + b x + c x^2 grows with |x| (16 x 1024 of rank 1: NaN at 20 iterations).  So
+// after SmallArgs::span iterations (small_span: 8 with the default quintic, the
+// error then 4e-8 at most) X becomes P X, in float32, A is formed from it anew,
+// positive semidefinite by construction, and P starts over.  Up to span
+// iterations, X is read twice.
 // Products run on v_mfma_f64_16x16x4 (lane l holds A(l % 16, l / 16),
 // B(l / 16, l % 16); result register r holds C(l / 16 + 4 r, l % 16)); only the
 // final O is rounded to bf16.
@@ -100,13 +106,13 @@ __device__ __forceinline__ void sm_put(double* D, const f64x4& c, int bi, int bj
   for (int r = 0; r < 4; ++r) D[(16 * bi + (lane >> 4) + 4 * r) * SM_LD + 16 * bj + (lane & 15)] = c[r];
 }
 
-// The iteration on s.A = A_0 (16 NB rows and columns); returns P.  Every thread
+// `steps` iterations on s.A (16 NB rows and columns); returns P.  Every thread
 // of the workgroup of NWAVES waves calls it; it ends with a barrier.
 template <int NWAVES>
-__device__ __forceinline__ const double* sm_iterate(SmCore& s, int NB, const SmallArgs& ns) {
+__device__ __forceinline__ const double* sm_iterate(SmCore& s, int NB, const SmallArgs& ns, int steps) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nblk = NB * NB;
   int cur = 0;
-  for (int it = 0; it < ns.steps; ++it) {
+  for (int it = 0; it < steps; ++it) {
     for (int w = wave; w < nblk; w += NWAVES) {   // B = a I + b A + c A A
       const int bi = w / NB, bj = w % NB;
       f64x4 v = sm_mul(s.A, s.A, bi, bj, NB, lane);
@@ -124,7 +130,7 @@ __device__ __forceinline__ const double* sm_iterate(SmCore& s, int NB, const Sma
         sm_put(s.P[cur ^ 1], sm_mul(s.B, s.P[cur], w / NB, w % NB, NB, lane), w / NB, w % NB, lane);
       cur ^= 1;
     }
-    if (it + 1 < ns.steps) {   // A <- B A B, on the waves the product above left free first
+    if (it + 1 < steps) {   // A <- B A B, on the waves the product above left free first
       for (int w = (wave + NWAVES - (it > 0 ? nblk % NWAVES : 0)) % NWAVES; w < nblk; w += NWAVES)
         sm_put(s.T, sm_mul(s.B, s.A, w / NB, w % NB, NB, lane), w / NB, w % NB, lane);
       __syncthreads();
@@ -136,14 +142,10 @@ __device__ __forceinline__ const double* sm_iterate(SmCore& s, int NB, const Sma
   return s.P[cur];
 }
 
-// The product with P for a wave's 64 columns: x becomes O rounded to bf16 (0
-// past mc rows and past the matrix), (o2, d2) gain its sums of o^2 and (Lm o
-// Ln)^2.  rowf: canonical row factors (0 past mc); cf: this lane's column
-// factor; in: its column lies in the matrix.
+// The product with P for a wave's 64 columns: x becomes P x, staged in buf.
 template <int MC>
-__device__ __forceinline__ void sm_apply(float* buf, const double (&pa)[SmDim<MC>::NB][MC > 16 ? 8 : 4],
-                                         const float* rowf, float cf, bool in, int mc, int lane, float (&x)[MC],
-                                         double& o2, double& d2) {
+__device__ __forceinline__ void sm_product(float* buf, const double (&pa)[SmDim<MC>::NB][MC > 16 ? 8 : 4], int lane,
+                                           const float (&x)[MC]) {
   constexpr int NB = SmDim<MC>::NB, KS = MC > 16 ? 8 : 4;
   sm_stage<MC>(buf, x, lane);
 #pragma unroll
@@ -167,6 +169,26 @@ __device__ __forceinline__ void sm_apply(float* buf, const double (&pa)[SmDim<MC
         if (MC >= 16 || i < MC) buf[i * SM_PITCH + cl] = (float)y[b][r];
       }
   }
+}
+
+// x <- P x (0 past mc rows and past the matrix); in: this lane's column lies in
+// the matrix.
+template <int MC>
+__device__ __forceinline__ void sm_advance(float* buf, const double (&pa)[SmDim<MC>::NB][MC > 16 ? 8 : 4], bool in,
+                                           int mc, int lane, float (&x)[MC]) {
+  sm_product<MC>(buf, pa, lane, x);
+#pragma unroll
+  for (int i = 0; i < MC; ++i) x[i] = in && i < mc ? buf[i * SM_PITCH + lane] : 0.f;
+}
+
+// The last product: x becomes O = P x rounded to bf16 (0 past mc rows and past
+// the matrix), (o2, d2) gain its sums of o^2 and (Lm o Ln)^2.  rowf: canonical
+// row factors (0 past mc); cf: this lane's column factor.
+template <int MC>
+__device__ __forceinline__ void sm_apply(float* buf, const double (&pa)[SmDim<MC>::NB][MC > 16 ? 8 : 4],
+                                         const float* rowf, float cf, bool in, int mc, int lane, float (&x)[MC],
+                                         double& o2, double& d2) {
+  sm_product<MC>(buf, pa, lane, x);
   float so = 0.f, sd = 0.f;
 #pragma unroll
   for (int i = 0; i < MC; ++i) {
@@ -179,6 +201,14 @@ __device__ __forceinline__ void sm_apply(float* buf, const double (&pa)[SmDim<MC
   o2 += (double)so;
   d2 += (double)(cf * cf * sd);
 }
+
+// The iterate between two Grams: canonical float32 rows < mc of pitch np, in the
+// bf16 iterate buffer that the final O does not take (mc <= 32 rows of 4 bytes in
+// NS_TILE of 2).
+__device__ __forceinline__ MALT_GLOBAL float* sm_iterate_x(const MatDesc& d, int o_parity) {
+  return reinterpret_cast<MALT_GLOBAL float*>(gptr(d.X[o_parity ^ 1]));
+}
+static_assert(SM_M * sizeof(float) <= NS_TILE * sizeof(bf16_t), "the float32 iterate fits a bf16 iterate buffer");
 
 // Column c of the canonical O, already rounded (rows < mc).
 template <int MC>
@@ -354,6 +384,17 @@ __device__ __forceinline__ void tiny_put16(MALT_GLOBAL bf16_t* p, const TinyCols
   }
 }
 
+// This lane's column of the float32 iterate.
+template <int MC>
+__device__ __forceinline__ void tiny_load_x(const MALT_GLOBAL float* X, const TinyCols& t, int np, float (&x)[MC]) {
+  const int c = t.c0 + t.lane;
+#pragma unroll
+  for (int i = 0; i < MC; ++i) {
+    const float y = X[(size_t)min(i, t.mc - 1) * np + min(c, t.nc - 1)];
+    x[i] = i < t.mc && c < t.nc ? y : 0.f;
+  }
+}
+
 // Adds v over the wave's lanes; afterwards lane l holds the sum of entry
 // l >> (6 - log2 N) (halves exchanged: N - 1 shuffles, not 6 N).
 template <int N>
@@ -383,7 +424,8 @@ __device__ __forceinline__ float tiny_reduce(float (&v)[N], int lane) {
 // waiting for them does not wait for that round's stores.  us of a step: 16 x
 // 1024 27 (55 with a bounds branch per row, 39 with clamped positions only),
 // 3072 x 16 62, 32 x 1024 63, 8 x 4096 54.
-template <bool MALTER, int MC, bool FULL>
+// LONG: more than ns.span iterations (see the top of this file).
+template <bool MALTER, int MC, bool FULL, bool LONG>
 __device__ __forceinline__ void tiny_step(const SmallArgs& ns, int mat, TinyLds& S) {
   constexpr int NB = SmDim<MC>::NB;
   constexpr int LOG = MC == 32 ? 5 : MC == 16 ? 4 : 3;
@@ -531,41 +573,80 @@ __device__ __forceinline__ void tiny_step(const SmallArgs& ns, int mat, TinyLds&
     nu = a.mu2 * (double)nu_p[0] + (1.0 - a.mu2) * q2;
     alpha = a.bc * s / (sqrt(nu) + a.eps);
   }
-#pragma unroll
-  for (int b = 0; b < SmDim<MC>::NBLK; ++b)
-#pragma unroll
-    for (int e = 0; e < 4; ++e) S.red[wave][b][lane * 4 + e] = acc[b][e];
-  __syncthreads();
-  // A_0 = sigma^2 (L M R)(L M R)^T.
-  for (int q = tid; q < SmDim<MC>::NBLK * 256; q += TINY_THREADS) {
-    const int b = q >> 8, ln = (q & 255) >> 2, e = q & 3;
-    double sum = 0.0;
-#pragma unroll
-    for (int w = 0; w < TY_NW; ++w) sum += S.red[w][b][q & 255];
-    sum *= sigma * sigma;
-    const int i = (b == 2 ? 16 : 0) + (ln >> 4) + 4 * e, j = (b > 0 ? 16 : 0) + (ln & 15);
-    S.core.A[i * SM_LD + j] = sum;
-    if (b == 1) S.core.A[j * SM_LD + i] = sum;
-  }
-  __syncthreads();
+  // A = sg^2 times the Gram in acc, then `steps` iterations on it; pa = sg P.
   double pa[NB][MC > 16 ? 8 : 4];
-  sm_operand<MC>(sm_iterate<TY_NW>(S.core, NB, ns), sigma, pa, lane);
-  __syncthreads();   // P is in registers; the staging rows are free again
+  auto iterate = [&](double sg, int steps) {
+#pragma unroll
+    for (int b = 0; b < SmDim<MC>::NBLK; ++b)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) S.red[wave][b][lane * 4 + e] = acc[b][e];
+    __syncthreads();
+    for (int q = tid; q < SmDim<MC>::NBLK * 256; q += TINY_THREADS) {
+      const int b = q >> 8, ln = (q & 255) >> 2, e = q & 3;
+      double sum = 0.0;
+#pragma unroll
+      for (int w = 0; w < TY_NW; ++w) sum += S.red[w][b][q & 255];
+      sum *= sg * sg;
+      const int i = (b == 2 ? 16 : 0) + (ln >> 4) + 4 * e, j = (b > 0 ? 16 : 0) + (ln & 15);
+      S.core.A[i * SM_LD + j] = sum;
+      if (b == 1) S.core.A[j * SM_LD + i] = sum;
+    }
+    __syncthreads();
+    sm_operand<MC>(sm_iterate<TY_NW>(S.core, NB, ns, steps), sg, pa, lane);
+    __syncthreads();   // P is in registers; the staging rows are free again
+  };
+  iterate(sigma, LONG ? ns.span : ns.steps);
 
-  // O = sigma P (L M R), its norm and ||L O R||.
+  MALT_GLOBAL float* const X = sm_iterate_x(d, a.o_parity);
+  if constexpr (LONG) {
+    // X = P X (P L M R the first time, with sigma in P) and its Gram, until at
+    // most span iterations are left.
+    for (int left = ns.steps - ns.span; left > 0; left -= ns.span) {
+#pragma unroll
+      for (int b = 0; b < SmDim<MC>::NBLK; ++b) acc[b] = sm_zero();
+#pragma unroll 1
+      for (t.c0 = wave * 64; t.c0 < nc; t.c0 += TINY_THREADS) {
+        const int c = t.c0 + lane;
+        float x[MC];
+        if (left == ns.steps - ns.span) {
+          tiny_load<MC, FULL>(v.M, t, x);
+          tiny_mask<MC, FULL>(t, x);
+          tiny_own<MC, FULL>(buf, t, x);
+          scale(x, c < nc ? cinv[c] : 0.f);
+        } else {
+          tiny_load_x<MC>(X, t, np, x);
+        }
+        sm_advance<MC>(buf, pa, c < nc, mc, lane, x);
+#pragma unroll
+        for (int i = 0; i < MC; ++i)
+          if (i < mc && c < nc) X[(size_t)i * np + c] = x[i];
+        sm_stage<MC>(buf, x, lane);
+        sm_gram<MC>(buf, acc, lane);
+      }
+      __syncthreads();   // the staging rows are free for the blocks
+      iterate(1.0, min(left, ns.span));
+    }
+  }
+
+  // O = sigma P (L M R), or P X, its norm and ||L O R||.
   double o2 = 0.0, d2 = 0.0;
   t.c0 = wave * 64;
-  if (t.c0 < nc) fetch(v.M, t);
+  if (!LONG && t.c0 < nc) fetch(v.M, t);
 #pragma unroll 1
   for (; t.c0 < nc; t.c0 += TINY_THREADS) {
     const int c = t.c0 + lane;
-    float x[MC];
-    copy(x, xn);
-    const float cf = FULL || c < nc ? cn : 0.f;
-    if (const TinyCols nx = next(t); nx.c0 < nc) fetch(v.M, nx);
-    tiny_mask<MC, FULL>(t, x);
-    tiny_own<MC, FULL>(buf, t, x);
-    scale(x, cf);
+    float x[MC], cf;
+    if constexpr (LONG) {
+      cf = c < nc ? cinv[c] : 0.f;
+      tiny_load_x<MC>(X, t, np, x);
+    } else {
+      copy(x, xn);
+      cf = FULL || c < nc ? cn : 0.f;
+      if (const TinyCols nx = next(t); nx.c0 < nc) fetch(v.M, nx);
+      tiny_mask<MC, FULL>(t, x);
+      tiny_own<MC, FULL>(buf, t, x);
+      scale(x, cf);
+    }
     sm_apply<MC>(buf, pa, S.rowf, cf, FULL || c < nc, FULL ? MC : mc, lane, x, o2, d2);
     tiny_put16<MC, FULL>(O, t, np, x);
   }
@@ -627,25 +708,39 @@ __global__ __launch_bounds__(TINY_THREADS) void tiny_step_kernel(SmallArgs ns) {
   const MatDesc& d = ns.e.desc[t.mat];
   const bool full = d.mc == t.ti && d.nc % 64 == 0;
   if (t.ti == 8) {
-    if (full) tiny_step<MALTER, 8, true>(ns, t.mat, S);
-    else tiny_step<MALTER, 8, false>(ns, t.mat, S);
+    if (full) tiny_step<MALTER, 8, true, false>(ns, t.mat, S);
+    else tiny_step<MALTER, 8, false, false>(ns, t.mat, S);
   } else if (t.ti == 16) {
-    if (full) tiny_step<MALTER, 16, true>(ns, t.mat, S);
-    else tiny_step<MALTER, 16, false>(ns, t.mat, S);
+    if (full) tiny_step<MALTER, 16, true, false>(ns, t.mat, S);
+    else tiny_step<MALTER, 16, false, false>(ns, t.mat, S);
   } else {
-    if (full) tiny_step<MALTER, 32, true>(ns, t.mat, S);
-    else tiny_step<MALTER, 32, false>(ns, t.mat, S);
+    if (full) tiny_step<MALTER, 32, true, false>(ns, t.mat, S);
+    else tiny_step<MALTER, 32, false, false>(ns, t.mat, S);
   }
 }
 
+// The same for more than ns.span iterations; one instance for every m'.
+template <bool MALTER>
+__global__ __launch_bounds__(TINY_THREADS) void tiny_long_step_kernel(SmallArgs ns) {
+  extern __shared__ __attribute__((aligned(16))) char lds[];
+  tiny_step<MALTER, SM_M, false, true>(ns, ns.e.tiles[blockIdx.x].mat, *reinterpret_cast<TinyLds*>(lds));
+}
+
 // ---------------------------------------------------------------------------
-// The three launches of larger matrices.
+// The three launches of larger matrices, once per span iterations.
 // ---------------------------------------------------------------------------
 constexpr int SL_NW = NTHREADS / 64;
 static_assert(SM_CH_U == NTHREADS, "one column per thread in the product");
 
-// Column c of L M R in the canonical orientation (rows < SM_M).
-__device__ __forceinline__ void sm_column(const MatDesc& d, int c, float (&x)[SM_M]) {
+// Column c, in the canonical orientation (rows < SM_M), of L M R (first) or of
+// the float32 iterate.
+__device__ __forceinline__ void sm_column(const MatDesc& d, const SmallArgs& ns, int c, float (&x)[SM_M]) {
+  if (!ns.first) {
+    const MALT_GLOBAL float* const X = sm_iterate_x(d, ns.e.o_parity);
+#pragma unroll
+    for (int i = 0; i < SM_M; ++i) x[i] = i < d.mc && c < d.nc ? X[(size_t)i * d.np + c] : 0.f;
+    return;
+  }
   const float cf = c < d.nc ? gptr(d.tall ? d.Lv : d.Rv)[c] : 0.f;
   const MALT_GLOBAL float* const rf = gptr(d.tall ? d.Rv : d.Lv);
   const MALT_GLOBAL float* const M = gptr(d.M);
@@ -667,7 +762,7 @@ __global__ __launch_bounds__(NTHREADS) void sm_gram_kernel(SmallArgs ns) {
   const int c0 = t.ti * d.sm_chunk, c1 = min(c0 + d.sm_chunk, d.nc);
   for (int c = c0 + wave * 64; c < c1; c += NTHREADS) {
     float x[SM_M];
-    sm_column(d, c + lane < c1 ? c + lane : d.nc, x);
+    sm_column(d, ns, c + lane < c1 ? c + lane : d.nc, x);
     sm_stage<SM_M>(buf, x, lane);
     sm_gram<SM_M>(buf, acc, lane);
   }
@@ -687,14 +782,14 @@ __global__ __launch_bounds__(SM_PART) void sm_iterate_kernel(SmallArgs ns) {
   __shared__ SmCore s;
   const MatDesc& d = ns.e.desc[ns.e.tiles[blockIdx.x].mat];
   const int tid = threadIdx.x;
-  double sg;
-  if (ns.norms) {   // the norm scalars are formed here
+  double sg = 1.0;   // the iterate has been normalised
+  if (ns.first && ns.norms) {   // the norm scalars are formed here
     __shared__ double sh[SM_PART / 64][2];
     double sums[2];
     block_sum_pairs<SM_PART>(d.k2part, d.k2_tiles, sh, sums);
     sg = 1.0 / (sqrt(sums[0]) + ns.e.ns_eps);
     if (tid == 0) norm_scalars(ns.e, d, sums);
-  } else {
+  } else if (ns.first) {
     sg = gptr(d.scal)[SC_SIGMA];
   }
   {
@@ -709,7 +804,7 @@ __global__ __launch_bounds__(SM_PART) void sm_iterate_kernel(SmallArgs ns) {
     if (b == 1) s.A[j * SM_LD + i] = sum;
   }
   __syncthreads();
-  const double* const P = sm_iterate<SM_PART / 64>(s, 2, ns);
+  const double* const P = sm_iterate<SM_PART / 64>(s, 2, ns, ns.steps);
   for (int q = tid; q < SM_M * SM_M; q += SM_PART) gptr(d.Bs)[q] = sg * P[(q / SM_M) * SM_LD + q % SM_M];
 }
 
@@ -726,10 +821,18 @@ __global__ __launch_bounds__(NTHREADS) void sm_apply_kernel(SmallArgs ns) {
   if (tid < SM_M) rowf[tid] = tid < mc ? gptr(d.tall ? d.Rv : d.Lv)[tid] : 0.f;
   const float cf = c < nc ? gptr(d.tall ? d.Lv : d.Rv)[c] : 0.f;
   float x[SM_M];
-  sm_column(d, c, x);
+  sm_column(d, ns, c, x);
   __syncthreads();
   double pa[2][8], o2 = 0.0, d2 = 0.0;
   sm_operand<SM_M>(P, 1.0, pa, lane);
+  if (!ns.last) {   // X = P X, in place where it came from X
+    sm_advance<SM_M>(stage + wave * SM_WAVE, pa, c < nc, mc, lane, x);
+    MALT_GLOBAL float* const X = sm_iterate_x(d, ns.e.o_parity);
+#pragma unroll
+    for (int i = 0; i < SM_M; ++i)
+      if (i < mc && c < nc) X[(size_t)i * d.np + c] = x[i];
+    return;
+  }
   sm_apply<SM_M>(stage + wave * SM_WAVE, pa, rowf, cf, c < nc, mc, lane, x, o2, d2);
   sm_store_o<SM_M>(gptr(d.X[ns.e.o_parity]), d.np, mc, c, c < nc, x);
   sm_block_sum<SL_NW>(o2, d2, red);
@@ -741,20 +844,46 @@ __global__ __launch_bounds__(NTHREADS) void sm_apply_kernel(SmallArgs ns) {
 
 }  // namespace
 
-// The whole-step kernel uses more dynamic LDS than the default limit (see
+// Iterations in the Gram space before A is formed from X again: as many as keep
+// 1e-16 a^(2 k) below 1e-7, at most 8 (8 with the default quintic, whose a is
+// 3.4445).
+int small_span(double a) {
+  int k = 1;
+  for (double g = a * a * a * a; k < 8 && g <= 1e9; g *= a * a) ++k;
+  return k;
+}
+
+namespace {
+const void* tiny_kernel(bool malter, bool lng) {
+  if (lng)
+    return malter ? reinterpret_cast<const void*>(&tiny_long_step_kernel<true>)
+                  : reinterpret_cast<const void*>(&tiny_long_step_kernel<false>);
+  return malter ? reinterpret_cast<const void*>(&tiny_step_kernel<true>)
+                : reinterpret_cast<const void*>(&tiny_step_kernel<false>);
+}
+}  // namespace
+
+// The whole-step kernels use more dynamic LDS than the default limit (see
 // ns_sym_setup).
 hipError_t tiny_step_setup(bool malter) {
-  return hipFuncSetAttribute(malter ? reinterpret_cast<const void*>(&tiny_step_kernel<true>)
-                                    : reinterpret_cast<const void*>(&tiny_step_kernel<false>),
-                             hipFuncAttributeMaxDynamicSharedMemorySize, sizeof(TinyLds));
+  for (int lng = 0; lng < 2; ++lng) {
+    const hipError_t e =
+        hipFuncSetAttribute(tiny_kernel(malter, lng), hipFuncAttributeMaxDynamicSharedMemorySize, sizeof(TinyLds));
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 hipError_t launch_tiny_step(const SmallArgs& a, hipStream_t s) {
   if (a.e.ntiles == 0) return hipSuccess;
-  if (a.e.malter)
-    hipLaunchKernelGGL(tiny_step_kernel<true>, dim3(a.e.ntiles), dim3(TINY_THREADS), sizeof(TinyLds), s, a);
-  else
-    hipLaunchKernelGGL(tiny_step_kernel<false>, dim3(a.e.ntiles), dim3(TINY_THREADS), sizeof(TinyLds), s, a);
+  const dim3 grid(a.e.ntiles), block(TINY_THREADS);
+  if (a.steps > a.span) {
+    if (a.e.malter) hipLaunchKernelGGL(tiny_long_step_kernel<true>, grid, block, sizeof(TinyLds), s, a);
+    else hipLaunchKernelGGL(tiny_long_step_kernel<false>, grid, block, sizeof(TinyLds), s, a);
+  } else {
+    if (a.e.malter) hipLaunchKernelGGL(tiny_step_kernel<true>, grid, block, sizeof(TinyLds), s, a);
+    else hipLaunchKernelGGL(tiny_step_kernel<false>, grid, block, sizeof(TinyLds), s, a);
+  }
   return hipGetLastError();
 }
 

@@ -1,0 +1,76 @@
+"""Matrices with a short side of at most 32 (Newton-Schulz in the Gram space, in
+float64) where that form can go wrong: gradients of low rank over many
+iterations, on both routes (whole step in one workgroup, three launches)."""
+import numpy as np
+import pytest
+
+from gpu_harness import run_gpu, run_oracle, say
+from oracle import rel_fro
+from paper_2608_05088_amd import libmalt as lm
+from paper_2608_05088_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    lm.lib()
+
+
+# Whole step: wide, tall, full, square; three launches: one and several Gram chunks.
+RANK_SHAPES = [(16, 1024), (1024, 16), (32, 2048), (9, 9), (16, 4097), (40000, 20)]
+QUINTIC, CUBIC = (3.4445, -4.7750, 2.0315), (1.5, -0.5, 0.0)
+
+
+def _low_rank(kind, shape, seed):
+    """A gradient of known rank: (G, rank)."""
+    rng = np.random.default_rng(seed)
+    m, n = shape
+    if kind == "constant":
+        return np.full(shape, 1e-2, np.float32), 1
+    if kind == "repeated":   # rows (columns) in equal pairs and more
+        k = (min(shape) + 3) // 4
+        base = rng.standard_normal((k, max(shape))) * 1e-2
+        g = base[np.arange(min(shape)) % k]
+        return np.ascontiguousarray(g if m <= n else g.T).astype(np.float32), k
+    r = {"rank1": 1, "rank8": min(8, min(shape))}[kind]
+    return (rng.standard_normal((m, r)) @ rng.standard_normal((r, n)) * 1e-2).astype(np.float32), r
+
+
+@pytest.mark.parametrize("abc,sup", [(QUINTIC, 1.2024), (CUBIC, 1.0)])
+@pytest.mark.parametrize("ns_steps", [5, 8, 9, 12, 24, 64])
+def test_low_rank_short_sides_stay_bounded(ns_steps, abc, sup):
+    # Newton-Schulz maps every singular value of the normalised M~ into [0, sup]
+    # at any count (the largest value of the scalar iteration from [0, 1]), so
+    # the spectral norm of O exceeds sup by its final rounding only, at most 2^-9
+    # ||O||_F <= 2^-9 sup sqrt(32); float32 noise in the null space stays inside
+    # the same interval.  On the range of the gradient O is the oracle's up to
+    # that rounding (in emulation the iteration itself adds 7e-8).
+    kinds = ("constant", "repeated", "rank1", "rank8")
+    shapes = [s for s in RANK_SHAPES for _ in kinds]
+    say(f"[short] low-rank {kinds} x {RANK_SHAPES} ns_steps={ns_steps} abc={abc}")
+    made = [_low_rank(kinds[i % len(kinds)], s, 100 + i) for i, s in enumerate(shapes)]
+    W0 = [wl.weight(84, i, s) for i, s in enumerate(shapes)]
+    hp = dict(lr=1e-2, ns_steps=ns_steps, ns_a=abc[0], ns_b=abc[1], ns_c=abc[2])
+    grads = [[g for g, _ in made]]
+    st = run_gpu(shapes, "malter", W0, grads, hp)[0]
+    orc = run_oracle(shapes, "malter", W0, grads, hp)[0]["inter"]
+    worst = 0.0
+    for k, s in enumerate(shapes):
+        where = f"{kinds[k % len(kinds)]} {s}"
+        assert np.isfinite(st.W[k]).all() and np.isfinite(st.O[k]).all(), where
+        assert np.linalg.norm(st.O[k], 2) <= sup * (1 + 2.0 ** -9 * np.sqrt(32)) + 1e-6, where
+        Mt = orc[k].M_tilde
+        if s[0] > s[1]:
+            Mt = Mt.T
+        U = np.linalg.svd(Mt, full_matrices=False)[0][:, :made[k][1]]
+        part = lambda O: U.T @ (O.T if s[0] > s[1] else O)
+        # On the range alone: the rounding of the whole O, seen through U.
+        err = rel_fro(part(st.O[k]), part(orc[k].O))
+        lim = 4e-3 * max(1.0, np.linalg.norm(st.O[k]) / np.linalg.norm(part(orc[k].O)))
+        worst = max(worst, err / lim)
+        assert err <= lim, f"{where}: rank-{made[k][1]} part of O rel err {err:.3e} > {lim:.1e}"
+    say(f"[short] low-rank ns_steps={ns_steps} worst error / bound {worst:.3f}")
