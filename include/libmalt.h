@@ -215,6 +215,23 @@ malt_status_t malt_debug_layout(const malt_plan_t* plan, int32_t i, malt_debug_l
 malt_status_t malt_check_bounds(const malt_shape_t* shapes, int32_t n, malt_variant_t variant,
                                 int64_t shrink_bytes, int64_t* ranges_checked);
 
+/* The route that the step of each matrix takes in a plan over these shapes, for
+ * tests and for callers who tune a set.  Needs no plan and no device.
+ *  route: 0 matrix cores (bf16), 1 short side in three launches, 2 whole step in
+ *    one workgroup;
+ *  gram_tile, poly_tile, update_tile: tile edges (64, 128 or 256; 0 unless route
+ *    is 0); gram_parts: parts the Gram's contraction is cut into (1: not cut);
+ *  domain_rows, domain_cols: the canonical matrix (rows <= cols) padded to the
+ *    plan's largest tile (0 unless route is 0).
+ * out receives n entries.  Errors: as malt_state_size. */
+typedef struct {
+  int32_t route;
+  int32_t gram_tile, poly_tile, update_tile;
+  int32_t gram_parts;
+  int32_t domain_rows, domain_cols;
+} malt_route_t;
+malt_status_t malt_plan_routes(const malt_shape_t* shapes, int32_t n, malt_variant_t variant, malt_route_t* out);
+
 /* Condition numbers of diag(l_t) and diag(r_t) for every matrix of the plan:
  * the quantity the paper's analysis of the diagonal preconditioners (Sec. 5.4,
  * the figure of preconditioner condition numbers per layer) reports for the

@@ -487,6 +487,45 @@ void fuse_scalars(Layout& L) {
   }
 }
 
+// Which matrices with more than TINY_COLS columns take their whole step in one
+// workgroup.  That workgroup's time grows with its columns, however few matrices
+// there are; the three-launch route's with the columns of all, its passes
+// covering 256 padded rows.  Measured, us per step of one matrix, of 16 and of 64
+// (whole step | three launches): 1 x 65536 864 | 63, 3 x 8192 125 | 50, 125 | 70,
+// 129 | 165; 8000 x 7 141 | 93 (of 8), 147 | 362; 3 x 5000 83 | 58 (of 8), 86 |
+// 128.  The estimates below, in us, fit these within a tenth.  The matrices longer
+// than some length take three launches; the length is the one with the least sum.
+void choose_whole_steps(Layout& L) {
+  auto whole = [](const MatPlan& q) { return 15.0 + 13.3 * double(q.nc) / 1024; };
+  auto three = [](const MatPlan& q) { return (q.tall ? 0.55 : 0.23) * double(q.nc) / 1024; };
+  std::vector<int32_t> lng;
+  double rest = 0.0;   // the longest whole step of the others
+  for (size_t i = 0; i < L.mats.size(); ++i) {
+    const MatPlan& q = L.mats[i];
+    if (!q.tiny) continue;
+    if (q.nc > TINY_COLS) lng.push_back(int32_t(i));
+    else rest = std::max(rest, whole(q));
+  }
+  std::sort(lng.begin(), lng.end(), [&](int32_t a, int32_t b) {
+    return L.mats[a].nc != L.mats[b].nc ? L.mats[a].nc > L.mats[b].nc : a < b;
+  });
+  double cost = 45.0, best = lng.empty() ? 0.0 : whole(L.mats[lng[0]]);   // three launches; the least sum
+  int64_t cut = 0;   // columns from which on a matrix takes three launches; 0: none
+  for (size_t k = 0; k < lng.size(); ++k) {
+    const MatPlan& q = L.mats[lng[k]];
+    cost += three(q);
+    if (k + 1 < lng.size() && L.mats[lng[k + 1]].nc == q.nc) continue;
+    const double sum = cost + (k + 1 < lng.size() ? whole(L.mats[lng[k + 1]]) : rest);
+    if (sum < best) {
+      best = sum;
+      cut = q.nc;
+    }
+  }
+  if (cut > 0)
+    for (int32_t i : lng)
+      if (L.mats[i].nc >= cut) L.mats[i].tiny = false;
+}
+
 Layout make_layout(const malt_shape_t* shapes, int32_t n, malt_variant_t variant, Lists& T, bool small_tiles = true) {
   Layout L;
   L.mats.resize(n);
@@ -510,6 +549,11 @@ Layout make_layout(const malt_shape_t* shapes, int32_t n, malt_variant_t variant
     p.split = !p.small && p.mc <= NS_SPLIT_MAX;
     p.tiny_rows = p.mc <= 8 ? 8 : p.mc <= 16 ? 16 : 32;
     p.tiny = p.small && p.m * p.n <= TINY_ELEMS;
+    p.ns_flops_sym_per_iter = 3.0 * double(p.mc) * p.mc * p.nc + double(p.mc) * p.mc * p.mc;
+  }
+  if (small_tiles) choose_whole_steps(L);
+  for (int32_t i = 0; i < n; ++i) {
+    MatPlan& p = L.mats[i];
     p.sm_chunk = std::max<int64_t>(SM_CH_G, pad_to(cdiv(p.nc, SM_CHUNKS), NTHREADS));
     p.sm_gchunks = p.small && !p.tiny ? cdiv(p.nc, p.sm_chunk) : 0;
     p.k1_ct = cdiv(p.n, EW_TC); p.k1_rt = cdiv(p.m, EW_TR);
@@ -517,7 +561,6 @@ Layout make_layout(const malt_shape_t* shapes, int32_t n, malt_variant_t variant
     if (p.tall) { p.k2_tr = p.np / K2_T; p.k2_tc = p.mp / K2_T; }
     else { p.k2_tr = p.mp / K2W_R; p.k2_tc = p.np / EW_TC; }
     p.k2_tiles = p.k2_tr * p.k2_tc;
-    p.ns_flops_sym_per_iter = 3.0 * double(p.mc) * p.mc * p.nc + double(p.mc) * p.mc * p.mc;
     if (p.tiny) continue;
     L.n_ew += p.k1_rt * p.k1_ct;
     L.n_fin += cdiv(p.m, fin_width(p.k1_ct)) + cdiv(p.n, fin_width(p.k1_rt));
@@ -578,9 +621,9 @@ Layout make_layout(const malt_shape_t* shapes, int32_t n, malt_variant_t variant
     p.ws_Bs = take(chunked ? sizeof(double) * NS_SMALL_MAX * NS_SMALL_MAX : 0);
   }
   L.ws_bytes = off;
-  // Smaller tiles have longer lists and more partial slots (under 1% of a
-  // workspace).  A set that would fit the static scratch array without them
-  // does without them.
+  // Smaller tiles have longer lists and more partial slots, and three launches
+  // have partials that whole steps have not (under 1% of a workspace).  A set that
+  // would fit the static scratch array without them does without them.
   if (small_tiles && off > MALT_SCRATCH_BYTES && off < MALT_SCRATCH_BYTES + MALT_SCRATCH_BYTES / 16) {
     Lists whole;
     Layout W = make_layout(shapes, n, variant, whole, false);
@@ -1469,6 +1512,22 @@ malt_status_t malt_check_bounds(const malt_shape_t* shapes, int32_t n, malt_vari
   Lists T;
   const Layout L = make_layout(shapes, n, variant, T);
   return check_bounds(L, T, shrink_bytes, ranges_checked);
+}
+
+malt_status_t malt_plan_routes(const malt_shape_t* shapes, int32_t n, malt_variant_t variant, malt_route_t* out) {
+  if (variant != MALT_VARIANT_MALT && variant != MALT_VARIANT_MALTER)
+    return fail(MALT_ERR_INVALID_ARG, "unknown variant %d", int(variant));
+  if (!out) return fail(MALT_ERR_INVALID_ARG, "output pointer is NULL");
+  malt_status_t st = check_shapes(shapes, n);
+  if (st != MALT_OK) return st;
+  Lists T;
+  const Layout L = make_layout(shapes, n, variant, T);
+  for (int32_t i = 0; i < n; ++i) {
+    const MatPlan& q = L.mats[i];
+    if (q.small) out[i] = {q.tiny ? 2 : 1, 0, 0, 0, 1, 0, 0};
+    else out[i] = {0, q.gmid ? L.tile_gm : L.tile_g, L.tile_p, L.tile_u, q.gsplit, int32_t(q.dm), int32_t(q.dn)};
+  }
+  return MALT_OK;
 }
 
 malt_status_t malt_state_layout(const malt_plan_t* p, int32_t i, malt_state_layout_t* out) {

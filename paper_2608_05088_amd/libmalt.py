@@ -60,6 +60,11 @@ class malt_debug_layout_t(ctypes.Structure):
                 ("A", c_int64), ("B", c_int64), ("AB_pitch", c_int64), ("B_split", c_int64)]
 
 
+class malt_route_t(ctypes.Structure):
+    _fields_ = [(k, c_int32) for k in ("route", "gram_tile", "poly_tile", "update_tile", "gram_parts",
+                                       "domain_rows", "domain_cols")]
+
+
 class malt_profile_t(ctypes.Structure):
     _fields_ = [("ms", c_double * NUM_PHASES), ("launches", c_int64 * NUM_PHASES),
                 ("bytes", c_double * NUM_PHASES), ("flops", c_double * NUM_PHASES)]
@@ -91,6 +96,7 @@ _SIGNATURES = [
     ("malt_plan_step", c_int64, [c_void_p]),
     ("malt_precond_condition", c_int32, [c_void_p, c_void_p, c_void_p]),
     ("malt_check_bounds", c_int32, [POINTER(malt_shape_t), c_int32, c_int32, c_int64, POINTER(c_int64)]),
+    ("malt_plan_routes", c_int32, [POINTER(malt_shape_t), c_int32, c_int32, POINTER(malt_route_t)]),
     ("malt_profile_enable", c_int32, [c_void_p, c_int32]),
     ("malt_profile_read", c_int32, [c_void_p, POINTER(malt_profile_t), c_int32]),
     ("malt_destroy_state", None, [c_void_p]),
@@ -168,6 +174,14 @@ def check_bounds(shapes: Sequence[Tuple[int, int]], variant: str = "malt", shrin
     _check(lib().malt_check_bounds(_shapes(shapes), len(shapes), VARIANTS[variant], int(shrink_bytes),
                                    ctypes.byref(checked)))
     return checked.value
+
+
+def plan_routes(shapes: Sequence[Tuple[int, int]], variant: str = "malt") -> List[dict]:
+    """malt_plan_routes: per matrix, the route and the tile edges its step would
+    take in a plan over `shapes`.  Host only."""
+    out = (malt_route_t * max(1, len(shapes)))()
+    _check(lib().malt_plan_routes(_shapes(shapes), len(shapes), VARIANTS[variant], out))
+    return [{k: getattr(out[i], k) for k, _ in malt_route_t._fields_} for i in range(len(shapes))]
 
 
 def _stream_handle(stream) -> Optional[int]:

@@ -83,3 +83,18 @@ def test_short_side_edges(variant, ns_steps):
     # 4e-3 covers it in norm, in O and in the update.
     worst = compare(g, o, variant, tol_ns=4e-3, label="short")
     say(f"[tiles] short worst {worst}")
+
+
+def test_short_side_sets_of_long_matrices():
+    # Past 4096 columns a matrix takes its whole step in one workgroup only beside
+    # many others: wide, tall and ragged ones, with one that leaves for three
+    # launches.
+    shapes = [(3, 4500), (5000, 2), (13, 4999)] * 20 + [(1, 65536), (16, 1024)]
+    assert [r["route"] for r in lm.plan_routes(shapes)] == [2] * 60 + [1, 2]
+    keep = [0, 1, 2, 59, 60, 61]
+    say(f"[tiles] long short sides {len(shapes)} matrices malter x2")
+    W0 = [wl.weight(82, i, s) for i, s in enumerate(shapes)]
+    grads = [[wl.grad(82, t, i, s, "row_loguniform") for i, s in enumerate(shapes)] for t in (1, 2)]
+    g = run_gpu(shapes, "malter", W0, grads, dict(lr=1e-2), collect=keep)
+    o = run_oracle(shapes, "malter", W0, grads, dict(lr=1e-2), collect=keep)
+    say(f"[tiles] long short sides worst {compare(g, o, 'malter', tol_ns=4e-3, label='long short')}")

@@ -1,0 +1,48 @@
+"""The routes a plan chooses for its matrices (host code, no GPU): which short
+sides take their whole step in one workgroup."""
+import os
+
+import pytest
+
+from paper_2608_05088_amd import libmalt as lm
+
+MATRIX_CORES, THREE_LAUNCHES, WHOLE_STEP = 0, 1, 2
+
+
+@pytest.fixture(scope="module", autouse=True)
+def L():
+    if not os.path.exists(lm.LIB_PATH):
+        from paper_2608_05088_amd import build
+        build.build()
+    return lm.lib()
+
+
+def _routes(shapes, variant="malt"):
+    return [r["route"] for r in lm.plan_routes(shapes, variant)]
+
+
+@pytest.mark.parametrize("shapes,want", [
+    # the largest whole step by columns and by elements, and one past each
+    ([(1, 4096)], [WHOLE_STEP]), ([(4096, 1)], [WHOLE_STEP]), ([(16, 4096)], [WHOLE_STEP]),
+    ([(32, 2048)], [WHOLE_STEP]), ([(32, 2049)], [THREE_LAUNCHES]), ([(16, 4097)], [THREE_LAUNCHES]),
+    ([(1, 4097)], [THREE_LAUNCHES]), ([(4097, 1)], [THREE_LAUNCHES]), ([(33, 64)], [MATRIX_CORES]),
+    # one or a few long thin matrices would keep one workgroup busy for 100 to
+    # 900 us (1 x 65536: 864 against 63 in three launches)
+    ([(1, 65536)], [THREE_LAUNCHES]), ([(65536, 1)] * 8, [THREE_LAUNCHES] * 8),
+    ([(2, 32768), (8192, 3)], [THREE_LAUNCHES] * 2), ([(3, 8192)] * 16, [THREE_LAUNCHES] * 16),
+    # many of them fill the chip: whole steps
+    ([(3, 8192)] * 64, [WHOLE_STEP] * 64), ([(1, 65536)] * 64, [WHOLE_STEP] * 64), ([(8000, 7)] * 40, [WHOLE_STEP] * 40),
+    # of a mixed set only the longest leave
+    ([(1, 65536)] + [(3, 5000)] * 60 + [(16, 1024)], [THREE_LAUNCHES] + [WHOLE_STEP] * 61),
+])
+def test_whole_step_only_where_it_is_the_shorter(shapes, want):
+    for variant in ("malt", "malter"):
+        assert _routes(shapes, variant) == want
+        assert lm.check_bounds(shapes, variant) > 0
+
+
+def test_routes_reject_bad_arguments(L):
+    out = (lm.malt_route_t * 1)()
+    assert L.malt_plan_routes(lm._shapes([(8, 8)]), 1, 5, out) == lm.MALT_ERR_INVALID_ARG
+    assert L.malt_plan_routes(lm._shapes([(8, 8)]), 1, 0, None) == lm.MALT_ERR_INVALID_ARG
+    assert L.malt_plan_routes(lm._shapes([(0, 8)]), 1, 0, out) == lm.MALT_ERR_SHAPE
