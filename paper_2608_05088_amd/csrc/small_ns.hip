@@ -32,6 +32,8 @@
 //                iteration, and the product with P over column chunks.
 // Measured (us per step): one 5 x 5 matrix 108 -> 16; 96 matrices of rank 16
 // (16 x 1024, 1024 x 16, 3072 x 16) 580 -> 107, of which the GPU 65.
+#include <type_traits>
+
 #include "malt_internal.h"
 
 namespace malt {
@@ -273,7 +275,7 @@ struct TinyLds {
     };
   };
   float rowf[SM_M];
-  float rows[TY_NW][SM_M];
+  double rows[TY_NW][SM_M];
   double red2[TY_NW][2];
 };
 static_assert(sizeof(TinyLds) <= 160 * 1024, "LDS of a whole-step workgroup");
@@ -396,22 +398,33 @@ __device__ __forceinline__ void tiny_load_x(const MALT_GLOBAL float* X, const Ti
   }
 }
 
-// Adds v over the wave's lanes; afterwards lane l holds the sum of entry
-// l >> (6 - log2 N) (halves exchanged: N - 1 shuffles, not 6 N).
-template <int N>
-__device__ __forceinline__ float tiny_reduce(float (&v)[N], int lane) {
-  int off = 32;
+// One exchange of halves: 2 N entries per lane in, the sums of N of them with the
+// lane `off` away out (the upper half where lane & off).
+template <int N, class F>
+__device__ __forceinline__ void tiny_halve(F* v, int lane, int off) {
+  const bool up = lane & off;
 #pragma unroll
-  for (int n = N / 2; n >= 1; n /= 2) {
-    const bool up = lane & off;
-#pragma unroll
-    for (int k = 0; k < n; ++k) {
-      const float send = up ? v[k] : v[k + n], keep = up ? v[k + n] : v[k];
-      v[k] = keep + __shfl_xor(send, off, 64);
-    }
-    off >>= 1;
+  for (int k = 0; k < N; ++k) {
+    const F send = up ? v[k] : v[k + N], keep = up ? v[k + N] : v[k];
+    v[k] = keep + __shfl_xor(send, off, 64);
   }
-  float s = v[0];
+}
+
+// Adds x over the wave's lanes; afterwards lane l holds the sum of entry
+// l >> (6 - log2 N) (halves exchanged: N - 1 shuffles, not 6 N).  The first two
+// exchanges in F, the others in float64.
+template <int N, class F>
+__device__ __forceinline__ double tiny_reduce(F (&x)[N], int lane) {
+  tiny_halve<N / 2>(x, lane, 32);
+  tiny_halve<N / 4>(x, lane, 16);
+  double v[N / 4];
+#pragma unroll
+  for (int k = 0; k < N / 4; ++k) v[k] = (double)x[k];
+  int off = 8;
+  if constexpr (N >= 8) { tiny_halve<N / 8>(v, lane, off); off >>= 1; }
+  if constexpr (N >= 16) { tiny_halve<N / 16>(v, lane, off); off >>= 1; }
+  if constexpr (N >= 32) { tiny_halve<N / 32>(v, lane, off); off >>= 1; }
+  double s = v[0];
   for (; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
   return s;
 }
@@ -456,11 +469,17 @@ __device__ __forceinline__ void tiny_step(const SmallArgs& ns, int mat, TinyLds&
     for (int i = 0; i < MC; ++i) to[i] = from[i];
   };
 
-  // Momentum, and the row and column sums of G^2.
+  // Momentum, and the row and column sums of G^2.  Those along the long side (up
+  // to 65536 terms) are float64; past 16 rows, whose at most 3855 columns are
+  // eight terms a lane, from float32 sums of four lanes (in float64 throughout the
+  // 64 registers more cost 32 x 2048 100 -> 118 us).  Those over a column's rows
+  // are float32.
   {
-    float rs[MC];
+    typedef typename std::conditional<(MC > 16), float, double>::type sum_t;
+    static_assert(TINY_ELEMS / 17 <= 8 * TINY_THREADS, "few float32 terms a lane");
+    sum_t rs[MC];
 #pragma unroll
-    for (int i = 0; i < MC; ++i) rs[i] = 0.f;
+    for (int i = 0; i < MC; ++i) rs[i] = 0;
     float gn[MC], mn[MC], en;
     auto fetch = [&](const TinyCols& t) {
       tiny_load<MC, FULL>(v.G, t, gn);
@@ -489,7 +508,7 @@ __device__ __forceinline__ void tiny_step(const SmallArgs& ns, int mat, TinyLds&
 #pragma unroll
       for (int i = 0; i < MC; ++i) {
         cs += g[i];
-        rs[i] += g[i];
+        rs[i] += (sum_t)g[i];
       }
       if (FULL || c < nc) {
         const double e = a.mu2 * old + (1.0 - a.mu2) * (double)cs;
@@ -497,7 +516,7 @@ __device__ __forceinline__ void tiny_step(const SmallArgs& ns, int mat, TinyLds&
         cinv[c] = a.identity ? 1.f : sm_inv_eighth(e + a.eps);
       }
     }
-    const float s = tiny_reduce<MC>(rs, lane);
+    const double s = tiny_reduce<MC>(rs, lane);
     if ((lane & ((64 >> LOG) - 1)) == 0) S.rows[wave][lane >> (6 - LOG)] = s;
   }
   __syncthreads();
@@ -506,7 +525,7 @@ __device__ __forceinline__ void tiny_step(const SmallArgs& ns, int mat, TinyLds&
     if (tid < mc) {
       double s = 0.0;
 #pragma unroll
-      for (int w = 0; w < TY_NW; ++w) s += (double)S.rows[w][tid];
+      for (int w = 0; w < TY_NW; ++w) s += S.rows[w][tid];
       const double e = a.mu2 * (double)rema[tid] + (1.0 - a.mu2) * s;
       rema[tid] = (float)e;
       f = a.identity ? 1.f : sm_inv_eighth(e + a.eps);

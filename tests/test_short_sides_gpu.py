@@ -1,6 +1,7 @@
 """Matrices with a short side of at most 32 (Newton-Schulz in the Gram space, in
 float64) where that form can go wrong: gradients of low rank over many
-iterations, on both routes (whole step in one workgroup, three launches)."""
+iterations, and sums over a long side, on both routes (whole step in one
+workgroup, three launches)."""
 import numpy as np
 import pytest
 
@@ -74,3 +75,33 @@ def test_low_rank_short_sides_stay_bounded(ns_steps, abc, sup):
         worst = max(worst, err / lim)
         assert err <= lim, f"{where}: rank-{made[k][1]} part of O rel err {err:.3e} > {lim:.1e}"
     say(f"[short] low-rank ns_steps={ns_steps} worst error / bound {worst:.3f}")
+
+
+# Entries of one magnitude that is not a power of two: float32 partial sums lose
+# the same way at every addition, so their error does not average out.
+SUM_SHAPES = [(1, 65536), (65536, 1), (1, 4096), (4096, 1), (16, 4096), (4096, 16), (3, 4095), (31, 2111), (2, 100000)]
+
+
+@pytest.mark.parametrize("shapes,keep", [(SUM_SHAPES, range(len(SUM_SHAPES))),
+                                         # whole steps of 65536 columns, beside many others
+                                         ([(1, 65536), (65536, 1)] * 32, (0, 1, 63))])
+def test_long_side_sums_keep_float64(shapes, keep):
+    # l and r after one step are (1 - mu2) times sums of G^2 over a long and over
+    # a short side.  Rounding: each square (2^-24), the long sums in float64 from
+    # float32 partials over at most 256 columns, 32 rows or, in whole steps past
+    # 16 rows, 32 columns (sums of equal values: at most 3 additions round, 2^-24 each), the
+    # stored float32 (2^-24): 5 * 2^-24 = 3.0e-7 at most.  Float32 over a whole
+    # side of 65536 was 1.2e-6 off.
+    say(f"[short] sums of equal squares over {shapes[:9]}, {len(shapes)} matrices")
+    keep = list(keep)
+    W0 = [wl.weight(83, i, s) for i, s in enumerate(shapes)]
+    rng = np.random.default_rng(83)
+    grads = [[(rng.integers(0, 2, s) * 2 - 1).astype(np.float32) * np.float32(0.0123) for s in shapes]]
+    for variant in ("malt", "malter"):
+        g = run_gpu(shapes, variant, W0, grads, dict(lr=1e-2), collect=keep)[0]
+        o = run_oracle(shapes, variant, W0, grads, dict(lr=1e-2), collect=keep)[0]
+        for k, i in enumerate(keep):
+            s = shapes[i]
+            err = rel_fro(g.l[k], o["l"][k]) if s[0] <= s[1] else rel_fro(g.r[k], o["r"][k])
+            say(f"[short] {variant} {s}: long-side sum rel err {err:.2e}")
+            assert err <= 3.0e-7, f"{variant} {s}: {err:.2e}"
