@@ -40,6 +40,8 @@
  *    anything is enqueued and leave the state untouched.
  *  - One plan must not be used from two threads at once, and two steps of
  *    one plan must be enqueued on the same stream (they share the workspace).
+ *  - A gradient may overlap another matrix's parameter: a step reads every
+ *    gradient before it writes any parameter.
  *  - NaN/Inf in gradients propagate; they are not checked.
  *  - Return codes are malt_status_t; malt_last_error() gives a message for
  *    the most recent failure on the calling thread.

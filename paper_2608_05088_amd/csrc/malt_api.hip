@@ -693,6 +693,7 @@ struct malt_plan {
   // pointer table last written to the workspace (compared on every step)
   std::vector<PtrPair> cur_ptrs;
   bool ptrs_valid = false;
+  bool defer_w = false;   // of that table: a gradient overlaps another matrix's W that a whole step writes
   // workspace in the library's static scratch array of device `device`,
   // valid while that device's scratch generation still equals scratch_gen
   bool scratch = false;
@@ -1333,15 +1334,28 @@ malt_status_t malt_step(malt_plan_t* p, float* const* params, const float* const
       return fail(MALT_ERR_ALIAS, "matrix %d: param/grad overlaps the state or workspace", i);
     if (p->cur_ptrs[i].W != params[i] || p->cur_ptrs[i].G != grads[i]) changed = true;
   }
+  bool defer_w = false;
   if (changed && n > 1) {
     // Parameters are updated in place: they must not overlap one another.
-    std::vector<std::pair<uintptr_t, size_t>> rs(n);
-    for (int32_t i = 0; i < n; ++i)
-      rs[i] = {reinterpret_cast<uintptr_t>(params[i]), size_t(p->shapes[i].rows) * p->shapes[i].cols * 4};
+    auto bytes_of = [&](int32_t i) { return size_t(p->shapes[i].rows) * p->shapes[i].cols * 4; };
+    std::vector<std::pair<uintptr_t, int32_t>> rs(n);
+    for (int32_t i = 0; i < n; ++i) rs[i] = {reinterpret_cast<uintptr_t>(params[i]), i};
     std::sort(rs.begin(), rs.end());
     for (int32_t i = 1; i < n; ++i)
-      if (rs[i - 1].first + rs[i - 1].second > rs[i].first)
+      if (rs[i - 1].first + bytes_of(rs[i - 1].second) > rs[i].first)
         return fail(MALT_ERR_ALIAS, "two parameter matrices overlap");
+    // A gradient may overlap another matrix's parameter: every gradient is read
+    // before any W is written.  Whole steps come first in a step and write their W
+    // at its end only in that case.
+    for (int32_t i = 0; i < n && p->L.n_tiny > 0 && !defer_w; ++i) {
+      const uintptr_t g0 = reinterpret_cast<uintptr_t>(grads[i]), g1 = g0 + bytes_of(i);
+      auto at = std::lower_bound(rs.begin(), rs.end(), std::make_pair(g1, int32_t(0)));   // the first W from g1 on
+      while (at != rs.begin() && !defer_w) {
+        --at;
+        if (at->first + bytes_of(at->second) <= g0) break;   // nor does any W before it reach g0
+        defer_w = p->L.mats[at->second].tiny;
+      }
+    }
   }
 
   if (p->scratch && !scratch_current(p->device, p->scratch_gen))
@@ -1377,6 +1391,7 @@ malt_status_t malt_step(malt_plan_t* p, float* const* params, const float* const
     if (e != hipSuccess) { p->ptrs_valid = false; return hip_fail(e, "uploading pointer table"); }
     p->cur_ptrs = next;
     p->ptrs_valid = true;
+    p->defer_w = defer_w;
   }
 
   const int64_t t = p->t + 1;
@@ -1420,6 +1435,7 @@ malt_status_t malt_step(malt_plan_t* p, float* const* params, const float* const
     sa.span = small_span(hp->ns_a);
     sa.norms = 0;
     sa.first = sa.last = 1;
+    sa.defer = p->defer_w;
     if (p->L.n_tiny > 0) {   // matrices whose step is one workgroup's
       sa.e = ea;
       sa.e.tiles = tiles_at(p->L.ws_t_tiny); sa.e.ntiles = int32_t(p->L.n_tiny);
@@ -1481,6 +1497,10 @@ malt_status_t malt_step(malt_plan_t* p, float* const* params, const float* const
       if (!p->L.fuse_graft) MALT_LAUNCH(7, launch_graft_scalars(ea, n, s));
       ea.tiles = tiles_at(p->L.ws_t_ew); ea.ntiles = int32_t(p->L.n_ew);
       MALT_LAUNCH(8, launch_backmap_write(ea, p->L.fuse_graft, s));
+    }
+    if (p->L.n_tiny > 0 && p->defer_w) {
+      ea.tiles = tiles_at(p->L.ws_t_tiny); ea.ntiles = int32_t(p->L.n_tiny);
+      MALT_LAUNCH(8, launch_tiny_write(ea, s));
     }
     if ((e = mark(-1)) != hipSuccess) goto hip_error;
   }

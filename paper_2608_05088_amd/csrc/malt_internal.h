@@ -179,6 +179,7 @@ struct SmallArgs {
   int32_t span;          // iterations before A is formed from X again (small_span)
   int32_t norms;         // the first iteration kernel also forms the norm scalars
   int32_t first, last;   // three launches: X is L M R; O follows
+  int32_t defer;         // whole step: all but W, which launch_tiny_write does
 };
 
 struct NsArgs {
@@ -223,6 +224,7 @@ int small_span(double a);
 hipError_t tiny_step_setup(bool malter);
 hipError_t launch_small_ns(const SmallArgs& a, int phase, hipStream_t s);
 hipError_t launch_tiny_step(const SmallArgs& a, hipStream_t s);
+hipError_t launch_tiny_write(const EwArgs& a, hipStream_t s);
 
 // One matrix's descriptor fields and caller pointers, as the tile passes use
 // them, read in one place before any branch: the compiler then issues them as

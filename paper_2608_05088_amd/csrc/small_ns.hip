@@ -438,7 +438,8 @@ __device__ __forceinline__ double tiny_reduce(F (&x)[N], int lane) {
 // waiting for them does not wait for that round's stores.  us of a step: 16 x
 // 1024 27 (55 with a bounds branch per row, 39 with clamped positions only),
 // 3072 x 16 62, 32 x 1024 63, 8 x 4096 54.
-// LONG: more than ns.span iterations (see the top of this file).
+// LONG: also more than ns.span iterations (see the top of this file), and steps
+// that leave W to tiny_write_kernel.
 template <bool MALTER, int MC, bool FULL, bool LONG>
 __device__ __forceinline__ void tiny_step(const SmallArgs& ns, int mat, TinyLds& S) {
   constexpr int NB = SmDim<MC>::NB;
@@ -615,9 +616,20 @@ __device__ __forceinline__ void tiny_step(const SmallArgs& ns, int mat, TinyLds&
     sm_operand<MC>(sm_iterate<TY_NW>(S.core, NB, ns, steps), sg, pa, lane);
     __syncthreads();   // P is in registers; the staging rows are free again
   };
-  iterate(sigma, LONG ? ns.span : ns.steps);
+  iterate(sigma, LONG ? min(ns.steps, ns.span) : ns.steps);
 
   MALT_GLOBAL float* const X = sm_iterate_x(d, a.o_parity);
+  // This lane's column of L M R, or of the float32 iterate; cf its column factor.
+  auto long_column = [&](bool first, float cf, float (&x)[MC]) {
+    if (first) {
+      tiny_load<MC, FULL>(v.M, t, x);
+      tiny_mask<MC, FULL>(t, x);
+      tiny_own<MC, FULL>(buf, t, x);
+      scale(x, cf);
+    } else {
+      tiny_load_x<MC>(X, t, np, x);
+    }
+  };
   if constexpr (LONG) {
     // X = P X (P L M R the first time, with sigma in P) and its Gram, until at
     // most span iterations are left.
@@ -628,14 +640,7 @@ __device__ __forceinline__ void tiny_step(const SmallArgs& ns, int mat, TinyLds&
       for (t.c0 = wave * 64; t.c0 < nc; t.c0 += TINY_THREADS) {
         const int c = t.c0 + lane;
         float x[MC];
-        if (left == ns.steps - ns.span) {
-          tiny_load<MC, FULL>(v.M, t, x);
-          tiny_mask<MC, FULL>(t, x);
-          tiny_own<MC, FULL>(buf, t, x);
-          scale(x, c < nc ? cinv[c] : 0.f);
-        } else {
-          tiny_load_x<MC>(X, t, np, x);
-        }
+        long_column(left == ns.steps - ns.span, c < nc ? cinv[c] : 0.f, x);
         sm_advance<MC>(buf, pa, c < nc, mc, lane, x);
 #pragma unroll
         for (int i = 0; i < MC; ++i)
@@ -658,7 +663,7 @@ __device__ __forceinline__ void tiny_step(const SmallArgs& ns, int mat, TinyLds&
     float x[MC], cf;
     if constexpr (LONG) {
       cf = c < nc ? cinv[c] : 0.f;
-      tiny_load_x<MC>(X, t, np, x);
+      long_column(ns.steps <= ns.span, cf, x);
     } else {
       copy(x, xn);
       cf = FULL || c < nc ? cn : 0.f;
@@ -684,6 +689,8 @@ __device__ __forceinline__ void tiny_step(const SmallArgs& ns, int mat, TinyLds&
     scal[SC_GRAFT] = graft;
     scal[SC_COEF] = coef_d;
   }
+
+  if (LONG && ns.defer) return;
 
   // W <- decay W - coef L O R.
   const float coef = (float)coef_d;
@@ -739,11 +746,24 @@ __global__ __launch_bounds__(TINY_THREADS) void tiny_step_kernel(SmallArgs ns) {
   }
 }
 
-// The same for more than ns.span iterations; one instance for every m'.
+// The LONG steps; one instance for every m'.
 template <bool MALTER>
 __global__ __launch_bounds__(TINY_THREADS) void tiny_long_step_kernel(SmallArgs ns) {
   extern __shared__ __attribute__((aligned(16))) char lds[];
   tiny_step<MALTER, SM_M, false, true>(ns, ns.e.tiles[blockIdx.x].mat, *reinterpret_cast<TinyLds*>(lds));
+}
+
+// The update of W by itself, after every gradient of the step has been read: for
+// a set in which another matrix's gradient overlaps a W of this route.
+__global__ __launch_bounds__(TINY_THREADS) void tiny_write_kernel(EwArgs a) {
+  const Tile t = a.tiles[blockIdx.x];
+  const EwView v = ew_view(a, t.mat);
+  const float coef = (float)v.scal[SC_COEF];
+  for (int e = threadIdx.x; e < v.m * v.n; e += TINY_THREADS) {
+    const int i = e / v.n, j = e % v.n;
+    const float o = bf16_lo(v.O[v.tall ? (size_t)j * v.np + i : (size_t)i * v.np + j]);
+    v.W[e] = a.decay * v.W[e] - coef * v.Lv[i] * o * v.Rv[j];
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -897,13 +917,19 @@ hipError_t tiny_step_setup(bool malter) {
 hipError_t launch_tiny_step(const SmallArgs& a, hipStream_t s) {
   if (a.e.ntiles == 0) return hipSuccess;
   const dim3 grid(a.e.ntiles), block(TINY_THREADS);
-  if (a.steps > a.span) {
+  if (a.steps > a.span || a.defer) {
     if (a.e.malter) hipLaunchKernelGGL(tiny_long_step_kernel<true>, grid, block, sizeof(TinyLds), s, a);
     else hipLaunchKernelGGL(tiny_long_step_kernel<false>, grid, block, sizeof(TinyLds), s, a);
   } else {
     if (a.e.malter) hipLaunchKernelGGL(tiny_step_kernel<true>, grid, block, sizeof(TinyLds), s, a);
     else hipLaunchKernelGGL(tiny_step_kernel<false>, grid, block, sizeof(TinyLds), s, a);
   }
+  return hipGetLastError();
+}
+
+hipError_t launch_tiny_write(const EwArgs& a, hipStream_t s) {
+  if (a.ntiles == 0) return hipSuccess;
+  hipLaunchKernelGGL(tiny_write_kernel, dim3(a.ntiles), dim3(TINY_THREADS), 0, s, a);
   return hipGetLastError();
 }
 

@@ -1,7 +1,8 @@
 """Matrices with a short side of at most 32 (Newton-Schulz in the Gram space, in
 float64) where that form can go wrong: gradients of low rank over many
 iterations, and sums over a long side, on both routes (whole step in one
-workgroup, three launches)."""
+workgroup, three launches); gradients that overlap a W which a whole step
+writes."""
 import numpy as np
 import pytest
 
@@ -105,3 +106,51 @@ def test_long_side_sums_keep_float64(shapes, keep):
             err = rel_fro(g.l[k], o["l"][k]) if s[0] <= s[1] else rel_fro(g.r[k], o["r"][k])
             say(f"[short] {variant} {s}: long-side sum rel err {err:.2e}")
             assert err <= 3.0e-7, f"{variant} {s}: {err:.2e}"
+
+
+@pytest.mark.parametrize("variant,ns_steps", [("malt", 5), ("malter", 2), ("malter", 12)])
+def test_gradients_overlapping_another_matrix_parameter(variant, ns_steps):
+    # Accepted, and every gradient is read before any W is written: the gradient of
+    # a whole-step matrix and of a matrix on the matrix cores that lie in the W of
+    # whole-step ones.  The same steps with copies of those gradients give the same
+    # M (up to the contraction of one expression), l, r and nu (sums in another
+    # order: 3e-7) and update (O's last bf16 bit may turn: 4e-3).  A gradient read
+    # after its W had been written would be off by about 1e-2, and M with it.
+    import torch
+    shapes = [(16, 1024), (1024, 16), (256, 512), (16, 1024), (9, 65)]
+    assert [r["route"] for r in lm.plan_routes(shapes, variant)] == [2, 2, 0, 2, 2]
+    say(f"[short] overlapping gradients {shapes} {variant} ns_steps={ns_steps} x2, then apart")
+    hp = lm.make_hparams(lr=1e-2, ns_steps=ns_steps, weight_decay=0.1)
+    results = []
+    for overlap in (True, False):
+        gen = torch.Generator(device="cuda").manual_seed(5)
+        flat = torch.randn(200000, device="cuda", generator=gen) * 0.02
+        W = [torch.randn(s, device="cuda", generator=gen) * 0.02 for s in shapes]
+        W[1] = flat[:16384].view(1024, 16)           # G[2] begins inside it
+        G = [torch.randn(s, device="cuda", generator=gen) * 0.01 for s in shapes]
+        plan = lm.Plan(shapes, variant)
+        steps = []
+        for t in range(3):
+            g = list(G)
+            if t < 2:
+                g[0], g[2] = W[3], flat[8192:8192 + 256 * 512].view(256, 512)
+                if not overlap:
+                    g[0], g[2] = g[0].clone(), g[2].clone()
+            before = [w.clone() for w in W]
+            plan.step(W, g, hp)
+            torch.cuda.synchronize()
+            views = [plan.state_views(i) for i in range(len(shapes))]
+            steps.append(([w - b for w, b in zip(W, before)], [[x.clone() for x in v if x is not None] for v in views]))
+        results.append(steps)
+        plan.close()
+    err = lambda x, y: float((x.double() - y.double()).norm() / y.double().norm())
+    for t, ((da, sa), (db, sb)) in enumerate(zip(*results)):
+        for i, s in enumerate(shapes):
+            where = f"step {t + 1} matrix {i} {s}"
+            # Later gradients are the W that the first step left: 4e-3 of an update
+            # of about 1e-2 |W|.
+            tol = 1e-6 if t == 0 else 1e-4
+            worst = max(err(x, y) for x, y in zip(sa[i], sb[i]))
+            say(f"[short] overlap {where}: state {worst:.2e} update {err(da[i], db[i]):.2e}")
+            assert worst <= tol, f"{where}: state {worst:.2e}"
+            assert err(da[i], db[i]) <= 4e-3, f"{where}: update {err(da[i], db[i]):.2e}"
