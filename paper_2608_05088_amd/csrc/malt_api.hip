@@ -487,43 +487,47 @@ void fuse_scalars(Layout& L) {
   }
 }
 
-// Which matrices with more than TINY_COLS columns take their whole step in one
-// workgroup.  That workgroup's time grows with its columns, however few matrices
-// there are; the three-launch route's with the columns of all, its passes
-// covering 256 padded rows.  Measured, us per step of one matrix, of 16 and of 64
-// (whole step | three launches): 1 x 65536 864 | 63, 3 x 8192 125 | 50, 125 | 70,
-// 129 | 165; 8000 x 7 141 | 93 (of 8), 147 | 362; 3 x 5000 83 | 58 (of 8), 86 |
-// 128.  The estimates below, in us, fit these within a tenth.  The matrices longer
-// than some length take three launches; the length is the one with the least sum.
+// Which of the matrices that fit take their whole step in one workgroup.  That
+// workgroup's time grows with its columns, however few matrices there are; the
+// three-launch route's with the columns of all, its passes covering 256 padded
+// rows.  Measured, us per step (whole step | three launches): 1 x 65536 864 | 63,
+// 32 x 2048 100 | 65, 1669 x 32 144 | 73, 16 x 2048 45 | 57; 3 x 8192, 16 of them
+// 125 | 70, 64 of them 129 | 165; 8000 x 7, 8 of them 141 | 93, 64 of them 147 |
+// 362; 64 of 32 x 2048 110 | 119.  The estimates below, in us, fit these within
+// about a tenth.  The matrices with the longest whole steps take three launches,
+// as many of them as make the sum least, if that gains a tenth.
 void choose_whole_steps(Layout& L) {
-  auto whole = [](const MatPlan& q) { return 15.0 + 13.3 * double(q.nc) / 1024; };
-  auto three = [](const MatPlan& q) { return (q.tall ? 0.55 : 0.23) * double(q.nc) / 1024; };
-  std::vector<int32_t> lng;
-  double rest = 0.0;   // the longest whole step of the others
+  auto ragged = [](const MatPlan& q) { return q.mc != q.tiny_rows || q.nc % 64 != 0; };
+  auto whole = [&](const MatPlan& q) {
+    const double k = double(q.nc) / 1024;
+    if (q.tiny_rows == 8) return 14.0 + (ragged(q) ? 13.3 : 10.7) * k;
+    if (q.tiny_rows == 16) return 12.0 + (ragged(q) ? 26.0 : 16.7) * k;
+    return ragged(q) ? 40.0 + (q.tall ? 60.0 : 47.0) * k : 26.0 + 37.0 * k;
+  };
+  auto launches = [&](const MatPlan& q) { return 46.0 + 0.6 * q.mc + (q.mc > 16 && ragged(q) ? 20.0 : 0.0); };
+  auto passes = [](const MatPlan& q) { return (q.tall ? 0.55 + 0.011 * q.mc : 0.23 + 0.006 * q.mc) * double(q.nc) / 1024; };
+  std::vector<std::pair<double, int32_t>> order;   // by whole step, longest first
+  double paid = 0.0;   // launches that the set has anyway, for matrices too large for a workgroup
   for (size_t i = 0; i < L.mats.size(); ++i) {
     const MatPlan& q = L.mats[i];
-    if (!q.tiny) continue;
-    if (q.nc > TINY_COLS) lng.push_back(int32_t(i));
-    else rest = std::max(rest, whole(q));
+    if (q.tiny) order.push_back({-whole(q), int32_t(i)});
+    else if (q.small) paid = std::max(paid, launches(q));
   }
-  std::sort(lng.begin(), lng.end(), [&](int32_t a, int32_t b) {
-    return L.mats[a].nc != L.mats[b].nc ? L.mats[a].nc > L.mats[b].nc : a < b;
-  });
-  double cost = 45.0, best = lng.empty() ? 0.0 : whole(L.mats[lng[0]]);   // three launches; the least sum
-  int64_t cut = 0;   // columns from which on a matrix takes three launches; 0: none
-  for (size_t k = 0; k < lng.size(); ++k) {
-    const MatPlan& q = L.mats[lng[k]];
-    cost += three(q);
-    if (k + 1 < lng.size() && L.mats[lng[k + 1]].nc == q.nc) continue;
-    const double sum = cost + (k + 1 < lng.size() ? whole(L.mats[lng[k + 1]]) : rest);
-    if (sum < best) {
-      best = sum;
-      cut = q.nc;
+  if (order.empty()) return;
+  std::sort(order.begin(), order.end());
+  double best = 0.9 * -order[0].first, fixed = paid, sum = 0.0;
+  size_t cut = 0;
+  for (size_t k = 0; k < order.size(); ++k) {
+    const MatPlan& q = L.mats[order[k].second];
+    fixed = std::max(fixed, launches(q));
+    sum += passes(q);
+    const double t = fixed - paid + sum + (k + 1 < order.size() ? -order[k + 1].first : 0.0);
+    if (t < best) {
+      best = t;
+      cut = k + 1;
     }
   }
-  if (cut > 0)
-    for (int32_t i : lng)
-      if (L.mats[i].nc >= cut) L.mats[i].tiny = false;
+  for (size_t k = 0; k < cut; ++k) L.mats[order[k].second].tiny = false;
 }
 
 Layout make_layout(const malt_shape_t* shapes, int32_t n, malt_variant_t variant, Lists& T, bool small_tiles = true) {

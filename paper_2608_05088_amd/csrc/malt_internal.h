@@ -42,15 +42,13 @@ constexpr int FIN_W = 64;
 constexpr int FIN_W_LONG = 8;
 constexpr int FIN_LONG = 512;
 // Matrices whose short side is at most this run Newton-Schulz in the Gram space
-// in float64 (small_ns.hip).  Those of at most TINY_ELEMS elements and TINY_COLS
-// columns take their whole step in one workgroup, longer ones where the set has
-// enough of them (choose_whole_steps); the others a Gram over chunks of at least SM_CH_G
+// in float64 (small_ns.hip).  Those of at most TINY_ELEMS elements can take their
+// whole step in one workgroup (choose_whole_steps); the others take a Gram over chunks of at least SM_CH_G
 // columns, at most SM_CHUNKS of them, and the final product over SM_CH_U columns
 // (one per thread).
 constexpr int NS_SMALL_MAX = 32;
 constexpr int TINY_THREADS = 512;
 constexpr int TINY_ELEMS = 65536;
-constexpr int TINY_COLS = 4096;
 constexpr int SM_CH_G = 1024;
 constexpr int SM_CHUNKS = 128;
 constexpr int SM_CH_U = 256;

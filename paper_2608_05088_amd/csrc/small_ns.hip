@@ -21,8 +21,8 @@
 // final O is rounded to bf16.
 //
 // Two routes:
-//   whole step   a matrix of at most TINY_ELEMS elements (past TINY_COLS columns
-//                only beside many others, choose_whole_steps) takes its whole step
+//   whole step   a matrix of at most TINY_ELEMS elements (of long ones only where
+//                there are many, choose_whole_steps) takes its whole step
 //                in one workgroup (tiny_step_kernel): one launch for all such
 //                matrices of a plan, in place of 21.  What bounds it is the
 //                chain of its phases, and for the larger ones what one CU can

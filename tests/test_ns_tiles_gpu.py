@@ -65,9 +65,9 @@ def test_cubic_iteration_on_256_tiles():
     say(f"[tiles] cubic worst {compare(g, o, 'malt', label='cubic')}")
 
 
-# Short sides: whole rows and rounds of the whole-step workgroup and their
-# remainders, wide and tall; its largest element count and the first past it
-# (three launches), a contraction of several Gram chunks.
+# Short sides in three launches (the large ones of the set take the others along):
+# whole rows and 64-column rounds and their remainders, wide and tall; a
+# contraction of several Gram chunks.  Whole steps: test_short_sides_gpu.py.
 SHORT = [(8, 64), (64, 8), (16, 1024), (1024, 16), (32, 2048), (2048, 32), (9, 65), (63, 7), (1, 64), (1, 1), (31, 513),
          (16, 4096), (16, 4097), (4097, 16), (32, 40000)]
 
@@ -83,18 +83,3 @@ def test_short_side_edges(variant, ns_steps):
     # 4e-3 covers it in norm, in O and in the update.
     worst = compare(g, o, variant, tol_ns=4e-3, label="short")
     say(f"[tiles] short worst {worst}")
-
-
-def test_short_side_sets_of_long_matrices():
-    # Past 4096 columns a matrix takes its whole step in one workgroup only beside
-    # many others: wide, tall and ragged ones, with one that leaves for three
-    # launches.
-    shapes = [(3, 4500), (5000, 2), (13, 4999)] * 20 + [(1, 65536), (16, 1024)]
-    assert [r["route"] for r in lm.plan_routes(shapes)] == [2] * 60 + [1, 2]
-    keep = [0, 1, 2, 59, 60, 61]
-    say(f"[tiles] long short sides {len(shapes)} matrices malter x2")
-    W0 = [wl.weight(82, i, s) for i, s in enumerate(shapes)]
-    grads = [[wl.grad(82, t, i, s, "row_loguniform") for i, s in enumerate(shapes)] for t in (1, 2)]
-    g = run_gpu(shapes, "malter", W0, grads, dict(lr=1e-2), collect=keep)
-    o = run_oracle(shapes, "malter", W0, grads, dict(lr=1e-2), collect=keep)
-    say(f"[tiles] long short sides worst {compare(g, o, 'malter', tol_ns=4e-3, label='long short')}")

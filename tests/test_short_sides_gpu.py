@@ -1,12 +1,13 @@
 """Matrices with a short side of at most 32 (Newton-Schulz in the Gram space, in
-float64) where that form can go wrong: gradients of low rank over many
+float64): whole steps against the oracle at the edges of their workgroup; where
+the form can go wrong, gradients of low rank over many
 iterations, and sums over a long side, on both routes (whole step in one
 workgroup, three launches); gradients that overlap a W which a whole step
 writes."""
 import numpy as np
 import pytest
 
-from gpu_harness import run_gpu, run_oracle, say
+from gpu_harness import compare, run_gpu, run_oracle, say
 from oracle import rel_fro
 from paper_2608_05088_amd import libmalt as lm
 from paper_2608_05088_amd import workloads as wl
@@ -22,8 +23,46 @@ def _gpu():
     lm.lib()
 
 
-# Whole step: wide, tall, full, square; three launches: one and several Gram chunks.
-RANK_SHAPES = [(16, 1024), (1024, 16), (32, 2048), (9, 9), (16, 4097), (40000, 20)]
+WHOLE_STEP, THREE_LAUNCHES = 2, 1
+
+
+def _route(shapes, variant, want):
+    assert [r["route"] for r in lm.plan_routes(shapes, variant)] == [want] * len(shapes)
+
+
+# Sets of whole steps: full and ragged rows and rounds of 64 columns, each register
+# size (8, 16, 32 rows), wide and tall, the smallest and the largest.
+WHOLE_SETS = {
+    "edges": [(8, 64), (64, 8), (16, 1024), (1024, 16), (9, 65), (63, 7), (1, 64), (1, 1), (31, 513), (513, 31),
+              (32, 1024), (1024, 32), (5, 512), (17, 1)],
+    "many_32_rows": [(32, 2048), (2048, 32), (2047, 32), (29, 2048)] * 16,
+    "many_16_rows": [(16, 4096), (4096, 16), (15, 4369), (4097, 9)] * 16,
+    "many_long": [(3, 4500), (5000, 2), (7, 4999), (8, 8192)] * 24 + [(16, 1024)],
+    "many_longest": [(1, 65536), (65536, 1)] * 32,
+}
+
+
+@pytest.mark.parametrize("name", sorted(WHOLE_SETS))
+@pytest.mark.parametrize("variant,ns_steps", [("malt", 5), ("malter", 2), ("malter", 9)])
+def test_whole_steps_against_the_oracle(name, variant, ns_steps):
+    # Only the final rounding of O to bf16 (2^-9 per entry at most) is left: 4e-3
+    # covers it in norm, in O and in the update.
+    shapes = WHOLE_SETS[name]
+    _route(shapes, variant, WHOLE_STEP)
+    keep = list(range(len(shapes))) if name == "edges" else [0, 1, 2, 3, len(shapes) - 1]
+    say(f"[short] whole steps {name} {len(shapes)} matrices {variant} ns_steps={ns_steps} x2")
+    W0 = [wl.weight(82, i, s) for i, s in enumerate(shapes)]
+    grads = [[wl.grad(82, t, i, s, "row_loguniform") for i, s in enumerate(shapes)] for t in (1, 2)]
+    hp = dict(lr=1e-2, ns_steps=ns_steps)
+    g = run_gpu(shapes, variant, W0, grads, hp, collect=keep)
+    o = run_oracle(shapes, variant, W0, grads, hp, collect=keep)
+    say(f"[short] whole steps {name} worst {compare(g, o, variant, tol_ns=4e-3, label=name)}")
+
+
+# By route.  Whole steps: wide, tall, full, ragged, square; three launches: one and
+# several Gram chunks.
+RANK_SETS = {WHOLE_STEP: [(16, 1024), (1024, 16), (32, 1024), (9, 9), (513, 31)],
+             THREE_LAUNCHES: [(16, 4097), (40000, 20), (32, 2048), (9, 9)]}
 QUINTIC, CUBIC = (3.4445, -4.7750, 2.0315), (1.5, -0.5, 0.0)
 
 
@@ -44,7 +83,8 @@ def _low_rank(kind, shape, seed):
 
 @pytest.mark.parametrize("abc,sup", [(QUINTIC, 1.2024), (CUBIC, 1.0)])
 @pytest.mark.parametrize("ns_steps", [5, 8, 9, 12, 24, 64])
-def test_low_rank_short_sides_stay_bounded(ns_steps, abc, sup):
+@pytest.mark.parametrize("route", sorted(RANK_SETS))
+def test_low_rank_short_sides_stay_bounded(route, ns_steps, abc, sup):
     # Newton-Schulz maps every singular value of the normalised M~ into [0, sup]
     # at any count (the largest value of the scalar iteration from [0, 1]), so
     # the spectral norm of O exceeds sup by its final rounding only, at most 2^-9
@@ -52,8 +92,9 @@ def test_low_rank_short_sides_stay_bounded(ns_steps, abc, sup):
     # the same interval.  On the range of the gradient O is the oracle's up to
     # that rounding (in emulation the iteration itself adds 7e-8).
     kinds = ("constant", "repeated", "rank1", "rank8")
-    shapes = [s for s in RANK_SHAPES for _ in kinds]
-    say(f"[short] low-rank {kinds} x {RANK_SHAPES} ns_steps={ns_steps} abc={abc}")
+    shapes = [s for s in RANK_SETS[route] for _ in kinds]
+    _route(shapes, "malter", route)
+    say(f"[short] low-rank {kinds} x {RANK_SETS[route]} ns_steps={ns_steps} abc={abc}")
     made = [_low_rank(kinds[i % len(kinds)], s, 100 + i) for i, s in enumerate(shapes)]
     W0 = [wl.weight(84, i, s) for i, s in enumerate(shapes)]
     hp = dict(lr=1e-2, ns_steps=ns_steps, ns_a=abc[0], ns_b=abc[1], ns_c=abc[2])
@@ -83,10 +124,12 @@ def test_low_rank_short_sides_stay_bounded(ns_steps, abc, sup):
 SUM_SHAPES = [(1, 65536), (65536, 1), (1, 4096), (4096, 1), (16, 4096), (4096, 16), (3, 4095), (31, 2111), (2, 100000)]
 
 
-@pytest.mark.parametrize("shapes,keep", [(SUM_SHAPES, range(len(SUM_SHAPES))),
-                                         # whole steps of 65536 columns, beside many others
-                                         ([(1, 65536), (65536, 1)] * 32, (0, 1, 63))])
-def test_long_side_sums_keep_float64(shapes, keep):
+@pytest.mark.parametrize("shapes,keep,route", [
+    (SUM_SHAPES, range(len(SUM_SHAPES)), THREE_LAUNCHES),
+    # whole steps of 65536 columns, and of 16 and 32 rows, beside many others
+    ([(1, 65536), (65536, 1)] * 32, (0, 1, 63), WHOLE_STEP),
+    ([(16, 4096), (4096, 15), (32, 2048), (2048, 31)] * 24, (0, 1, 2, 3), WHOLE_STEP)])
+def test_long_side_sums_keep_float64(shapes, keep, route):
     # l and r after one step are (1 - mu2) times sums of G^2 over a long and over
     # a short side.  Rounding: each square (2^-24), the long sums in float64 from
     # float32 partials over at most 256 columns, 32 rows or, in whole steps past
@@ -94,6 +137,7 @@ def test_long_side_sums_keep_float64(shapes, keep):
     # stored float32 (2^-24): 5 * 2^-24 = 3.0e-7 at most.  Float32 over a whole
     # side of 65536 was 1.2e-6 off.
     say(f"[short] sums of equal squares over {shapes[:9]}, {len(shapes)} matrices")
+    _route(shapes, "malt", route)
     keep = list(keep)
     W0 = [wl.weight(83, i, s) for i, s in enumerate(shapes)]
     rng = np.random.default_rng(83)
