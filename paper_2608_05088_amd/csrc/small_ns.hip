@@ -772,10 +772,12 @@ __global__ __launch_bounds__(TINY_THREADS) void tiny_write_kernel(EwArgs a) {
 constexpr int SL_NW = NTHREADS / 64;
 static_assert(SM_CH_U == NTHREADS, "one column per thread in the product");
 
-// Column c, in the canonical orientation (rows < SM_M), of L M R (first) or of
-// the float32 iterate.
+// Column c, in the canonical orientation (rows < SM_M), of L M R (FIRST) or of
+// the float32 iterate.  (Instances: chosen at run time, the product took 124
+// registers in place of 72.)
+template <bool FIRST>
 __device__ __forceinline__ void sm_column(const MatDesc& d, const SmallArgs& ns, int c, float (&x)[SM_M]) {
-  if (!ns.first) {
+  if constexpr (!FIRST) {
     const MALT_GLOBAL float* const X = sm_iterate_x(d, ns.e.o_parity);
 #pragma unroll
     for (int i = 0; i < SM_M; ++i) x[i] = i < d.mc && c < d.nc ? X[(size_t)i * d.np + c] : 0.f;
@@ -792,6 +794,7 @@ __device__ __forceinline__ void sm_column(const MatDesc& d, const SmallArgs& ns,
   }
 }
 
+template <bool FIRST>
 __global__ __launch_bounds__(NTHREADS) void sm_gram_kernel(SmallArgs ns) {
   __shared__ union { float stage[SL_NW * SM_WAVE]; double red[SL_NW][3][64 * 4]; } S;
   const Tile t = ns.e.tiles[blockIdx.x];   // (mat, chunk, -, -)
@@ -802,7 +805,7 @@ __global__ __launch_bounds__(NTHREADS) void sm_gram_kernel(SmallArgs ns) {
   const int c0 = t.ti * d.sm_chunk, c1 = min(c0 + d.sm_chunk, d.nc);
   for (int c = c0 + wave * 64; c < c1; c += NTHREADS) {
     float x[SM_M];
-    sm_column(d, ns, c + lane < c1 ? c + lane : d.nc, x);
+    sm_column<FIRST>(d, ns, c + lane < c1 ? c + lane : d.nc, x);
     sm_stage<SM_M>(buf, x, lane);
     sm_gram<SM_M>(buf, acc, lane);
   }
@@ -848,6 +851,7 @@ __global__ __launch_bounds__(SM_PART) void sm_iterate_kernel(SmallArgs ns) {
   for (int q = tid; q < SM_M * SM_M; q += SM_PART) gptr(d.Bs)[q] = sg * P[(q / SM_M) * SM_LD + q % SM_M];
 }
 
+template <bool FIRST, bool LAST>
 __global__ __launch_bounds__(NTHREADS) void sm_apply_kernel(SmallArgs ns) {
   __shared__ float stage[SL_NW * SM_WAVE];
   __shared__ double P[SM_M * SM_LD];
@@ -861,11 +865,11 @@ __global__ __launch_bounds__(NTHREADS) void sm_apply_kernel(SmallArgs ns) {
   if (tid < SM_M) rowf[tid] = tid < mc ? gptr(d.tall ? d.Rv : d.Lv)[tid] : 0.f;
   const float cf = c < nc ? gptr(d.tall ? d.Lv : d.Rv)[c] : 0.f;
   float x[SM_M];
-  sm_column(d, ns, c, x);
+  sm_column<FIRST>(d, ns, c, x);
   __syncthreads();
   double pa[2][8], o2 = 0.0, d2 = 0.0;
   sm_operand<SM_M>(P, 1.0, pa, lane);
-  if (!ns.last) {   // X = P X, in place where it came from X
+  if constexpr (!LAST) {   // X = P X, in place where it came from X
     sm_advance<SM_M>(stage + wave * SM_WAVE, pa, c < nc, mc, lane, x);
     MALT_GLOBAL float* const X = sm_iterate_x(d, ns.e.o_parity);
 #pragma unroll
@@ -935,12 +939,19 @@ hipError_t launch_tiny_write(const EwArgs& a, hipStream_t s) {
 
 hipError_t launch_small_ns(const SmallArgs& a, int phase, hipStream_t s) {
   if (a.e.ntiles == 0) return hipSuccess;
-  if (phase == PH_GRAM)
-    hipLaunchKernelGGL(sm_gram_kernel, dim3(a.e.ntiles), dim3(NTHREADS), 0, s, a);
-  else if (phase == PH_POLY)
-    hipLaunchKernelGGL(sm_iterate_kernel, dim3(a.e.ntiles), dim3(SM_PART), 0, s, a);
-  else
-    hipLaunchKernelGGL(sm_apply_kernel, dim3(a.e.ntiles), dim3(NTHREADS), 0, s, a);
+  const dim3 grid(a.e.ntiles), block(NTHREADS);
+  if (phase == PH_POLY) {
+    hipLaunchKernelGGL(sm_iterate_kernel, grid, dim3(SM_PART), 0, s, a);
+  } else if (phase == PH_GRAM) {
+    if (a.first) hipLaunchKernelGGL((sm_gram_kernel<true>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((sm_gram_kernel<false>), grid, block, 0, s, a);
+  } else if (a.first) {
+    if (a.last) hipLaunchKernelGGL((sm_apply_kernel<true, true>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((sm_apply_kernel<true, false>), grid, block, 0, s, a);
+  } else {
+    if (a.last) hipLaunchKernelGGL((sm_apply_kernel<false, true>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((sm_apply_kernel<false, false>), grid, block, 0, s, a);
+  }
   return hipGetLastError();
 }
 
