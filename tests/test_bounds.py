@@ -52,7 +52,7 @@ def test_every_kernel_range_is_inside_its_buffer(L, name, variant):
         assert ei.value.status == lm.MALT_ERR_BOUNDS
         assert "ns_" in str(ei.value)
     else:
-        # Only the fp32 path: no buffer-resource operands to shrink.
+        # Only the float64 Gram space: no buffer-resource operands to shrink.
         assert lm.check_bounds(shapes, variant, shrink_bytes=16) == checked
 
 

@@ -492,7 +492,7 @@ SMALL = [(5, 5), (32, 4000), (4000, 32), (33, 600), (2, 3), (17, 70000), (31, 31
 
 @pytest.mark.parametrize("variant", ["malt", "malter"])
 def test_short_side_up_to_32_runs_in_fp32(variant):
-    # Short side <= 32: Newton-Schulz in fp32 (X, A, B' never rounded), so with
+    # Short side <= 32: Newton-Schulz in float64 on the Gram matrix, so with
     # rows scaled over three decades (a spread spectrum the quintic does not
     # flatten in five steps) the only bf16 rounding left is the final O's.
     # (33, 600) sits just past the boundary, on the matrix-core path.
@@ -507,7 +507,7 @@ def test_short_side_up_to_32_runs_in_fp32(variant):
         for k, s in enumerate(SMALL):
             if min(s) <= 32:
                 err = rel_fro(g[t].O[k], o[t]["inter"][k].O)
-                assert err <= 4e-3, f"step {t + 1} {s}: O rel err {err:.3e} (fp32 path)"
+                assert err <= 4e-3, f"step {t + 1} {s}: O rel err {err:.3e} (float64 Gram space)"
     say(f"[parity] small worst {worst}")
 
 

@@ -1,9 +1,11 @@
 """The routes a plan chooses for its matrices (host code, no GPU): which short
-sides take their whole step in one workgroup."""
+sides take their whole step in one workgroup, and that the sets of the GPU tests
+of the tile edges still reach the edges they are there for."""
 import os
 
 import pytest
 
+import test_ns_tiles_gpu as tiles
 from paper_2608_05088_amd import libmalt as lm
 
 MATRIX_CORES, THREE_LAUNCHES, WHOLE_STEP = 0, 1, 2
@@ -43,6 +45,11 @@ def test_whole_step_only_where_it_is_the_shorter(shapes, want):
     for variant in ("malt", "malter"):
         assert _routes(shapes, variant) == want
         assert lm.check_bounds(shapes, variant) > 0
+
+
+@pytest.mark.parametrize("name", sorted(tiles.CASES))
+def test_tile_cases_reach_their_edges(name):
+    tiles.check_edges(name)
 
 
 def test_routes_reject_bad_arguments(L):
