@@ -267,10 +267,10 @@ void build_tiles(const Layout& L, Lists& O) {
 // h: added when one round of tiles fills the chip, in part before that.
 // Measured (us per launch, 64 / 128 / 256 tiles): a GPT-2 Small block, Gram 16 /
 // 35 / 60, polynomial 9 / 15 / 26, update 24 / 24 / 22; the 48 matrices of
-// GPT-2 Small, 119 / 91 / 78, 45 / 40 / 57, 260 / 180 / 130.  Over 22 sets from
-// one 576 x 1984 to 24 768-wide matrices the step with the chosen edges was 0.59
-// to 1.01 of the best of the three edges used throughout (one at 1.15), and
-// never behind 256.
+// GPT-2 Small, 119 / 91 / 78, 45 / 40 / 57, 260 / 180 / 130.  Over 25 sets from
+// one 256 x 512 to 124 matrices (profiles/tile_choice.md) the step with the chosen
+// edges was 0.90 to 1.03 of the best of the three edges used throughout (1.15 for
+// twenty GPT-2 blocks of width 300), and 0.32 to 1.01 of 256 throughout.
 // ---------------------------------------------------------------------------
 struct TileCost {
   double a, f, b, g, h;

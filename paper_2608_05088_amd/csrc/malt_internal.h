@@ -34,7 +34,8 @@ constexpr int NS_BK = 64;
 // pair (hi, lo = bf16(B - hi)) into the update product: with few singular
 // values the rounding of the small m' x m' polynomial is not averaged away.
 constexpr int NS_SPLIT_MAX = 128;
-// Threads of every workgroup.
+// Threads of a workgroup of the finalise, scalar, zero-fill and condition-number
+// kernels and of the short sides' Gram and product.
 constexpr int NTHREADS = 256;
 // Preconditioner finalise: rows or columns per workgroup, NTHREADS / FIN_W
 // threads each; FIN_W_LONG of them where each has more than FIN_LONG partials.

@@ -6,8 +6,10 @@
 //               fixed order, rounds once and mirrors
 //   Polynomial  B' = a I + b A + c A A^T   (upper tiles, mirrored)
 //   Update      X' = s B' X, as C^T = X^T B'^T blocks
-// Same operands, instruction (v_mfma_f32_16x16x32_bf16), accumulation order in
-// k and rounding as the 256-tile kernels.  One workgroup of 4 waves per tile,
+// Same operands, instruction (v_mfma_f32_16x16x32_bf16) and roundings to bf16 as
+// the 256-tile kernels, and the same accumulation order in k except in the
+// polynomial: b A is added in fp32 after the sum here, where the 256-tile kernel
+// adds (b / c) A within it (c != 0).  One workgroup of 4 waves per tile,
 // two or three workgroups per CU, so one tile's prologue and epilogue run
 // beside another's main loop.
 //
@@ -18,8 +20,8 @@
 // flop, and a CU takes about 28 and 20 B/clk of them (64-tile update of 96
 // GPT-2 Medium matrices 1130 us, without its MFMAs 1270; without its loads
 // 830).  Measured against the 256-tile kernels alone, us per step: one 256 x 512
-// matrix 216 -> 83; one GPT-2 Small block (MALTER) 608 -> 311; eight ragged
-// matrices 787 -> 346; GPT-2 Small with its embeddings, whose 50257 x 768 Gram
+// matrix 216 -> 83; one GPT-2 Small block (MALTER) 608 -> 302; eight ragged
+// matrices 787 -> 246; GPT-2 Small with its embeddings, whose 50257 x 768 Gram
 // was 6 tiles of 788 stages, 6375 -> 2720.
 #include "ns_common.h"
 
@@ -167,7 +169,8 @@ void ns_mid_sym_kernel(NsArgs args) {
   bf16_t* const out = poly ? Bm : Am;
   const int ldo = lo_off ? 2 * mp : mp;
   if (poly && diag && t.ti == dm / T - 1) {
-    // B' = a I on the padding past the last tile.
+    // B' = a I on the padding past the last tile, which no kernel reads: the
+    // documented B' of malt_debug_layout, padded to whole 256-tiles.
     const uint32_t h = pack_bf16x2(args.a, 0.f);
     const uint32_t l = pack_bf16x2(args.a - bf16_lo(h), 0.f);
     for (int r = dm + tid; r < mp; r += G::NT) {

@@ -31,7 +31,7 @@
 //                a Gram over column chunks, one workgroup per matrix for the
 //                iteration, and the product with P over column chunks.
 // Measured (us per step): one 5 x 5 matrix 108 -> 16; 96 matrices of rank 16
-// (16 x 1024, 1024 x 16, 3072 x 16) 580 -> 107, of which the GPU 65.
+// (16 x 1024, 1024 x 16, 3072 x 16) 580 -> 76, of which the GPU 65.
 #include <type_traits>
 
 #include "malt_internal.h"
