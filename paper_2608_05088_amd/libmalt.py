@@ -252,8 +252,12 @@ class Plan:
         # of the time of a test per tensor: 96 matrices 105 -> 70 us a step).
         params, grads = list(params), list(grads)
         for what, xs in (("param", params), ("grad", grads)):
-            if (list(map(_TENSOR_FIELDS, xs)) != self._expected
-                    or not all(map(torch.Tensor.is_contiguous, xs))):
+            try:
+                same = (list(map(_TENSOR_FIELDS, xs)) == self._expected
+                        and all(map(torch.Tensor.is_contiguous, xs)))
+            except TypeError:   # objects that are no tensors but behave as one: asked one by one
+                same = False
+            if not same:
                 for i, x in enumerate(xs):
                     if (x.dtype != torch.float32 or not x.is_contiguous() or x.device != self.device
                             or tuple(x.shape) != self.shapes[i]):

@@ -152,6 +152,34 @@ def test_binding_rejects_tensors_the_c_abi_cannot_check():
     assert plan.t == 1
 
 
+def test_binding_accepts_objects_that_behave_as_tensors():
+    # step() asks dtype, device, shape, is_contiguous() and data_ptr() of each
+    # parameter and gradient; an object that wraps a tensor answers them.
+    import torch
+
+    class Wrapped:
+        def __init__(self, t):
+            self.t = t
+
+        def __getattr__(self, name):
+            return getattr(self.t, name)
+
+    shapes = [(8, 70), (64, 40)]
+    out = []
+    for wrap in (lambda t: t, Wrapped):
+        plan = lm.Plan(shapes, "malt")
+        W = to_dev([wl.weight(95, i, s) for i, s in enumerate(shapes)])
+        G = to_dev([wl.grad(95, 1, i, s) for i, s in enumerate(shapes)])
+        plan.step([wrap(w) for w in W], [wrap(g) for g in G])
+        torch.cuda.synchronize()
+        out.append(W)
+        with pytest.raises(ValueError, match="matrix 1: grad"):
+            plan.step([wrap(w) for w in W], [wrap(G[0]), wrap(G[1].half())])
+        plan.close()
+    for a, b in zip(*out):
+        assert torch.equal(a, b)
+
+
 def test_non_finite_gradient_stays_in_its_matrix():
     """NaN/Inf propagate without checks, but only inside the matrix that has
     them: every other matrix of the grouped step is bitwise the same as in a
