@@ -504,7 +504,7 @@ void choose_whole_steps(Layout& L) {
     if (q.tiny_rows == 16) return 12.0 + (ragged(q) ? 26.0 : 16.7) * k;
     return ragged(q) ? 40.0 + (q.tall ? 60.0 : 47.0) * k : 26.0 + 37.0 * k;
   };
-  auto launches = [&](const MatPlan& q) { return 46.0 + 0.6 * q.mc + (q.mc > 16 && ragged(q) ? 20.0 : 0.0); };
+  auto launches = [&](const MatPlan& q) { return 46.0 + 0.6 * q.mc + (q.mc > 16 && ragged(q) ? (q.tall ? 3.0 : 20.0) : 0.0); };
   auto passes = [](const MatPlan& q) { return (q.tall ? 0.55 + 0.011 * q.mc : 0.23 + 0.006 * q.mc) * double(q.nc) / 1024; };
   std::vector<std::pair<double, int32_t>> order;   // by whole step, longest first
   double paid = 0.0;   // launches that the set has anyway, for matrices too large for a workgroup
