@@ -21,7 +21,7 @@
 // GPT-2 Medium matrices 1130 us, without its MFMAs 1270; without its loads
 // 830).  Measured against the 256-tile kernels alone, us per step: one 256 x 512
 // matrix 216 -> 83; one GPT-2 Small block (MALTER) 608 -> 302; eight ragged
-// matrices 787 -> 246; GPT-2 Small with its embeddings, whose 50257 x 768 Gram
+// matrices 787 -> 243; GPT-2 Small with its embeddings, whose 50257 x 768 Gram
 // was 6 tiles of 788 stages, 6375 -> 2720.
 #include "ns_common.h"
 
